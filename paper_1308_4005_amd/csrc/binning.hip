@@ -687,7 +687,6 @@ struct LbCharge {
   static constexpr int kThreads = kBlock;
   static __device__ void run(const Args& a, int blk) {
     const int s = blk * kBlock + threadIdx.x;
-    if (s >= a.n + kSortedPad) return;
     double q = 0.0;
     if (s < a.n) {
       const double sg = a.sig_s[s];
@@ -696,9 +695,10 @@ struct LbCharge {
       const int binom = a.k == 0 || a.k == 6 ? 1 : (a.k == 1 || a.k == 5 ? 6 : (a.k == 2 || a.k == 4 ? 15 : 20));
       q = sk * sqrt((double)binom) * a.xs[s].w * 0.125;
     }
-    a.charge[s] = q;
+    if (s < a.n + kSortedPad) a.charge[s] = q;
     if (a.partial) {
-      // per-block sum of the charges (fixed order; padding rows add 0)
+      // per-block sum of the charges (fixed order; padding rows and the last
+      // block's threads past them add 0)
       __shared__ double sh[kBlock];
       sh[threadIdx.x] = q;
       __syncthreads();
