@@ -96,6 +96,37 @@ struct Repulsion {
   double rc;
 };
 
+hipError_t ensure_side(mls_plan_s* P) {
+  hipError_t e = hipSuccess;
+  if (!P->side) {
+    if ((e = hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking)) != hipSuccess) return e;
+    if ((e = hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming)) != hipSuccess) return e;
+    e = hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming);
+  }
+  return e;
+}
+
+// Up to kForkAtoms atoms the local part and the grid chain run one after the
+// other on the caller's stream: the local part, its rows dealt to eight waves
+// per 64 targets, is then shorter than what the second stream costs (two
+// events and two waits: about 25 us of host time per call and 10 us on the
+// device).  FP64 evaluation in one stream / two: 1000 atoms 80 / 88 us, 4000
+// atoms 107 / 110, 32,000 atoms 125 / 128, 64,000 atoms 148 / 138.
+constexpr int64_t kForkAtoms = 32768;
+bool forks(const mls_plan_s* P, int64_t n) { return !P->serial && n > kForkAtoms; }
+
+// The grid chain's stream for an evaluation on stream s: the plan's second
+// one, started after what s holds so far, or s itself; and back again.
+hipError_t fork_chain(mls_plan_s* P, int n, hipStream_t s, hipStream_t& g) {
+  g = s;
+  if (!forks(P, n)) return hipSuccess;
+  hipError_t e = ensure_side(P);
+  if (e == hipSuccess) e = hipEventRecord(P->ev_fork, s);
+  if (e == hipSuccess) e = hipStreamWaitEvent(P->side, P->ev_fork, 0);
+  if (e == hipSuccess) g = P->side;
+  return e;
+}
+
 // mls_evaluate, optionally with the repulsion (rep non-null) run after the
 // local part on the caller's stream and added in the interpolation.
 // binning of an evaluation: a fresh one, one that records the positions
@@ -133,14 +164,10 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   }
   auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev[k], s) : hipSuccess; };
   // with per-stage timing every stage runs in order on the caller's stream;
-  // otherwise the grid chain runs on the plan's second stream, concurrently
-  // with the local part
-  const bool fork = !ev && !P->serial;
-  if (fork && !P->side) {
-    HIP_TRY(hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking), "hipStreamCreateWithFlags");
-    HIP_TRY(hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
-    HIP_TRY(hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
-  }
+  // otherwise (beyond kForkAtoms) the grid chain runs on the plan's second
+  // stream, concurrently with the local part
+  const bool fork = !ev && forks(P, n);
+  if (fork) HIP_TRY(ensure_side(P), "second stream");
   const hipStream_t g = fork ? P->side : s;
   HIP_TRY(mark(0), "timing event");
   if (binmode == kBinRecord) {
@@ -167,7 +194,7 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   auto pair = [&]() -> mls_status {
     if (rep) HIP_TRY(launch_rep_gather(P, ni, rep->c12, s), "repulsion");
     bool fused = false;
-    HIP_TRY(launch_pair(P, ni, s, rep ? &prep : nullptr, &fused), "pair kernel");
+    HIP_TRY(launch_pair(P, ni, s, rep ? &prep : nullptr, &fused, !fork), "pair kernel");
     if (rep && !fused) HIP_TRY(launch_repulsion(P, ni, rep->rc, s), "repulsion");
     HIP_TRY(mark(1 + MLS_T_PAIR), "timing event");
     return MLS_OK;
@@ -207,7 +234,7 @@ hipError_t evaluate_fast(mls_plan_t P, int n, const double* pos, const double* c
   if (e == hipSuccess) e = launch_rep_gather(P, n, rep.c12, s);
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
-  if (e == hipSuccess) e = launch_pair(P, n, s, &prep, &fused);
+  if (e == hipSuccess) e = launch_pair(P, n, s, &prep, &fused, true);
   if (e == hipSuccess && !fused) e = launch_repulsion(P, n, rep.rc, s);
   if (e == hipSuccess) e = launch_local_out(P, n, energy, forces, s);
   return e;
@@ -220,40 +247,24 @@ hipError_t evaluate_fast(mls_plan_t P, int n, const double* pos, const double* c
 hipError_t evaluate_split(mls_plan_t P, int n, const double* pos, const double* c6, const Repulsion& rep,
                           double* energy, double* forces, double* fslow, hipStream_t s) {
   hipError_t e;
-  if (!P->side) {
-    if ((e = hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking)) != hipSuccess) return e;
-    if ((e = hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming)) != hipSuccess) return e;
-    if ((e = hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming)) != hipSuccess) return e;
-  }
-  const hipStream_t g = P->side;
+  hipStream_t g;
   if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_fork, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(g, P->ev_fork, 0)) != hipSuccess) return e;
+  if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
   if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
-  if ((e = launch_pair(P, n, s, &prep, &fused)) != hipSuccess) return e;
+  if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
   if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
   if ((e = launch_stencils(P, g)) != hipSuccess) return e;
   if ((e = launch_coarsest(P, g)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
+  if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
+  if (g != s && (e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
   return launch_interpolate(P, n, energy, fslow, nullptr, nullptr, s, kInterpGridOnly);
-}
-
-hipError_t ensure_side(mls_plan_s* P) {
-  hipError_t e = hipSuccess;
-  if (!P->side) {
-    if ((e = hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking)) != hipSuccess) return e;
-    if ((e = hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming)) != hipSuccess) return e;
-    e = hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming);
-  }
-  return e;
 }
 
 // Multiple time stepping per level, fast and mid forces at the same
@@ -268,22 +279,20 @@ hipError_t evaluate_fast_mid(mls_plan_s* P, int n, const double* pos, const doub
     if ((e = evaluate_fast(P, n, pos, c6, rep, energy, forces, s)) != hipSuccess) return e;
     return launch_zero(fmid, 3 * (int64_t)n, s);
   }
-  if ((e = ensure_side(P)) != hipSuccess) return e;
-  const hipStream_t g = P->side;
+  hipStream_t g;
   if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_fork, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(g, P->ev_fork, 0)) != hipSuccess) return e;
+  if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
   if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
-  if ((e = launch_pair(P, n, s, &prep, &fused)) != hipSuccess) return e;
+  if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
   if ((e = launch_stencils(P, g, 1)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
+  if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
+  if (g != s && (e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
   return launch_interpolate(P, n, energy, fmid, nullptr, nullptr, s, kInterpGridOnly | kInterpLevel1 | kInterpNoSelf);
 }
 
@@ -294,26 +303,24 @@ hipError_t evaluate_fast_mid(mls_plan_s* P, int n, const double* pos, const doub
 hipError_t evaluate_split3(mls_plan_s* P, int n, const double* pos, const double* c6, const Repulsion& rep,
                            double* energy, double* forces, double* fmid, double* fslow, hipStream_t s) {
   hipError_t e;
-  if ((e = ensure_side(P)) != hipSuccess) return e;
-  const hipStream_t g = P->side;
+  hipStream_t g;
   const bool two = P->levels >= 2;
   if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_fork, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(g, P->ev_fork, 0)) != hipSuccess) return e;
+  if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
   if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
-  if ((e = launch_pair(P, n, s, &prep, &fused)) != hipSuccess) return e;
+  if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
   if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
   if ((e = launch_stencils(P, g)) != hipSuccess) return e;
   if ((e = launch_coarsest(P, g)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g, two)) != hipSuccess) return e;
-  if ((e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
+  if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
-  if ((e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
+  if (g != s && (e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
   if (two) {
     e = launch_interpolate(P, n, energy, fmid, nullptr, nullptr, s, kInterpGridOnly | kInterpLevel1 | kInterpNoSelf);
   } else {
@@ -563,21 +570,15 @@ mls_status mls_evaluate_lb(mls_plan_t P, int64_t n, const double* pos, const dou
   P->last_stream = s;
   P->last_n = n;
   const int ni = (int)n;
-  if (!P->side) {
-    HIP_TRY(hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking), "hipStreamCreateWithFlags");
-    HIP_TRY(hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
-    HIP_TRY(hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
-  }
-  const hipStream_t g = P->side;
   // binning with xi = sqrt(2 eps) (the e_i of the pair coefficient) and the
   // sorted sigma
   HIP_TRY(launch_binning_scaled(P, ni, pos, eps, 2.0, s), "binning");
   HIP_TRY(launch_lb_gather(P, ni, sigma, s), "sigma gather");
   // the seven grid chains run on the plan's second stream, concurrently with
   // the local part, and meet it at interpolation
-  HIP_TRY(hipEventRecord(P->ev_fork, s), "fork");
-  HIP_TRY(hipStreamWaitEvent(g, P->ev_fork, 0), "fork");
-  HIP_TRY(launch_pair_lb(P, ni, s), "pair kernel");
+  hipStream_t g;
+  HIP_TRY(fork_chain(P, ni, s, g), "fork");
+  HIP_TRY(launch_pair_lb(P, ni, s, g == s), "pair kernel");
   // grid part once per charge vector (their grids in turn become the plan's
   // working levels; the vectors share one charge buffer, in stream order)
   for (int k = 0; k < 7; ++k) {
@@ -597,8 +598,10 @@ mls_status mls_evaluate_lb(mls_plan_t P, int64_t n, const double* pos, const dou
     std::swap(P->lv, P->lb_lv[k]);
     if (e != hipSuccess) return hip_fail(e, "grid part");
   }
-  HIP_TRY(hipEventRecord(P->ev_join, g), "join");
-  HIP_TRY(hipStreamWaitEvent(s, P->ev_join, 0), "join");
+  if (g != s) {
+    HIP_TRY(hipEventRecord(P->ev_join, g), "join");
+    HIP_TRY(hipStreamWaitEvent(s, P->ev_join, 0), "join");
+  }
   HIP_TRY(launch_interpolate_lb(P, ni, energy, forces, s), "interpolation");
   return MLS_OK;
 }

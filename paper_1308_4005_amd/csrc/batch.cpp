@@ -208,7 +208,11 @@ mls_status build_phases(mls_batch_s* B) {
   // ------------------------------------------------ local part (eq:g_0)
   {
     // boxes share the smoothing function; 0x10 selects the LB source weight
-    const int pv = pair_variant(B->plans[0]) | (lb ? 0x10 : 0);
+    int64_t groups = 0;
+    for (int b = 0; b < nb; ++b)
+      if (B->plans[b]->pair_fast) groups += nblk(n_of(b), 64);
+    const int split = mixed ? (groups <= kSplitGroupsF ? 8 : 1) : pair_split(groups, groups <= kSplitGroupsF);
+    const int pv = pair_variant(B->plans[0]) | (lb ? 0x10 : 0) | (split << 8);
     HostPhase f32 = make_phase<PairArgsF>(BK_PAIR_TRIM_F32, MLS_T_PAIR, pv, nb);
     HostPhase f64 = make_phase<PairArgs>(BK_PAIR_TRIM_F64, MLS_T_PAIR, pv, nb);
     HostPhase gen = make_phase<PairArgs>(BK_PAIR_GENERIC, MLS_T_PAIR, pv, nb);

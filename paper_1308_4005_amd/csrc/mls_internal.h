@@ -571,7 +571,9 @@ hipError_t launch_binning_reuse(mls_plan_s* P, int n, const double* pos, const d
 hipError_t launch_sum_xi(mls_plan_s* P, int n, hipStream_t s);
 // With `rep`, the FP32 and FP64 half-cell kernels also evaluate the repulsion
 // (*fused set); other kernels leave it to launch_repulsion.
-hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep = nullptr, bool* fused = nullptr);
+// `alone`: nothing runs beside it (pair_split).
+hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep = nullptr, bool* fused = nullptr,
+                       bool alone = false);
 hipError_t launch_scan(mls_plan_s* P, int* count, int m, int* start, hipStream_t s);
 hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s);
 hipError_t launch_restrict(mls_plan_s* P, int k_fine, hipStream_t s);
@@ -595,7 +597,7 @@ hipError_t launch_interpolate(mls_plan_s* P, int n, double* energy, double* forc
 // Lorentz-Berthelot pieces: sorted sigma and flags, the sorted charges of
 // vector k, and the interpolation of all seven vectors with the energy
 hipError_t launch_lb_gather(mls_plan_s* P, int n, const double* sigma, hipStream_t s);
-hipError_t launch_pair_lb(mls_plan_s* P, int n, hipStream_t s);
+hipError_t launch_pair_lb(mls_plan_s* P, int n, hipStream_t s, bool alone = false);
 hipError_t launch_lb_charge(mls_plan_s* P, int n, int k, hipStream_t s);
 hipError_t launch_interpolate_lb(mls_plan_s* P, int n, double* energy, double* forces, hipStream_t s);
 hipError_t launch_binning_scaled(mls_plan_s* P, int n, const double* pos, const double* c6, double scale,
@@ -642,6 +644,12 @@ bool stencil_tile_ok(int R, int zc);
 PairConst pair_const(const mls_plan_s* P);
 PairConstF pair_const_f(const mls_plan_s* P);
 int pair_variant(const mls_plan_s* P);
+// waves that share 64 targets in the trimmed pair kernels (8, 4, 2 or 1) for a
+// launch of `groups` such blocks, alone on the chip or beside the grid chain
+constexpr int kPairSlots = 4096;
+int pair_split(int64_t groups, bool alone);
+// groups up to which the FP32 pair kernels give 64 targets to eight waves
+constexpr int kSplitGroupsF = 512;
 
 // batched launchers: one phase of a batched evaluation (per kernel file)
 hipError_t launch_batched_binning(const BatchPhase& ph, hipStream_t s);

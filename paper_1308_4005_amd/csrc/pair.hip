@@ -461,18 +461,79 @@ __device__ __forceinline__ void store_rep(const PairRep& rp, bool active, int sc
   if (lane == 0) rp.partial[blk] = e;
 }
 
-template <int K, bool LB = false, bool R = false>
+// NS waves share a block's 64 targets (pair_split): each scans a contiguous
+// share of the 25 rows (a simulation gives 3.7 to 5.6 filter steps per row: it
+// takes as many as its slowest lane), and the waves' sums are added in wave
+// order at the end.
+template <int NS>
+struct RowSpan {
+  int wv = 0, r0 = 0, r1 = 25;
+  __device__ __forceinline__ RowSpan() {
+    if constexpr (NS > 1) {
+      wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveQ);
+      r0 = 25 * wv / NS;
+      r1 = 25 * (wv + 1) / NS;
+    }
+  }
+  // the rows as (dz, dy) loops over [-2, 2]^2
+  __device__ __forceinline__ int z0() const { return NS > 1 ? r0 / 5 - 2 : -2; }
+  __device__ __forceinline__ int z1() const { return NS > 1 ? (r1 - 1) / 5 - 2 : 2; }
+  __device__ __forceinline__ int y0(int dz) const { return NS > 1 ? max(r0 - 5 * (dz + 2), 0) - 2 : -2; }
+  __device__ __forceinline__ int y1(int dz) const { return NS > 1 ? min(r1 - 5 * (dz + 2), 5) - 3 : 2; }
+};
+
+// Outputs of a block of NS waves from their sums: e_0 and the force in
+// `sums` (kSumSlots per wave), the repulsive ones (R) put into the waves' own
+// parts of the drained queues (qw ints each) first.  Component c of every
+// target is added up by wave c mod NS, over the waves in order.
+template <int NS, bool R>
+__device__ __forceinline__ void store_split(const double* sums, int* queues, int qw, const RepAcc& B, int wv, int lane,
+                                            bool active, int sc, int blk, double wi, double* __restrict__ e0,
+                                            double* __restrict__ floc, const PairRep& rp) {
+  if constexpr (R) {
+    double* const mine = reinterpret_cast<double*>(queues + wv * qw);
+    sums_fence();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) mine[c * kWaveQ + lane] = B[c];
+  }
+  __syncthreads();
+  for (int c = wv; c < 4; c += NS) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < NS; ++w) v += sums[w * kSumSlots + c * kWaveQ + lane];
+    if (active) {
+      if (c == 0) e0[sc] = v;
+      else floc[3 * (size_t)sc + c - 1] = wi * v;
+    }
+    if constexpr (R) {
+      v = 0.0;
+#pragma unroll
+      for (int w = 0; w < NS; ++w) v += reinterpret_cast<const double*>(queues + w * qw)[c * kWaveQ + lane];
+      const double ci = active ? rp.x12[sc] : 0.0;
+      if (c == 0) {
+        const double e = wave_sum(active ? ci * v : 0.0);
+        if (lane == 0) rp.partial[blk] = e;
+      } else if (active) {
+        rp.frep[3 * (size_t)sc + c - 1] = ci * v;
+      }
+    }
+  }
+}
+
+template <int K, bool LB = false, bool R = false, int NS = 1>
 struct PairTrimF64 {
   using Args = PairArgs;
-  static constexpr int kThreads = kWaveQ;
+  static constexpr int kThreads = kWaveQ * NS;
   static __device__ void run(const Args& ar, int blk) {
   const double4* __restrict__ xs = ar.xs;
   const int* __restrict__ cstart = ar.cstart;
   const CellGeom& g = ar.g;
   const PairConst& pc = ar.pc;
   const int n = ar.n;
-  __shared__ int queue[kQueue * kWaveQ];
-  const int lane = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) int queues[NS * kQueue * kWaveQ];
+  const int lane = threadIdx.x & (kWaveQ - 1);
+  const RowSpan<NS> span;
+  int* const queue = queues + span.wv * (kQueue * kWaveQ);
   const int k = blk * kWaveQ + lane;
   const bool active = k < n;
   const int sc = active ? k : n - 1;
@@ -485,20 +546,22 @@ struct PairTrimF64 {
   const int cx = c % g.nc[0], cy = (c / g.nc[0]) % g.nc[1], cz = c / (g.nc[0] * g.nc[1]);
   // the target itself, seen in the home image, is skipped in the drain
   const int self_ent = active ? ((sc << 6) | image_bits(0, 0, 0)) : -1;
-  __shared__ double sums[kSumSlots];
+  __shared__ double all_sums[NS * kSumSlots];
+  double* const sums = all_sums + span.wv * kSumSlots;
   for (int k = 0; k < kSumSlots / kWaveQ; ++k) sums[k * kWaveQ + lane] = 0.0;
   PairAcc A{LaneSums{sums + lane}, 0, 0};
   RepAcc B{{0.0, 0.0, 0.0, 0.0}};
   const PairRep& rp = ar.rep;
   const float reach = (float)(1.0 + 1e-5);
-  for (int dz = -2; dz <= 2; ++dz) {
+  for (int dz = span.z0(); dz <= span.z1(); ++dz) {
     const int uz = cz + dz;
     const int iz = uz < 0 ? -1 : (uz >= g.nc[2] ? 1 : 0);
     const int tz = uz - iz * g.nc[2];
     // gaps shrunk (and the reach below grown) by the skin margin: with
     // neighbour reuse atoms may sit that far outside their cells
     const double gz = gap1(xi.z, uz * g.w[2], g.w[2], 1e-12 * g.L[2] + g.margin);
-    for (int dy = -2; dy <= 2; ++dy) {
+    const int y1 = span.y1(dz);
+    for (int dy = span.y0(dz); dy <= y1; ++dy) {
       const int uy = cy + dy;
       const int iy = uy < 0 ? -1 : (uy >= g.nc[1] ? 1 : 0);
       const int ty = uy - iy * g.nc[1];
@@ -538,6 +601,10 @@ struct PairTrimF64 {
     }
   }
   pair_drain_f64<K, LB, R>(queue, kQueue, lane, self_ent, sc, xi, xs, g, pc, ar.sig, sig_i, A, rp, B);
+  if constexpr (NS > 1) {
+    store_split<NS, R>(all_sums, queues, kQueue * kWaveQ, B, span.wv, lane, active, sc, blk, xi.w, ar.e0, ar.floc, rp);
+    return;
+  }
   if (active) {
     ar.e0[sc] = A.a[0];
     ar.floc[3 * (size_t)sc + 0] = xi.w * A.a[1];
@@ -586,23 +653,61 @@ struct PairLaneF {
 // bits), the three as two's-complement fields.
 __device__ __forceinline__ int entry_bits(int ix, int dy, int dz) { return (ix & 3) | ((dy & 7) << 2) | ((dz & 7) << 5); }
 
+// The (at most 16) terms of one drain are summed in FP32: e_0, the force and,
+// with R, the repulsive energy and force.
+template <bool R>
+struct DrainF {
+  float s[R ? 8 : 4] = {};
+};
+
+// One source (queue entry ent, rows xj, wsrc) through the full g_0
+// evaluation, added to D; !ok: a harmless pair of weight 0, which adds exactly
+// 0 (no branches).
+template <int K, bool R, bool LB>
+__device__ __forceinline__ void pair_term_f32(bool ok, int ent, int j, const float4& xj, float wsrc,
+                                              const PairLaneF& L, const float* __restrict__ sig,
+                                              const PairConstF& pc, const PairRep& rp, DrainF<R>& D) {
+  const int ix = (ent << 30) >> 30, dy = (ent << 27) >> 29, dz = (ent << 24) >> 29;
+  const float bx = fmaf((float)ix, -L.ncf, L.cxf);
+  const float dxv = fmaf(bx - xj.w, pc.w[0], L.xx) - xj.x;
+  const float dyv = fmaf((float)-dy, pc.w[1], L.yy) - xj.y;
+  const float dzv = fmaf((float)-dz, pc.w[2], L.zz) - xj.z;
+  const float r2 = ok ? dxv * dxv + dyv * dyv + dzv * dzv : 0.25f * pc.a2;
+  float gg, fr;
+  g0_pair<float, K>(r2, pc, gg, fr);
+  float wj = wsrc;
+  if constexpr (LB) {
+    // source weight e_j ((sigma_i + sigma_j) / 2)^6, as in the FP64 kernels
+    const float m = 0.5f * (L.sig_i + sig[j]);
+    const float m3 = m * m * m;
+    wj *= m3 * m3;
+  }
+  D.s[0] = fmaf(wj, gg, D.s[0]);
+  const float f = wj * fr;
+  D.s[1] = fmaf(f, dxv, D.s[1]);
+  D.s[2] = fmaf(f, dyv, D.s[2]);
+  D.s[3] = fmaf(f, dzv, D.s[3]);
+  if constexpr (R) {
+    const float ir2 = recip(r2);
+    const float ir6 = ir2 * ir2 * ir2;
+    const float v = (ok && r2 < (float)rp.rc2 ? rp.x12f[j] : 0.0f) * ir6 * ir6;
+    const float fv = 12.0f * v * ir2;
+    D.s[4] += v;
+    D.s[5] = fmaf(fv, dxv, D.s[5]);
+    D.s[6] = fmaf(fv, dyv, D.s[6]);
+    D.s[7] = fmaf(fv, dzv, D.s[7]);
+  }
+}
+
 // Full g_0 evaluation of up to `limit` queued sources per lane, oldest first.
-// The loop body has no branches: slots past a lane's count (and the target
-// itself) evaluate a harmless pair with zero weight, so every lane adds
-// exactly 0 for them.
 template <int K, bool R, bool LB>
 __device__ __forceinline__ void pair_drain_f32(const int* __restrict__ queue, int limit, int lane,
                                                const PairLaneF& L, const float4* __restrict__ xr,
                                                const float* __restrict__ xif, const float* __restrict__ sig,
                                                const PairConstF& pc, PairAccM& A, const PairRep& rp, RepAcc& B) {
   sums_fence();
-  const float r2_idle = 0.25f * pc.a2;
-  const float rc2 = (float)rp.rc2;
   const int cnt = A.cnt;
-  // the (at most 32) terms of one drain are summed in FP32, the drains' sums
-  // in FP64
-  float e = 0.0f, fx = 0.0f, fy = 0.0f, fz = 0.0f;
-  float re = 0.0f, rfx = 0.0f, rfy = 0.0f, rfz = 0.0f;
+  DrainF<R> D;
   for (int t = 0; t < limit && __any(t < cnt); ++t) {
     const int q = queue[((A.head + t) & (kQueueF - 1)) * kWaveQ + lane];
     const bool ok = (t < cnt) & (q != L.self_ent);
@@ -615,47 +720,11 @@ __device__ __forceinline__ void pair_drain_f32(const int* __restrict__ queue, in
       xj = at32(xr, j);
       wsrc = at32(xif, j);
     }
-    const int ix = (ent << 30) >> 30, dy = (ent << 27) >> 29, dz = (ent << 24) >> 29;
-    const float bx = fmaf((float)ix, -L.ncf, L.cxf);
-    const float dxv = fmaf(bx - xj.w, pc.w[0], L.xx) - xj.x;
-    const float dyv = fmaf((float)-dy, pc.w[1], L.yy) - xj.y;
-    const float dzv = fmaf((float)-dz, pc.w[2], L.zz) - xj.z;
-    const float r2 = ok ? dxv * dxv + dyv * dyv + dzv * dzv : r2_idle;
-    float gg, fr;
-    g0_pair<float, K>(r2, pc, gg, fr);
-    float wj = wsrc;
-    if constexpr (LB) {
-      // source weight e_j ((sigma_i + sigma_j) / 2)^6, as in the FP64 kernels
-      const float m = 0.5f * (L.sig_i + sig[j]);
-      const float m3 = m * m * m;
-      wj *= m3 * m3;
-    }
-    e = fmaf(wj, gg, e);
-    const float f = wj * fr;
-    fx = fmaf(f, dxv, fx);
-    fy = fmaf(f, dyv, fy);
-    fz = fmaf(f, dzv, fz);
-    if constexpr (R) {
-      const float ir2 = recip(r2);
-      const float ir6 = ir2 * ir2 * ir2;
-      const float v = (ok && r2 < rc2 ? rp.x12f[j] : 0.0f) * ir6 * ir6;
-      const float fv = 12.0f * v * ir2;
-      re += v;
-      rfx = fmaf(fv, dxv, rfx);
-      rfy = fmaf(fv, dyv, rfy);
-      rfz = fmaf(fv, dzv, rfz);
-    }
+    pair_term_f32<K, R, LB>(ok, ent, j, xj, wsrc, L, sig, pc, rp, D);
   }
-  A.a[0] += (double)e;
-  A.a[1] += (double)fx;
-  A.a[2] += (double)fy;
-  A.a[3] += (double)fz;
-  if constexpr (R) {
-    B[0] += (double)re;
-    B[1] += (double)rfx;
-    B[2] += (double)rfy;
-    B[3] += (double)rfz;
-  }
+  for (int c = 0; c < 4; ++c) A.a[c] += (double)D.s[c];
+  if constexpr (R)
+    for (int c = 0; c < 4; ++c) B[c] += (double)D.s[4 + c];
   const int done = min(cnt, limit);
   A.head = (A.head + done) & (kQueueF - 1);
   A.cnt = cnt - done;
@@ -724,106 +793,363 @@ __device__ __forceinline__ void pair_scan_f32(int j, int j1, int ix, int dy, int
   A.cnt = cnt;
 }
 
-template <int K, bool R = false, bool LB = false>
-struct PairTrimF32 {
-  using Args = PairArgsF;
-  static constexpr int kThreads = kWaveQ;
-  static __device__ void run(const Args& ar, int blk) {
-  const float4* __restrict__ xr = ar.xr;
-  const float* __restrict__ xif = ar.xif;
-  const int* __restrict__ cstart = ar.cstart;
+// Set-up of a block's targets: lane's target, its cell and its scan data.
+struct TargetF {
+  int lane, sc, cx, cy, cz;
+  bool active;
+  float4 xi;
+  PairLaneF L;
+};
+
+template <bool LB>
+__device__ __forceinline__ TargetF pair_target_f32(const PairArgsF& ar, int blk) {
+  TargetF t;
   const CellGeom& g = ar.g;
+  t.lane = threadIdx.x & (kWaveQ - 1);
+  const int k = blk * kWaveQ + t.lane;
+  t.active = k < ar.n;
+  t.sc = t.active ? k : ar.n - 1;
+  t.xi = ar.xr[t.sc];
+  const int c = ar.cell_s[t.sc];
+  t.cx = c % g.nc[0];
+  t.cy = (c / g.nc[0]) % g.nc[1];
+  t.cz = c / (g.nc[0] * g.nc[1]);
+  t.L = PairLaneF{t.xi.x, t.xi.y, t.xi.z, (float)t.cx, (float)g.nc[0],
+                  t.active ? ((t.sc << 8) | entry_bits(0, 0, 0)) : -1, t.sc, LB ? ar.sig[t.sc] : 0.0f, ar.xf[t.sc]};
+  return t;
+}
+
+// The two runs [j0, j1), [k0, k1) of one row of cells (x images ix1, ix2) that
+// a target's cutoff sphere can reach; empty for an idle lane.
+struct RowRuns {
+  int j0, j1, ix1, k0, k1, ix2;
+};
+
+// Rows are chosen and trimmed in the target's cell-relative FP32 coordinates.
+// The gaps are shrunk and the reach grown by margins (1e-5 of a cell, 2e-5 of
+// the cutoff) far above their FP32 rounding (~1e-7), so no cell that holds a
+// source inside the cutoff is ever skipped; mg, the skin margin of neighbour
+// reuse (atoms may sit that far outside their cells), does the same.
+// tz, ty: the row's wrapped cell coordinates.
+__device__ __forceinline__ float row_gap_f32(int d, float w, float x, float mg) {
+  return d == 0 ? 0.0f
+                : fmaxf(0.0f, (d > 0 ? fmaf((float)d, w, -x) : fmaf((float)(-d - 1), w, x)) - 1e-5f * w - mg);
+}
+
+__device__ __forceinline__ RowRuns row_runs_f32(const PairArgsF& ar, const TargetF& t, float rem, float inv_wx, float mg,
+                                                int row) {
   const PairConstF& pc = ar.pc;
-  const int n = ar.n;
-  __shared__ int queue[kQueueF * kWaveQ];
-  const int lane = threadIdx.x;
-  const int k = blk * kWaveQ + lane;
-  const bool active = k < n;
-  const int sc = active ? k : n - 1;
-  const float4 xi = xr[sc];
-  const int c = ar.cell_s[sc];
-  const int cx = c % g.nc[0], cy = (c / g.nc[0]) % g.nc[1], cz = c / (g.nc[0] * g.nc[1]);
-  const float* __restrict__ sig = ar.sig;
-  const float* __restrict__ xf = ar.xf;
-  const int xfs = ar.xf_stride;
-  const PairLaneF L{xi.x, xi.y, xi.z, (float)cx, (float)g.nc[0], active ? ((sc << 8) | entry_bits(0, 0, 0)) : -1, sc,
-                    LB ? sig[sc] : 0.0f, xf[sc]};
-  __shared__ double sums[kSumSlots];
-  for (int k = 0; k < kSumSlots / kWaveQ; ++k) sums[k * kWaveQ + lane] = 0.0;
-  PairAccM A{LaneSums{sums + lane}, 0, 0};
-  RepAcc B{{0.0, 0.0, 0.0, 0.0}};
-  const PairRep& rp = ar.rep;
-  // Rows are chosen and trimmed in the target's cell-relative FP32
-  // coordinates.  The gaps are shrunk and the reach grown by margins (1e-5 of
-  // a cell, 2e-5 of the cutoff) far above their FP32 rounding (~1e-7), so no
-  // cell that holds a source inside the cutoff is ever skipped.
-  const float a2m = pc.a2 * (1.0f + 2e-5f);
   const float reach = 1.0f + 2e-5f;
+  const int nc0 = ar.g.nc[0];
+  int clo = 0, chi = -1;
+  if (t.active && rem > 0.0f) {
+    // hardware square root (about 1 ulp): far inside the margin
+    const float rx = fmaf(__builtin_amdgcn_sqrtf(rem), reach, 1e-5f * pc.w[0] + mg);
+    clo = t.cx + max(-2, (int)floorf((t.xi.x - rx) * inv_wx));
+    chi = t.cx + min(2, (int)floorf((t.xi.x + rx) * inv_wx));
+  }
+  int lo1 = clo, hi1 = chi, lo2 = 0, hi2 = -1;
+  RowRuns r{0, 0, 0, 0, 0, 0};
+  if (clo < 0) {
+    lo1 = clo + nc0; hi1 = nc0 - 1; r.ix1 = -1;
+    lo2 = 0; hi2 = chi; r.ix2 = 0;
+  } else if (chi >= nc0) {
+    lo1 = clo; hi1 = nc0 - 1; r.ix1 = 0;
+    lo2 = 0; hi2 = chi - nc0; r.ix2 = 1;
+  }
+  if (lo1 <= hi1) {
+    r.j0 = at32(ar.cstart, row + lo1);
+    r.j1 = at32(ar.cstart, row + hi1 + 1);
+  }
+  if (lo2 <= hi2) {
+    r.k0 = at32(ar.cstart, row + lo2);
+    r.k1 = at32(ar.cstart, row + hi2 + 1);
+  }
+  return r;
+}
+
+// One wave's scan of all rows of its targets, into A and B.
+template <int K, bool R, bool LB>
+__device__ __forceinline__ void pair_rows_f32(const PairArgsF& ar, const TargetF& t, int* queue, PairAccM& A, RepAcc& B) {
+  const PairConstF& pc = ar.pc;
+  const CellGeom& g = ar.g;
+  const float a2m = pc.a2 * (1.0f + 2e-5f);
   const float inv_wx = 1.0f / pc.w[0];
-  // the skin margin of neighbour reuse (atoms may sit that far outside their
-  // cells): shrinks the gaps and grows the reach
   const float mg = (float)g.margin;
   const int nc0 = g.nc[0], nc1 = g.nc[1], nc2 = g.nc[2];
   // the candidate registers of the scans, carried from run to run
   float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X;
   for (int dz = -2; dz <= 2; ++dz) {
-    const int uz = cz + dz;
+    const int uz = t.cz + dz;
     const int tz = uz < 0 ? uz + nc2 : (uz >= nc2 ? uz - nc2 : uz);
-    const float gz = dz == 0 ? 0.0f
-                             : fmaxf(0.0f, (dz > 0 ? fmaf((float)dz, pc.w[2], -xi.z)
-                                                   : fmaf((float)(-dz - 1), pc.w[2], xi.z)) - 1e-5f * pc.w[2] - mg);
+    const float gz = row_gap_f32(dz, pc.w[2], t.xi.z, mg);
     const float rem_z = a2m - gz * gz;
     const int rowz = tz * nc1;
-    int ty = cy - 2 < 0 ? cy - 2 + nc1 : cy - 2;
+    int ty = t.cy - 2 < 0 ? t.cy - 2 + nc1 : t.cy - 2;
     for (int dy = -2; dy <= 2; ++dy) {
-      const float gy = dy == 0 ? 0.0f
-                               : fmaxf(0.0f, (dy > 0 ? fmaf((float)dy, pc.w[1], -xi.y)
-                                                     : fmaf((float)(-dy - 1), pc.w[1], xi.y)) - 1e-5f * pc.w[1] - mg);
-      const float rem = rem_z - gy * gy;
-      int clo = 0, chi = -1;
-      if (active && rem > 0.0f) {
-        // hardware square root (about 1 ulp): far inside the margin
-        const float rx = fmaf(__builtin_amdgcn_sqrtf(rem), reach, 1e-5f * pc.w[0] + mg);
-        clo = cx + max(-2, (int)floorf((xi.x - rx) * inv_wx));
-        chi = cx + min(2, (int)floorf((xi.x + rx) * inv_wx));
-      }
-      int lo1 = clo, hi1 = chi, ix1 = 0, lo2 = 0, hi2 = -1, ix2 = 0;
-      if (clo < 0) {
-        lo1 = clo + nc0; hi1 = nc0 - 1; ix1 = -1;
-        lo2 = 0; hi2 = chi; ix2 = 0;
-      } else if (chi >= nc0) {
-        lo1 = clo; hi1 = nc0 - 1; ix1 = 0;
-        lo2 = 0; hi2 = chi - nc0; ix2 = 1;
-      }
-      const int row = (rowz + ty) * nc0;
+      const float gy = row_gap_f32(dy, pc.w[1], t.xi.y, mg);
+      const RowRuns r = row_runs_f32(ar, t, rem_z - gy * gy, inv_wx, mg, (rowz + ty) * nc0);
       ty = ty + 1 == nc1 ? 0 : ty + 1;
-      int j0 = 0, j1 = 0;
-      if (lo1 <= hi1) {
-        j0 = at32(cstart, row + lo1);
-        j1 = at32(cstart, row + hi1 + 1);
-      }
-      int k0 = 0, k1 = 0;
-      if (lo2 <= hi2) {
-        k0 = at32(cstart, row + lo2);
-        k1 = at32(cstart, row + hi2 + 1);
-      }
       // the second run (across the periodic edge) is empty for most waves:
       // its set-up is skipped unless some lane has one
-      if (__any(j0 < j1))
-        pair_scan_f32<K, R, LB>(j0, j1, ix1, dy, dz, queue, lane, L, xr, xf, xfs, xif, sig, pc, A, rp, B, X, Y, Z);
-      if (__any(k0 < k1))
-        pair_scan_f32<K, R, LB>(k0, k1, ix2, dy, dz, queue, lane, L, xr, xf, xfs, xif, sig, pc, A, rp, B, X, Y, Z);
+      if (__any(r.j0 < r.j1))
+        pair_scan_f32<K, R, LB>(r.j0, r.j1, r.ix1, dy, dz, queue, t.lane, t.L, ar.xr, ar.xf, ar.xf_stride, ar.xif,
+                                ar.sig, pc, A, ar.rep, B, X, Y, Z);
+      if (__any(r.k0 < r.k1))
+        pair_scan_f32<K, R, LB>(r.k0, r.k1, r.ix2, dy, dz, queue, t.lane, t.L, ar.xr, ar.xf, ar.xf_stride, ar.xif,
+                                ar.sig, pc, A, ar.rep, B, X, Y, Z);
     }
   }
-  pair_drain_f32<K, R, LB>(queue, kQueueF, lane, L, xr, xif, sig, pc, A, rp, B);
-  if (active) {
-    const double wi = (double)xif[sc];
-    ar.e0[sc] = A.a[0];
-    ar.floc[3 * (size_t)sc + 0] = wi * A.a[1];
-    ar.floc[3 * (size_t)sc + 1] = wi * A.a[2];
-    ar.floc[3 * (size_t)sc + 2] = wi * A.a[3];
+  pair_drain_f32<K, R, LB>(queue, kQueueF, t.lane, t.L, ar.xr, ar.xif, ar.sig, pc, A, ar.rep, B);
+}
+
+template <int K, bool R = false, bool LB = false>
+struct PairTrimF32 {
+  using Args = PairArgsF;
+  static constexpr int kThreads = kWaveQ;
+  static __device__ void run(const Args& ar, int blk) {
+    __shared__ int queue[kQueueF * kWaveQ];
+    __shared__ double sums[kSumSlots];
+    const TargetF t = pair_target_f32<LB>(ar, blk);
+    for (int k = 0; k < kSumSlots / kWaveQ; ++k) sums[k * kWaveQ + t.lane] = 0.0;
+    PairAccM A{LaneSums{sums + t.lane}, 0, 0};
+    RepAcc B{{0.0, 0.0, 0.0, 0.0}};
+    pair_rows_f32<K, R, LB>(ar, t, queue, A, B);
+    if (t.active) {
+      const double wi = (double)ar.xif[t.sc];
+      ar.e0[t.sc] = A.a[0];
+      ar.floc[3 * (size_t)t.sc + 0] = wi * A.a[1];
+      ar.floc[3 * (size_t)t.sc + 1] = wi * A.a[2];
+      ar.floc[3 * (size_t)t.sc + 2] = wi * A.a[3];
+    }
+    if constexpr (R) store_rep(ar.rep, t.active, t.sc, t.lane, blk, B);
   }
-  if constexpr (R) store_rep(rp, active, sc, lane, blk, B);
+};
+
+// The FP32 scan dealt to the eight waves of a block (pair_split), with the
+// sums of PairTrimF32 to the last FP32 bit: there the terms that meet in one
+// drain are summed in FP32, and which terms meet depends on all 64 lanes'
+// queues.  So the waves first only filter: each scans its share of the rows
+// and leaves, per step of four candidates and lane, the mask of its hits and
+// the step's place (run, step of the run).  Then each lane's hits are listed in
+// order, every wave replays the queue lengths over all steps (counts only)
+// and evaluates every eighth drain, and the drains' sums are added in FP64.
+// LDS: 69 KB, two blocks per CU.  A block that finds more steps or hits than
+// fit (beyond about 280 neighbours per target) lets its first wave do the
+// whole scan as PairTrimF32 does.
+constexpr int kSplitF = 8;           // waves per block
+constexpr int kSplitSteps = 40;      // filter steps of one wave
+constexpr int kSplitHits = 288;      // hits of one target
+constexpr int kSplitRuns = 50;       // 25 rows, two runs each
+
+template <int K, bool R = false, bool LB = false>
+struct PairSplitF32 {
+  using Args = PairArgsF;
+  static constexpr int kThreads = kWaveQ * kSplitF;
+  static __device__ void run(const Args& ar, int blk) {
+    constexpr int NS = kSplitF, W = kWaveQ;
+    __shared__ unsigned char mask[NS * kSplitSteps * W];
+    __shared__ unsigned short place[NS * kSplitSteps];
+    __shared__ int first[kSplitRuns * W];       // queue entry of a run's first source
+    // hit lists (step << 2 | candidate); later the waves' sums
+    __shared__ __attribute__((aligned(16))) unsigned short list[kSplitHits * W];
+    __shared__ unsigned short hits[NS * W];
+    __shared__ int steps[NS];                   // filter steps of each wave, -1: too many
+    const TargetF t = pair_target_f32<LB>(ar, blk);
+    const int lane = t.lane;
+    const RowSpan<NS> span;
+    const int wv = span.wv;
+    const PairConstF& pc = ar.pc;
+    const PairRep& rp = ar.rep;
+    // ---- filter
+    {
+      const CellGeom& g = ar.g;
+      const float a2m = pc.a2 * (1.0f + 2e-5f);
+      const float inv_wx = 1.0f / pc.w[0];
+      const float mg = (float)g.margin;
+      const float* const xf0 = ar.xf;
+      const float* const xf1 = xf0 + ar.xf_stride;
+      const float* const xf2 = xf1 + ar.xf_stride;
+      int ns = 0, nh = 0;
+      // the cell ranges of all rows first, their loads in flight together
+      constexpr int kRows = (25 + NS - 1) / NS;
+      RowRuns rr[kRows];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const int r = span.r0 + u;
+        const int dz = r / 5 - 2, dy = r % 5 - 2;
+        int tz = t.cz + dz, ty = t.cy + dy;
+        tz = tz < 0 ? tz + g.nc[2] : (tz >= g.nc[2] ? tz - g.nc[2] : tz);
+        ty = ty < 0 ? ty + g.nc[1] : (ty >= g.nc[1] ? ty - g.nc[1] : ty);
+        const float gz = row_gap_f32(dz, pc.w[2], t.xi.z, mg), gy = row_gap_f32(dy, pc.w[1], t.xi.y, mg);
+        const float rem = r < span.r1 ? (a2m - gz * gz) - gy * gy : 0.0f;
+        rr[u] = row_runs_f32(ar, t, rem, inv_wx, mg, (tz * g.nc[1] + ty) * g.nc[0]);
+      }
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const int r = span.r0 + u;
+        const int dz = r / 5 - 2, dy = r % 5 - 2;
+        const float ay = fmaf((float)-dy, pc.w[1], t.L.yy);
+        const float az = fmaf((float)-dz, pc.w[2], t.L.zz);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          int j = h ? rr[u].k0 : rr[u].j0;
+          const int j1 = h ? rr[u].k1 : rr[u].j1, ix = h ? rr[u].ix2 : rr[u].ix1;
+          if (!__any(j < j1)) continue;
+          const float ax = fmaf((float)-ix, pc.L[0], t.L.xa);
+          first[(2 * r + h) * W + lane] = (j << 8) | entry_bits(ix, dy, dz);
+          // the next step's candidates are loaded before this step's are used
+          float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X, Xn = X, Yn = X, Zn = X;
+          auto load = [&](int i) {
+            if (i < j1) {
+              const unsigned off = (unsigned)i * 4u;
+              Xn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf0) + off));
+              Yn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf1) + off));
+              Zn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf2) + off));
+            }
+          };
+          load(j);
+          for (int k = 0; ns >= 0 && __any(j < j1); ++k) {
+            if (ns == kSplitSteps) {
+              ns = -1;
+              break;
+            }
+            const int rem = j1 - j;
+            X = Xn;
+            Y = Yn;
+            Z = Zn;
+            load(j + kBatchF);
+            const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
+            int m = 0;
+#pragma unroll
+            for (int b = 0; b < kBatchF; ++b) {
+              const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
+              const float r2 = dxv * dxv + dyv * dyv + dzv * dzv;
+              m |= ((b < rem) & (r2 < pc.a2f)) ? 1 << b : 0;
+            }
+            mask[(wv * kSplitSteps + ns) * W + lane] = (unsigned char)m;
+            if (lane == 0) place[wv * kSplitSteps + ns] = (unsigned short)((2 * r + h) | (k << 6));
+            nh += __builtin_popcount(m);
+            ++ns;
+            j += kBatchF;
+          }
+        }
+      }
+      hits[wv * W + lane] = (unsigned short)nh;
+      if (lane == 0) steps[wv] = ns;
+    }
+    __syncthreads();
+    int base = 0, total = 0, few = 0;
+#pragma unroll
+    for (int w = 0; w < NS; ++w) {
+      const int h = hits[w * W + lane];
+      base += w < wv ? h : 0;
+      total += h;
+      few = min(few, steps[w]);
+    }
+    double sum[R ? 8 : 4] = {};
+    if (few < 0 || __any(total > kSplitHits)) {   // the same in every wave
+      if (wv == 0) {
+        int* const queue = reinterpret_cast<int*>(list);
+        double* const sums = reinterpret_cast<double*>(list) + kQueueF * W / 2;
+        for (int c = 0; c < 4; ++c) sums[c * W + lane] = 0.0;
+        PairAccM A{LaneSums{sums + lane}, 0, 0};
+        RepAcc B{{0.0, 0.0, 0.0, 0.0}};
+        pair_rows_f32<K, R, LB>(ar, t, queue, A, B);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          sum[c] = A.a[c];
+          if constexpr (R) sum[4 + c] = B[c];
+        }
+      }
+    } else {
+      // ---- the hits in order
+      for (int s = 0; s < steps[wv]; ++s) {
+        const int st = wv * kSplitSteps + s;
+        const int m = mask[st * W + lane];
+#pragma unroll
+        for (int b = 0; b < kBatchF; ++b)
+          if (m >> b & 1) list[base++ * W + lane] = (unsigned short)(st << 2 | b);
+      }
+      __syncthreads();
+      // ---- the drains
+      int cnt = 0, pos = 0, drain = 0;
+      auto evaluate = [&](int m) {
+        DrainF<R> D;
+        // four sources at a time, their look-ups and loads in flight together
+        constexpr int kAhead = 4;
+        for (int u0 = 0; __any(u0 < m); u0 += kAhead) {
+          bool ok[kAhead];
+          int ent[kAhead], src[kAhead];
+          float4 xj[kAhead];
+          float wsrc[kAhead];
+#pragma unroll
+          for (int u = 0; u < kAhead; ++u) {
+            int q = t.L.self_ent;
+            if (u0 + u < m) {
+              const int e = list[(pos + u0 + u) * W + lane];
+              const int pl = place[e >> 2];
+              q = first[(pl & 63) * W + lane] + ((((pl >> 6) << 2) + (e & 3)) << 8);
+            }
+            // idle slots (and the target itself): as in pair_drain_f32
+            ok[u] = q != t.L.self_ent;
+            ent[u] = ok[u] ? q : 0;
+            src[u] = ok[u] ? (int)((unsigned)q >> 8) : t.L.safe_j;
+            xj[u] = make_float4(t.L.xx + pc.w[0], t.L.yy, t.L.zz, t.L.cxf);
+            wsrc[u] = 0.0f;
+            if (ok[u]) {
+              xj[u] = at32(ar.xr, src[u]);
+              wsrc[u] = at32(ar.xif, src[u]);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kAhead; ++u)
+            pair_term_f32<K, R, LB>(ok[u], ent[u], src[u], xj[u], wsrc[u], t.L, ar.sig, pc, rp, D);
+        }
+#pragma unroll
+        for (int c = 0; c < (R ? 8 : 4); ++c) sum[c] += (double)D.s[c];
+      };
+      for (int w = 0; w < NS; ++w) {
+        const int n = steps[w];
+        const unsigned char* mw = mask + w * kSplitSteps * W + lane;
+        int next = mw[0];
+        for (int s = 0; s < n; ++s) {
+          cnt += __builtin_popcount(next);
+          next = mw[min(s + 1, kSplitSteps - 1) * W];
+          if (__any(cnt > kQueueF - kBatchF)) {
+            const int m = min(cnt, kDrainF);
+            if ((drain++ & (NS - 1)) == wv) evaluate(m);
+            pos += m;
+            cnt -= m;
+          }
+        }
+      }
+      if ((drain & (NS - 1)) == wv) evaluate(cnt);
+    }
+    __syncthreads();
+    // ---- the waves' sums, in wave order
+    double* const out = reinterpret_cast<double*>(list);
+    static_assert(sizeof(list) >= sizeof(double) * 8 * NS * W, "the sums reuse the hit lists");
+#pragma unroll
+    for (int c = 0; c < (R ? 8 : 4); ++c) out[(wv * 8 + c) * W + lane] = sum[c];
+    __syncthreads();
+    if (wv < (R ? 8 : 4)) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < NS; ++w) v += out[(w * 8 + wv) * W + lane];
+      if (wv >= 4) {
+        const double ci = t.active ? rp.x12[t.sc] : 0.0;
+        if (wv == 4) {
+          const double e = wave_sum(t.active ? ci * v : 0.0);
+          if (lane == 0) rp.partial[blk] = e;
+        } else if (t.active) {
+          rp.frep[3 * (size_t)t.sc + wv - 5] = ci * v;
+        }
+      } else if (t.active) {
+        if (wv == 0) ar.e0[t.sc] = v;
+        else ar.floc[3 * (size_t)t.sc + wv - 1] = (double)ar.xif[t.sc] * v;
+      }
+    }
   }
 };
 
@@ -864,8 +1190,41 @@ PairConstF pair_const_f(const mls_plan_s* P) {
 
 int pair_variant(const mls_plan_s* P) { return P->continuity == 2 ? 2 : 0; }
 
+// Waves per 64 targets.  One wave walks its 25 rows in about 100 us whatever
+// the number of atoms (dependent cell-range and candidate loads), so a launch
+// of fewer waves than the chip holds (16 per CU in FP64, 26 in FP32) is bound
+// by that chain; dealing the rows to more waves shortens it.  Pair kernel
+// alone with 1 / 2 / 4 / 8 waves (us, FP64; cube at density 0.8, a = 3):
+// 1000 atoms 101 / 63 / 38 / 24, 32,000 atoms 106 / 66 / 42 / 32, 10^5 atoms
+// 119 / 82 / 83 / 85, 250,000 atoms 164 / 162 / 167 / 180, 10^6 atoms 516 /
+// 543 / 577 / 636 (the filter steps of a row are set by its slowest lane
+// either way; what grows is the set-up): hence at most kPairSlots waves.
+// Beside the grid chain two waves at most: the chain's kernels then find free
+// slots (evaluation of 64,000 atoms, FP64: 164 / 140 / 167 / 160 us).
+int pair_split(int64_t groups, bool alone) {
+  for (int ns = alone ? 8 : 2; ns > 1; ns /= 2)
+    if (groups * ns <= kPairSlots) return ns;
+  return 1;
+}
+
+template <int K, bool R, bool LB>
+hipError_t launch_split_f32(const mls_plan_s* P, const PairArgsF& a, int groups, hipStream_t s) {
+  if (P->pair_blocks <= 0 && groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
+  return launch_persist<PairTrimF32<K, R, LB>>(a, groups, P->pair_blocks, s);
+}
+
+template <int K, bool LB, bool R>
+hipError_t launch_split_f64(const mls_plan_s* P, const PairArgs& a, int groups, bool alone, hipStream_t s) {
+  switch (P->pair_blocks > 0 ? 1 : pair_split(groups, alone)) {
+    case 8: return launch_one<PairTrimF64<K, LB, R, 8>>(a, groups, s);
+    case 4: return launch_one<PairTrimF64<K, LB, R, 4>>(a, groups, s);
+    case 2: return launch_one<PairTrimF64<K, LB, R, 2>>(a, groups, s);
+    default: return launch_persist<PairTrimF64<K, LB, R>>(a, groups, P->pair_blocks, s);
+  }
+}
+
 template <int K>
-hipError_t launch_pair_k(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep, bool* fused) {
+hipError_t launch_pair_k(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep, bool* fused, bool alone) {
   const CellGeom& g = P->cg;
   const int waves = (n + kWaveQ - 1) / kWaveQ;
   if (P->precision == MLS_MIXED && P->pair_fast && n < (1 << 24)) {
@@ -873,21 +1232,21 @@ hipError_t launch_pair_k(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep
                 P->d_floc};
     a.xf = P->d_xf;
     a.xf_stride = P->xf_stride;
-    if (!rep) return launch_persist<PairTrimF32<K>>(a, waves, P->pair_blocks, s);
+    if (!rep) return launch_split_f32<K, false, false>(P, a, waves, s);
     a.rep = *rep;
     *fused = true;
     P->rep_nb = waves;
-    return launch_persist<PairTrimF32<K, true>>(a, waves, P->pair_blocks, s);
+    return launch_split_f32<K, true, false>(P, a, waves, s);
   }
   PairArgs a{P->d_xs, P->d_cell_s, P->d_cell_start, n, g, pair_const(P), P->d_e0, P->d_floc, nullptr};
   a.xf = P->d_xf;
   a.xf_stride = P->xf_stride;
   if (P->pair_fast && n < (1 << 25)) {
-    if (!rep) return launch_persist<PairTrimF64<K>>(a, waves, P->pair_blocks, s);
+    if (!rep) return launch_split_f64<K, false, false>(P, a, waves, alone, s);
     a.rep = *rep;
     *fused = true;
     P->rep_nb = waves;
-    return launch_persist<PairTrimF64<K, false, true>>(a, waves, P->pair_blocks, s);
+    return launch_split_f64<K, false, true>(P, a, waves, alone, s);
   }
   if (!P->pair_fast) return launch_one<PairWave<K>>(a, n, s);
   return launch_one<PairGeneric<K>>(a, (n + kBlock - 1) / kBlock, s);
@@ -895,34 +1254,46 @@ hipError_t launch_pair_k(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep
 
 // Lorentz-Berthelot: the same kernels with the LB source weight.
 template <int K>
-hipError_t launch_pair_lb_k(mls_plan_s* P, int n, hipStream_t s) {
+hipError_t launch_pair_lb_k(mls_plan_s* P, int n, hipStream_t s, bool alone) {
   if (P->precision == MLS_MIXED && P->pair_fast && n < (1 << 24)) {
     PairArgsF a{P->d_xr, P->d_xif, P->d_xs, P->d_cell_s, P->d_cell_start, n, P->cg, pair_const_f(P), P->d_e0,
                 P->d_floc};
     a.sig = P->d_sigf;
     a.xf = P->d_xf;
     a.xf_stride = P->xf_stride;
-    return launch_one<PairTrimF32<K, false, true>>(a, (n + kWaveQ - 1) / kWaveQ, s);
+    return launch_split_f32<K, false, true>(P, a, (n + kWaveQ - 1) / kWaveQ, s);
   }
   PairArgs a{P->d_xs, P->d_cell_s, P->d_cell_start, n, P->cg, pair_const(P), P->d_e0, P->d_floc, P->d_sig};
   a.xf = P->d_xf;
   a.xf_stride = P->xf_stride;
-  if (P->pair_fast && n < (1 << 25)) return launch_one<PairTrimF64<K, true>>(a, (n + kWaveQ - 1) / kWaveQ, s);
+  if (P->pair_fast && n < (1 << 25)) return launch_split_f64<K, true, false>(P, a, (n + kWaveQ - 1) / kWaveQ, alone, s);
   if (!P->pair_fast) return launch_one<PairWave<K, true>>(a, n, s);
   return launch_one<PairGeneric<K, true>>(a, (n + kBlock - 1) / kBlock, s);
 }
 
-hipError_t launch_pair_lb(mls_plan_s* P, int n, hipStream_t s) {
+hipError_t launch_pair_lb(mls_plan_s* P, int n, hipStream_t s, bool alone) {
   if (n == 0) return hipSuccess;
-  return pair_variant(P) == 2 ? launch_pair_lb_k<2>(P, n, s) : launch_pair_lb_k<0>(P, n, s);
+  return pair_variant(P) == 2 ? launch_pair_lb_k<2>(P, n, s, alone) : launch_pair_lb_k<0>(P, n, s, alone);
 }
 
-hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep, bool* fused) {
+hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep, bool* fused, bool alone) {
   bool f = false;
   if (!fused) fused = &f;
   *fused = false;
   if (n == 0) return hipSuccess;
-  return pair_variant(P) == 2 ? launch_pair_k<2>(P, n, s, rep, fused) : launch_pair_k<0>(P, n, s, rep, fused);
+  return pair_variant(P) == 2 ? launch_pair_k<2>(P, n, s, rep, fused, alone)
+                              : launch_pair_k<0>(P, n, s, rep, fused, alone);
+}
+
+template <int K, int NS>
+hipError_t launch_batched_trim(const BatchPhase& ph, hipStream_t s, bool lb) {
+  if (ph.kernel == BK_PAIR_TRIM_F64)
+    return lb ? launch_batched_phase<PairTrimF64<K, true, false, NS>>(ph, s)
+              : launch_batched_phase<PairTrimF64<K, false, false, NS>>(ph, s);
+  if constexpr (NS == kSplitF)
+    return lb ? launch_batched_phase<PairSplitF32<K, false, true>>(ph, s)
+              : launch_batched_phase<PairSplitF32<K>>(ph, s);
+  return lb ? launch_batched_phase<PairTrimF32<K, false, true>>(ph, s) : launch_batched_phase<PairTrimF32<K>>(ph, s);
 }
 
 template <int K>
@@ -933,16 +1304,19 @@ hipError_t launch_batched_pair_k(const BatchPhase& ph, hipStream_t s, bool lb) {
     case BK_PAIR_WAVE:
       return lb ? launch_batched_phase<PairWave<K, true>>(ph, s) : launch_batched_phase<PairWave<K>>(ph, s);
     case BK_PAIR_TRIM_F64:
-      return lb ? launch_batched_phase<PairTrimF64<K, true>>(ph, s) : launch_batched_phase<PairTrimF64<K>>(ph, s);
     case BK_PAIR_TRIM_F32:
-      return lb ? launch_batched_phase<PairTrimF32<K, false, true>>(ph, s)
-                : launch_batched_phase<PairTrimF32<K>>(ph, s);
+      switch (ph.variant >> 8) {
+        case 8: return launch_batched_trim<K, 8>(ph, s, lb);
+        case 4: return launch_batched_trim<K, 4>(ph, s, lb);
+        case 2: return launch_batched_trim<K, 2>(ph, s, lb);
+        default: return launch_batched_trim<K, 1>(ph, s, lb);
+      }
     default: return hipErrorInvalidValue;
   }
 }
 
 // Batched phases of this file; variant = the pair_variant of its boxes, | 0x10
-// under Lorentz-Berthelot mixing.
+// under Lorentz-Berthelot mixing, | waves per block << 8 of the trimmed kernels.
 hipError_t launch_batched_pair(const BatchPhase& ph, hipStream_t s) {
   const bool lb = (ph.variant & 0x10) != 0;
   return (ph.variant & 0xf) == 2 ? launch_batched_pair_k<2>(ph, s, lb) : launch_batched_pair_k<0>(ph, s, lb);
