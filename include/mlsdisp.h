@@ -124,8 +124,9 @@ typedef struct {
 /* Level-stencil kernels (mls_plan_info.stencil_path).  R is the stencil's
  * half width in finest-grid points, ceil(2a / h) per dimension at most.
  * FP32 tiles serve MLS_MIXED plans up to R = 12, FP64 tiles FP64 plans up
- * to R = 8; beyond that both precisions run FP64 kernels (a streaming kernel
- * up to R = 12, then one thread per output point over the tap table). */
+ * to R = 8; beyond that both precisions run FP64 kernels (FP64 plans: tiles
+ * streamed through LDS in slabs up to R = 12; then one thread per output point
+ * over the tap table). */
 typedef enum {
   MLS_STENCIL_NONE = 0,        /* l = 1: no level stencils */
   MLS_STENCIL_TILE_F32 = 1,
@@ -395,7 +396,7 @@ mls_status mls_plan_destroy(mls_plan_t plan);
  * ------------------------------------------------------------------------- */
 typedef struct {
   int blocks[MLS_NUM_STAGES]; /* persistent grid of each MLS_T_* stage in blocks; 0 = one block per item */
-  int stencil_zc;             /* z extent of a level-stencil tile: 16 or 8 (16 applies to windows <= 6) */
+  int stencil_zc;             /* z extent of a level-stencil tile: 16 or 8 (16 applies to FP32 tiles with windows <= 6) */
   double tuned_ms;            /* one evaluation with this shape, as timed by the autotuner (0: not timed) */
   double stage_ms[MLS_NUM_STAGES]; /* its MLS_T_* stages (0: not timed) */
 } mls_batch_tuning;

@@ -311,7 +311,7 @@ mls_status build_phases(mls_batch_s* B) {
   // ------------------------------------------------ level stencils (all levels < l of all chains)
   for (int Rt : {8, 6, 4}) {
     int zc = B->tune.stencil_zc;
-    if (!stencil_tile_ok(Rt, zc)) zc = 8;
+    if (!stencil_tile_ok(Rt, zc, !mixed)) zc = 8;
     const int var = Rt | (zc << 8) | (mixed ? 0x10000 : 0);
     HostPhase st;
     st.ph.kernel = BK_STENCIL;
@@ -649,7 +649,7 @@ mls_status mls_batch_create(int nbox, const mls_params* per_box, const int64_t* 
       set_error("box " + std::to_string(b) + ": " + mls_last_error());
       return fail(st);
     }
-    if (P->levels > 1 && (P->stencil_kernel != 1 || !stencil_tile_ok(stencil_window(P), 8))) {
+    if (P->levels > 1 && (P->stencil_kernel != 1 || !stencil_tile_ok(stencil_window(P), 8, false))) {
       set_error("box " + std::to_string(b) + ": batched level stencils need a window of at most 8 grid points "
                 "(2a / h <= 8)");
       return fail(MLS_ERR_UNSUPPORTED);

@@ -438,8 +438,8 @@ struct mls_plan_s {
   float* d_row_wf_tile = nullptr;  // the same in FP32 (mixed precision)
   int4* d_tiles = nullptr;         // (level-1, tile x, tile y, tile z) of the tiled stencil
   int ntiles = 0;
-  int stencil_kernel = 1;          // 1: LDS tile kernel, 0: plane-streaming kernel
-  int stencil_min_waves = 1536;    // launch-shape knob of the level stencils
+  int stencil_kernel = 1;          // 1: LDS tile kernel, 0: slab kernel (FP64) for every window
+  int stencil_zc = 16;             // z extent of a level-stencil tile
   double* d_row_w = nullptr;
   float* d_row_wf = nullptr;
   double taps_wsum = 0;            // sum of level-1 weights (mean term in mixed precision)
@@ -557,7 +557,7 @@ int stencil_window(const mls_plan_s* P);
 // the rows argument for a batched launch of level g.
 int coarsest_rows_form(const GridDims& g);
 int coarsest_blocks(const GridDims& g, int outs, int rows);
-int stencil_tile_zc(int R, bool f64);
+int stencil_tile_zc(int R, bool f64, int64_t tiles16);
 
 // kernel launchers (one per file); all enqueue on `s` and return the launch status
 hipError_t launch_binning(mls_plan_s* P, int n, const double* pos, const double* c6, hipStream_t s);
@@ -637,7 +637,7 @@ inline double* lb_ant_scratch(const mls_plan_s* P, int k) {
   return P->d_ant_scratch ? P->d_ant_scratch + (size_t)lb_slot(P, k) * P->ant_scratch_n : nullptr;
 }
 // z extent candidates of a stencil tile for window R
-bool stencil_tile_ok(int R, int zc);
+bool stencil_tile_ok(int R, int zc, bool f64);
 
 // constants of the pair kernels (pair.hip) and their template variant (2:
 // eq:gamma folded in, 0: any member of the smoothing family)

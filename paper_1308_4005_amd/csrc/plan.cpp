@@ -372,7 +372,13 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
   }
   if (l > 1) {
     const int Rw = stencil_window(P);
-    const int zc = stencil_tile_zc(Rw, P->precision != MLS_MIXED);
+    int64_t tiles16 = 0;
+    for (int k = 1; k < l; ++k) {
+      const GridDims& g = P->lv[k - 1].g;
+      tiles16 += (int64_t)((g.n[0] + 7) / 8) * ((g.n[1] + 7) / 8) * ((g.n[2] + 15) / 16);
+    }
+    const int zc = stencil_tile_zc(Rw, P->precision != MLS_MIXED, tiles16);
+    P->stencil_zc = zc;
     for (int k = 1; k < l; ++k) {
       const GridDims& g = P->lv[k - 1].g;
       const int tx = (g.n[0] + 7) / 8, ty = (g.n[1] + 7) / 8, tz = (g.n[2] + zc - 1) / zc;

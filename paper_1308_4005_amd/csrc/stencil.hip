@@ -5,13 +5,11 @@
 //   level l:       e^l[mu] = sum_nu K_l[(mu - nu) mod n_l] q^l[nu]   with the pre-summed periodic kernel of
 //                  eq:last-grid-periodic-transformed (all-to-all, FP64).
 //
-// Level stencil kernel (k_stencil_stream): a block owns a TX x TY column of
-// output points and a chunk of ZC planes.  It streams input planes z through
-// LDS (one xy plane plus an R-wide periodic halo at a time).  For every tap
-// column (|dx|,|dy|) the up to four mirror images q[x+-dx, y+-dy] are summed
-// once and then applied to the 2 hz + 1 outputs z_in - hz .. z_in + hz held
-// in a rolling register window acc[0..2R]; after each plane the oldest output
-// is complete, written, and the window shifts.
+// Level stencil kernels: a block owns an 8 x 8 x ZC box of output points and
+// reads the box plus an R-wide periodic halo from LDS, whole (k_stencil_tile)
+// or in slabs of z planes (k_stencil_slab).  For every tap column (|dx|,|dy|)
+// the up to four mirror images q[x+-dx, y+-dy] of a plane are summed once and
+// applied to the outputs within hz planes, held in registers.
 #include <algorithm>
 
 #include "device_math.h"
@@ -44,115 +42,6 @@ __global__ void __launch_bounds__(kBlock) k_stencil_taps_f64(const double* __res
   e[mu] = scale * acc;
 }
 
-// Apply one tap column with half height hz (compile-time) to the window.
-template <class T, int R, int HZ>
-__device__ __forceinline__ void apply_column(T (&acc)[2 * R + 1], T s, const T* __restrict__ w) {
-  acc[R] += w[0] * s;
-#pragma unroll
-  for (int d = 1; d <= HZ; ++d) {
-    const T wd = w[d] * s;
-    acc[R + d] += wd;
-    acc[R - d] += wd;
-  }
-}
-
-template <class T, int R, int H = 0>
-__device__ __forceinline__ void apply_switch(int hz, T (&acc)[2 * R + 1], T s, const T* __restrict__ w) {
-  if constexpr (H <= R) {
-    if (hz == H) {
-      apply_column<T, R, H>(acc, s, w);
-      return;
-    }
-    apply_switch<T, R, H + 1>(hz, acc, s, w);
-  }
-}
-
-// W waves share one 8 x 8 output column and one LDS plane; wave w applies
-// the tap columns [wave_rows[w], wave_rows[w+1]) (balanced by cost on the
-// host) and the W partial sums of each finished output are added in LDS.
-// The wrapped halo offsets of the plane are computed once per block, and the
-// next plane is prefetched into registers while the current one is used.
-template <class T, int R, int W>
-__global__ void __launch_bounds__(64 * W) k_stencil_stream(const T* __restrict__ q, GridDims g,
-                                                           const StencilRow* __restrict__ rows,
-                                                           const int* __restrict__ wave_rows,
-                                                           const T* __restrict__ wts, T scale, int zc,
-                                                           T* __restrict__ e) {
-  constexpr int TX = 8, TY = 8;
-  constexpr int SX = TX + 2 * R, SY = TY + 2 * R, NP = SX * SY, NT = 64 * W;
-  constexpr int PER = (NP + NT - 1) / NT;
-  __shared__ T plane[NP];
-  __shared__ T red[W][64];
-  const int tid = threadIdx.x, lane = tid & 63;
-  // wave index made provably uniform: row and weight reads become scalar
-  // loads and the hz dispatch scalar branches
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tx = lane & 7, ty = lane >> 3;
-  const int x0 = blockIdx.x * TX, y0 = blockIdx.y * TY;
-  const int z0 = blockIdx.z * zc;
-  const int zend = min(z0 + zc, g.n[2]);
-  const int x = x0 + tx, y = y0 + ty;
-  const bool owner = x < g.n[0] && y < g.n[1];
-  const size_t pstride = (size_t)g.n[0] * g.n[1];
-  int off[PER];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int i = tid + k * NT;
-    const int lx = i % SX, ly = i / SX;
-    off[k] = i < NP ? wrapi(y0 - R + ly, g.n[1]) * g.n[0] + wrapi(x0 - R + lx, g.n[0]) : 0;
-  }
-  const int r0 = wave_rows[wv], r1 = wave_rows[wv + 1];
-  T acc[2 * R + 1];
-#pragma unroll
-  for (int k = 0; k <= 2 * R; ++k) acc[k] = T(0);
-  T pre[PER];
-  {
-    const T* src = q + (size_t)wrapi(z0 - R, g.n[2]) * pstride;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) pre[k] = src[off[k]];
-  }
-  const T* c = plane + (ty + R) * SX + (tx + R);
-  for (int zin = z0 - R; zin < zend + R; ++zin) {
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if (tid + k * NT < NP) plane[tid + k * NT] = pre[k];
-    __syncthreads();
-    if (zin + 1 < zend + R) {
-      const T* src = q + (size_t)wrapi(zin + 1, g.n[2]) * pstride;
-#pragma unroll
-      for (int k = 0; k < PER; ++k) pre[k] = src[off[k]];
-    }
-    for (int r = r0; r < r1; ++r) {
-      const StencilRow row = rows[r];
-      T s;
-      if (row.dx == 0 && row.dy == 0) {
-        s = c[0];
-      } else if (row.dx == 0) {
-        s = c[-row.dy * SX] + c[row.dy * SX];
-      } else if (row.dy == 0) {
-        s = c[-row.dx] + c[row.dx];
-      } else {
-        s = (c[-row.dy * SX - row.dx] + c[-row.dy * SX + row.dx]) + (c[row.dy * SX - row.dx] + c[row.dy * SX + row.dx]);
-      }
-      apply_switch<T, R>(row.hz, acc, s, wts + row.woff);
-    }
-    // output z = zin - R is complete: add the W partial sums
-    red[wv][lane] = acc[0];
-    __syncthreads();
-    const int zout = zin - R;
-    if (wv == 0 && owner && zout >= z0 && zout < zend) {
-      T sum = red[0][lane];
-#pragma unroll
-      for (int w = 1; w < W; ++w) sum += red[w][lane];
-      e[(size_t)zout * pstride + (size_t)y * g.n[0] + x] = scale * sum;
-    }
-#pragma unroll
-    for (int k = 0; k < 2 * R; ++k) acc[k] = acc[k + 1];
-    acc[2 * R] = T(0);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Tiled level stencil.  A block owns an 8 x 8 x ZC box of output points of
 // one level (all levels share one launch through a tile table).  It loads the
@@ -170,7 +59,15 @@ __global__ void __launch_bounds__(64 * W) k_stencil_stream(const T* __restrict__
 // 2R) doubles, 90 KB at R = 6: one block per CU; at depth 8, 64 KB: two)
 constexpr int tile_zc(int R, bool f64) { return R <= 6 && !f64 ? 16 : 8; }
 
-int stencil_tile_zc(int R, bool f64) { return tile_zc(R, f64); }
+// tiles16: the plan's tiles at depth 16.  FP64 slab tiles of depth 16 read
+// fewer planes per output, and pay once they fill the chip (R = 8 / R = 12,
+// depth 8 against 16: 585 tiles of depth 8 50 / 54 us, 3159 tiles 235 / 209;
+// 4000 atoms 53 / 73, 585 tiles 146 / 133, 3159 tiles 630 / 467; at R = 10
+// depth 16 was never faster, 159 / 176 us at 1975 tiles).
+int stencil_tile_zc(int R, bool f64, int64_t tiles16) {
+  if (f64 && ((R > 6 && R <= 8 && tiles16 >= 1024) || (R > 10 && R <= 12 && tiles16 >= 256))) return 16;
+  return tile_zc(R, f64);
+}
 
 namespace {
 
@@ -259,7 +156,7 @@ __device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 t
   // the column index is wave-uniform, so the rows and weights are scalar
   // loads (staging them in LDS measured slower)
   const StencilRow* __restrict__ rows = V.rows;
-  const T* __restrict__ wts = (const T*)V.wts;
+  const T* __restrict__ wts = (const T*)(const void*)V.wts;
   const int r0 = V.wave_rows[wv], r1 = V.wave_rows[wv + 1];
   for (int r = r0; r < r1; ++r) {
     const StencilRow row = rows[r];
@@ -290,6 +187,164 @@ template <class T, int R, int ZC, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_tile(StencilLaunch L, const int4* __restrict__ tiles) {
   const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
   stencil_tile<T, R, ZC, W>(L.lv[tinfo.x], tinfo);
+}
+
+// FP64 tile read in NCH slabs of z planes: the same columns, weights and
+// register outputs, but only a slab of the ZC + 2 R input planes is in LDS at a
+// time: an FP64 tile of R = 10 would take 176 KB.  LDS reads bound it (four
+// 8-byte reads per plane and column against 2 hz + 1 FMAs per output), so the
+// slabs are as large as two blocks per CU allow.  Level stencils of 60,013 atoms
+// at a = 4, h = 0.8 (56^3 and two coarser levels, R = 10): 950 us with a kernel
+// that streamed single planes through LDS, 46 us here; R = 12 at 300,000 atoms
+// 467 us; R = 8 at 10^6 atoms 266 us with whole tiles (110 KB, one block per
+// CU), 209 us here.  Up to R = 6 the whole tile (64 KB) is faster: 71 against
+// 82 us at 10^6 atoms in two slabs.
+template <int R, int ZC, int P0, int P1, int HZ>
+__device__ __forceinline__ void slab_column(double (&acc)[ZC], const double* __restrict__ c, int o0, int o1, int o2,
+                                            int o3, const double* __restrict__ w) {
+  constexpr int PS = (8 + 2 * R) * (8 + 2 * R);
+  double wr[HZ + 1];
+#pragma unroll
+  for (int d = 0; d <= HZ; ++d) wr[d] = w[d];
+#pragma unroll
+  for (int p = P0; p < P1; ++p) {
+    const int zi = p - R;   // relative to the first output plane
+    if (zi < -HZ || zi >= ZC + HZ) continue;
+    const double* q = c + (p - P0) * PS;
+    const double s = (q[o0] + q[o1]) + (q[o2] + q[o3]);
+#pragma unroll
+    for (int dz = -HZ; dz <= HZ; ++dz) {
+      const int zo = zi + dz;
+      if (zo >= 0 && zo < ZC) acc[zo] += wr[dz < 0 ? -dz : dz] * s;
+    }
+  }
+}
+
+template <int R, int ZC, int P0, int P1, int H = 0>
+__device__ __forceinline__ void slab_switch(int hz, double (&acc)[ZC], const double* c, int o0, int o1, int o2, int o3,
+                                            const double* w) {
+  if constexpr (H <= R) {
+    if (hz == H) {
+      slab_column<R, ZC, P0, P1, H>(acc, c, o0, o1, o2, o3, w);
+      return;
+    }
+    slab_switch<R, ZC, P0, P1, H + 1>(hz, acc, c, o0, o1, o2, o3, w);
+  }
+}
+
+template <int R, int ZC, int NCH, int W>
+struct SlabShape {
+  static constexpr int SX = 8 + 2 * R, PS = SX * SX, NZ = ZC + 2 * R, SP = (NZ + NCH - 1) / NCH, NT = 64 * W;
+  static constexpr int RZ = 8;   // output planes added up at a time
+  static constexpr int NL = PS * SP > W * RZ * 64 ? PS * SP : W * RZ * 64;
+};
+
+// Slab CH and the ones after it: fill, then every column of the wave.
+template <int R, int ZC, int NCH, int W, int CH>
+__device__ __forceinline__ void slab_pass(const StencilLevel& V, double* slab, const int* wrapx, const int* wrapy,
+                                          const int* wrapz, int tid, int wv, int c0, double (&acc)[ZC]) {
+  if constexpr (CH < NCH) {
+    using S = SlabShape<R, ZC, NCH, W>;
+    constexpr int P0 = CH * S::SP, P1 = P0 + S::SP < S::NZ ? P0 + S::SP : S::NZ;
+    constexpr int NP = S::PS * (P1 - P0), kIters = (NP + S::NT - 1) / S::NT, kFill = 8;
+    const size_t gps = (size_t)V.n[0] * V.n[1];
+    const double* __restrict__ q = V.q;
+    if constexpr (CH > 0) __syncthreads();   // the slab before it has been read
+    // kFill loads in flight per thread; indexes past the slab are clamped
+    for (int b0 = 0; b0 < kIters; b0 += kFill) {
+      double v[kFill];
+#pragma unroll
+      for (int u = 0; u < kFill; ++u) {
+        const int i = min(tid + (b0 + u) * S::NT, NP - 1);
+        const int lx = i % S::SX, ly = (i / S::SX) % S::SX, lz = i / S::PS;
+        v[u] = q[(size_t)wrapz[P0 + lz] * gps + (size_t)wrapy[ly] * V.n[0] + wrapx[lx]];
+      }
+#pragma unroll
+      for (int u = 0; u < kFill; ++u) {
+        const int i = tid + (b0 + u) * S::NT;
+        if (i < NP) slab[i] = v[u];
+      }
+    }
+    __syncthreads();
+    const StencilRow* __restrict__ rows = V.rows;
+    const double* __restrict__ wts = (const double*)(const void*)V.wts;
+    const int r0 = V.wave_rows[wv], r1 = V.wave_rows[wv + 1];
+    for (int r = r0; r < r1; ++r) {
+      const StencilRow row = rows[r];
+      const int o0 = -row.dy * S::SX - row.dx, o1 = -row.dy * S::SX + row.dx;
+      const int o2 = row.dy * S::SX - row.dx, o3 = row.dy * S::SX + row.dx;
+      slab_switch<R, ZC, P0, P1>(row.hz, acc, slab + c0, o0, o1, o2, o3, wts + row.woff);
+    }
+    slab_pass<R, ZC, NCH, W, CH + 1>(V, slab, wrapx, wrapy, wrapz, tid, wv, c0, acc);
+  }
+}
+
+template <int R, int ZC, int NCH, int W>
+__device__ __forceinline__ void stencil_slab(const StencilLevel& V, const int4 tinfo) {
+  using S = SlabShape<R, ZC, NCH, W>;
+  // the slab doubles as the reduction buffer of the W partial sums
+  __shared__ double slab[S::NL];
+  __shared__ int wrapx[S::SX], wrapy[S::SX], wrapz[S::NZ];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x0 = tinfo.y * 8, y0 = tinfo.z * 8, z0 = tinfo.w * ZC;
+  if (tid < S::SX) {
+    wrapx[tid] = wrapi(x0 - R + tid, V.n[0]);
+    wrapy[tid] = wrapi(y0 - R + tid, V.n[1]);
+  }
+  if (tid < S::NZ) wrapz[tid] = wrapi(z0 - R + tid, V.n[2]);
+  __syncthreads();
+  const int tx = lane & 7, ty = ((lane >> 3) & 3) * 2 + (lane >> 5);   // as stencil_tile
+  double acc[ZC];
+#pragma unroll
+  for (int k = 0; k < ZC; ++k) acc[k] = 0.0;
+  slab_pass<R, ZC, NCH, W, 0>(V, slab, wrapx, wrapy, wrapz, tid, wv, (ty + R) * S::SX + (tx + R), acc);
+  const int x = x0 + tx, y = y0 + ty;
+  const size_t gps = (size_t)V.n[0] * V.n[1];
+#pragma unroll
+  for (int k0 = 0; k0 < ZC; k0 += S::RZ) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < S::RZ; ++k) slab[(wv * S::RZ + k) * 64 + lane] = acc[k0 + k];
+    __syncthreads();
+    for (int k = wv; k < S::RZ; k += W) {
+      const int z = z0 + k0 + k;
+      if (x < V.n[0] && y < V.n[1] && z < V.n[2]) {
+        double sum = slab[k * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) sum += slab[(w * S::RZ + k) * 64 + lane];
+        V.e[(size_t)z * gps + (size_t)y * V.n[0] + x] = V.scale * sum;
+      }
+    }
+  }
+}
+
+// Batched, one block per item.  Without the loop over items the compiler keeps
+// 78 instead of 127 VGPRs (FP32, R = 6), so that LDS alone limits the blocks
+// per CU to three instead of the registers to two.
+template <class T, int R, int ZC, int W>
+__global__ void __launch_bounds__(64 * W) k_stencil_tile_each(const StencilLevel* __restrict__ lv,
+                                                              const int4* __restrict__ tiles) {
+  const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
+  const StencilLevel V = lv[tinfo.x];
+  stencil_tile<T, R, ZC, W>(V, tinfo);
+}
+
+template <int R, int ZC, int NCH, int W>
+__global__ void __launch_bounds__(64 * W) k_stencil_slab(StencilLaunch L, const int4* __restrict__ tiles) {
+  const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
+  stencil_slab<R, ZC, NCH, W>(L.lv[tinfo.x], tinfo);
+}
+
+template <int R, int ZC, int NCH, int W>
+__global__ void __launch_bounds__(64 * W) k_stencil_slab_batched(const StencilLevel* __restrict__ lv,
+                                                                 const int4* __restrict__ tiles, int ntiles) {
+  for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x) {
+    const int4 tinfo = tiles[t];
+    const StencilLevel V = lv[tinfo.x];
+    stencil_slab<R, ZC, NCH, W>(V, tinfo);
+    __syncthreads();
+  }
 }
 
 // MFMA recast of the FP32 tile (window R <= 6, 8 x 8 x 16 outputs per block).
@@ -389,7 +444,7 @@ __global__ void __launch_bounds__(64 * W) k_stencil_mfma(StencilLaunch L, const 
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) acc[nb] = mfma_f4{0.0f, 0.0f, 0.0f, 0.0f};
   const StencilRow* __restrict__ rows = V.rows;
-  const float* __restrict__ atab = (const float*)V.wts;
+  const float* __restrict__ atab = (const float*)(const void*)V.wts;
   const int r0 = V.wave_rows[wv], r1 = V.wave_rows[wv + 1];
   for (int r = r0; r < r1; ++r) {
     const StencilRow row = rows[r];
@@ -422,7 +477,8 @@ __global__ void __launch_bounds__(64 * W) k_stencil_tile_batched(const StencilLe
                                                                  const int4* __restrict__ tiles, int ntiles) {
   for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x) {
     const int4 tinfo = tiles[t];
-    stencil_tile<T, R, ZC, W>(lv[tinfo.x], tinfo);
+    const StencilLevel V = lv[tinfo.x];
+    stencil_tile<T, R, ZC, W>(V, tinfo);
     __syncthreads();
   }
 }
@@ -609,34 +665,6 @@ struct Coarsest {
 };
 inline int nblocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
-constexpr int kTX = 8, kTY = 8;
-
-template <class T, int R>
-hipError_t launch_stream(const mls_plan_s* P, const T* q, GridDims g, const T* w, T scale, T* e, hipStream_t s) {
-  constexpr int W = kStencilWaves;
-  // z chunk: halve while the launch has fewer than ~1.5k waves, but keep the
-  // 2R warm-up planes below half of the chunk
-  const int xy = nblocks(g.n[0], kTX) * nblocks(g.n[1], kTY);
-  int zc = g.n[2];
-  while (zc > 4 * R && (int64_t)xy * W * nblocks(g.n[2], zc) < P->stencil_min_waves) zc = (zc + 1) / 2;
-  dim3 grid(nblocks(g.n[0], kTX), nblocks(g.n[1], kTY), nblocks(g.n[2], zc));
-  k_stencil_stream<T, R, W><<<grid, 64 * W, 0, s>>>(q, g, P->d_rows, P->d_wave_rows, w, scale, zc, e);
-  return hipGetLastError();
-}
-
-template <class T>
-hipError_t launch_stream_r(const mls_plan_s* P, int R, const T* q, GridDims g, const T* w, T scale, T* e,
-                           hipStream_t s) {
-  switch (R) {
-    case 1: case 2: case 3: case 4: return launch_stream<T, 4>(P, q, g, w, scale, e, s);
-    case 5: case 6: return launch_stream<T, 6>(P, q, g, w, scale, e, s);
-    case 7: case 8: return launch_stream<T, 8>(P, q, g, w, scale, e, s);
-    case 9: case 10: return launch_stream<T, 10>(P, q, g, w, scale, e, s);
-    case 11: case 12: return launch_stream<T, 12>(P, q, g, w, scale, e, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 }  // namespace
 
 // Blocks of the coarsest-level kernel for grid g with `outs` output points
@@ -652,19 +680,20 @@ int stencil_window(const mls_plan_s* P) {
   return std::max(P->stencil_R[0], std::max(P->stencil_R[1], P->stencil_R[2]));
 }
 
-template <class T, int R>
-hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
-  constexpr int kTileZ = tile_zc(R, sizeof(T) == 8);
-  StencilLaunch L{};
+// Level descriptors of levels 1..kmax of a plan (the head of its tile table)
+// and their number of tiles.
+int stencil_levels(const mls_plan_s* P, const void* wts, int kmax, StencilLaunch& L) {
+  const int zc = P->stencil_zc;
+  L = StencilLaunch{};
   L.nlev = P->levels - 1;
   int t = 0;
   for (int k = 1; k < P->levels; ++k) {
-    Level& Lv = P->lv[k - 1];
+    const Level& Lv = P->lv[k - 1];
     StencilLevel& V = L.lv[k - 1];
     V.q = Lv.q;
     V.e = Lv.e;
     for (int d = 0; d < 3; ++d) V.n[d] = Lv.g.n[d];
-    V.tiles_z = nblocks(Lv.g.n[2], kTileZ);
+    V.tiles_z = nblocks(Lv.g.n[2], zc);
     V.tile0 = t;
     V.scale = std::ldexp(1.0, -6 * (k - 1));
     V.inv_size = 1.0 / (double)Lv.g.size;
@@ -674,11 +703,35 @@ hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
     V.sum_xi = P->sum_q ? P->sum_q : P->d_scratch;
     V.wsum = P->taps_wsum;
     t += nblocks(Lv.g.n[0], 8) * nblocks(Lv.g.n[1], 8) * V.tiles_z;
-    // the tile table lists the levels in order: levels 1..kmax are its head
     if (k == kmax) break;
   }
-  k_stencil_tile<T, R, kTileZ, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
+  return t;
+}
+
+template <class T, int R, int ZC = tile_zc(R, sizeof(T) == 8)>
+hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
+  StencilLaunch L;
+  const int t = stencil_levels(P, wts, kmax, L);
+  k_stencil_tile<T, R, ZC, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
+}
+
+template <int R, int ZC, int NCH>
+hipError_t launch_slab(mls_plan_s* P, hipStream_t s, int kmax) {
+  StencilLaunch L;
+  const int t = stencil_levels(P, P->d_row_w_tile, kmax, L);
+  k_stencil_slab<R, ZC, NCH, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_slab_f64(mls_plan_s* P, int R, hipStream_t s, int kmax) {
+  const bool deep = P->stencil_zc == 16;
+  if (R <= 4) return launch_slab<4, 8, 1>(P, s, kmax);
+  if (R <= 6) return launch_slab<6, 8, 1>(P, s, kmax);
+  if (R <= 8) return deep ? launch_slab<8, 16, 2>(P, s, kmax) : launch_slab<8, 8, 2>(P, s, kmax);
+  if (R <= 10) return launch_slab<10, 8, 3>(P, s, kmax);
+  if (R <= 12) return deep ? launch_slab<12, 16, 5>(P, s, kmax) : launch_slab<12, 8, 4>(P, s, kmax);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_tile_f64(mls_plan_s* P, int R, hipStream_t s, int kmax) {
@@ -686,7 +739,7 @@ hipError_t launch_tile_f64(mls_plan_s* P, int R, hipStream_t s, int kmax) {
   switch (R) {
     case 1: case 2: case 3: case 4: return launch_tile<double, 4>(P, w, s, kmax);
     case 5: case 6: return launch_tile<double, 6>(P, w, s, kmax);
-    case 7: case 8: return launch_tile<double, 8>(P, w, s, kmax);
+    case 7: case 8: return launch_slab_f64(P, R, s, kmax);
     default: return hipErrorInvalidValue;
   }
 }
@@ -757,18 +810,14 @@ hipError_t launch_stencils(mls_plan_s* P, hipStream_t s, int kmax) {
   const int path = stencil_path(P);
   if (path == MLS_STENCIL_TILE_MFMA_F32) return launch_tile_mfma(P, R, s, kmax);
   if (path == MLS_STENCIL_TILE_F32) return launch_tile_f32(P, R, s, kmax);
+  if (path == MLS_STENCIL_STREAM_F64) return launch_slab_f64(P, R, s, kmax);
   if (path == MLS_STENCIL_TILE_F64) return launch_tile_f64(P, R, s, kmax);
   const int ntaps = (int)P->taps.size();
   for (int k = 1; k <= kmax; ++k) {
     Level& L = P->lv[k - 1];
     const double scale = std::ldexp(1.0, -6 * (k - 1));
-    hipError_t e;
-    if (path == MLS_STENCIL_STREAM_F64) {
-      e = launch_stream_r<double>(P, R, L.q, L.g, P->d_row_w, scale, L.e, s);
-    } else {
-      k_stencil_taps_f64<<<nblocks(L.g.size, kBlock), kBlock, 0, s>>>(L.q, L.g, P->d_taps, ntaps, scale, L.e);
-      e = hipGetLastError();
-    }
+    k_stencil_taps_f64<<<nblocks(L.g.size, kBlock), kBlock, 0, s>>>(L.q, L.g, P->d_taps, ntaps, scale, L.e);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -779,17 +828,27 @@ hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s) {
   return launch_one<Coarsest>(CoarsestArgs{L.q, L.g, P->d_Kl, L.e, 1, 0}, coarsest_blocks(L.g, 1, 0), s);
 }
 
-bool stencil_tile_ok(int R, int zc) {
+bool stencil_tile_ok(int R, int zc, bool f64) {
   if (R < 1 || R > 8) return false;
   if (zc == 8) return true;
-  return zc == 16 && R <= 6;
+  return zc == 16 && R <= 6 && !f64;
 }
 
 template <class T, int R, int ZC>
 hipError_t launch_tiles_batched(const BatchPhase& ph, hipStream_t s) {
+  const StencilLevel* lv = (const StencilLevel*)ph.args;
+  const int4* work = (const int4*)ph.work;
+  if (ph.grid > 0 && ph.grid < ph.nwork)
+    k_stencil_tile_batched<T, R, ZC, kStencilWaves><<<ph.grid, 64 * kStencilWaves, 0, s>>>(lv, work, ph.nwork);
+  else
+    k_stencil_tile_each<T, R, ZC, kStencilWaves><<<ph.nwork, 64 * kStencilWaves, 0, s>>>(lv, work);
+  return hipGetLastError();
+}
+
+hipError_t launch_slabs_batched(const BatchPhase& ph, hipStream_t s) {
   const int grid = ph.grid > 0 ? std::min(ph.grid, ph.nwork) : ph.nwork;
-  k_stencil_tile_batched<T, R, ZC, kStencilWaves><<<grid, 64 * kStencilWaves, 0, s>>>(
-      (const StencilLevel*)ph.args, (const int4*)ph.work, ph.nwork);
+  k_stencil_slab_batched<8, 8, 2, kStencilWaves><<<grid, 64 * kStencilWaves, 0, s>>>((const StencilLevel*)ph.args,
+                                                                                    (const int4*)ph.work, ph.nwork);
   return hipGetLastError();
 }
 
@@ -808,11 +867,9 @@ hipError_t launch_batched_stencil(const BatchPhase& ph, hipStream_t s) {
     if (R == 6 && zc == 8) return launch_tiles_batched<float, 6, 8>(ph, s);
     if (R == 8 && zc == 8) return launch_tiles_batched<float, 8, 8>(ph, s);
   } else {
-    if (R == 4 && zc == 16) return launch_tiles_batched<double, 4, 16>(ph, s);
     if (R == 4 && zc == 8) return launch_tiles_batched<double, 4, 8>(ph, s);
-    if (R == 6 && zc == 16) return launch_tiles_batched<double, 6, 16>(ph, s);
     if (R == 6 && zc == 8) return launch_tiles_batched<double, 6, 8>(ph, s);
-    if (R == 8 && zc == 8) return launch_tiles_batched<double, 8, 8>(ph, s);
+    if (R == 8 && zc == 8) return launch_slabs_batched(ph, s);
   }
   return hipErrorInvalidValue;
 }
