@@ -101,122 +101,142 @@ struct PairConstF {
   float L[3];   // box (periodic image shift of the filter's x)
 };
 
-struct OutPtrs {
-  double* forces;
-  double* potential;
-  double* dE_dc6;
+// A pointer of a kernel's argument record, to device memory.  In device code it
+// keeps the global address space: a plain pointer that a kernel loads from a
+// record in memory (the batched form's per-box records) is a generic one, its
+// accesses compile to flat instructions, which no uniform address makes scalar
+// and which wait on the LDS counter as well.
+template <class T>
+struct gptr {
+#ifdef __HIP_DEVICE_COMPILE__
+  __attribute__((address_space(1))) T* p = nullptr;
+  gptr() = default;
+  __host__ __device__ gptr(T* q) : p((__attribute__((address_space(1))) T*)q) {}
+#else
+  T* p = nullptr;
+  gptr() = default;
+  __host__ __device__ gptr(T* q) : p(q) {}
+#endif
+  __host__ __device__ gptr(decltype(nullptr)) {}
+  __host__ __device__ operator T*() const { return (T*)p; }
 };
 
-struct FillArgs { int* p; int n; };
-struct FillDArgs { double* p; int n; };
+struct OutPtrs {
+  gptr<double> forces;
+  gptr<double> potential;
+  gptr<double> dE_dc6;
+};
+
+struct FillArgs { gptr<int> p; int n; };
+struct FillDArgs { gptr<double> p; int n; };
 struct BinCountArgs {
-  const double* pos; const double* c6; int n; CellGeom g;
-  int* cid; int* slot; int* count; double4* xw; int* flags;
+  gptr<const double> pos; gptr<const double> c6; int n; CellGeom g;
+  gptr<int> cid; gptr<int> slot; gptr<int> count; gptr<double4> xw; gptr<int> flags;
   double c6_scale;   // xi = sqrt(c6_scale * c6): 1 for C6, 2 for Lorentz-Berthelot epsilon
-  double* xi_partial = nullptr;   // per-block sums of xi in original order (single plans, mixed)
-  const int* cond = nullptr;      // if set and *cond == 0 the binning is skipped (neighbour reuse)
-  double* xref = nullptr;         // if set: the positions of this binning (neighbour reuse)
+  gptr<double> xi_partial = nullptr;   // per-block sums of xi in original order (single plans, mixed)
+  gptr<const int> cond = nullptr;      // if set and *cond == 0 the binning is skipped (neighbour reuse)
+  gptr<double> xref = nullptr;         // if set: the positions of this binning (neighbour reuse)
 };
 // Neighbour reuse (plans with a skin): after a binning the atoms keep their
 // sorted slots and cells; each later evaluation either bins again (*cond set
 // by the displacement check) or re-gathers the new positions through perm.
-struct DispCheckArgs { const double* pos; const double* xref; int n; double lim2; int* cond; };
+struct DispCheckArgs { gptr<const double> pos; gptr<const double> xref; int n; double lim2; gptr<int> cond; };
 struct RegatherArgs {
-  const double* pos; const int* perm; const int* cell_s; int n; CellGeom g; const int* cond;
-  double4* xs; float4* xr; float* xf; int xf_stride;
+  gptr<const double> pos; gptr<const int> perm; gptr<const int> cell_s; int n; CellGeom g; gptr<const int> cond;
+  gptr<double4> xs; gptr<float4> xr; gptr<float> xf; int xf_stride;
 };
 // molecular dynamics (md.hip): repulsion of eq:disp-pair-pot and velocity Verlet
-struct RepGatherArgs { const int* perm; const double* c12; int n; double* x12s; float* x12f; int* flags; };
+struct RepGatherArgs { gptr<const int> perm; gptr<const double> c12; int n; gptr<double> x12s; gptr<float> x12f; gptr<int> flags; };
 struct RepPairArgs {
-  const double4* xs; const double* x12s; const int* cell_s; const int* cell_start; CellGeom g;
-  int nr[3]; double rc2; int n; double* frep; double* partial;
+  gptr<const double4> xs; gptr<const double> x12s; gptr<const int> cell_s; gptr<const int> cell_start; CellGeom g;
+  int nr[3]; double rc2; int n; gptr<double> frep; gptr<double> partial;
 };
 constexpr int kMdEnd = 1, kMdStart = 2, kMdSlowEnd = 4, kMdSlowStart = 8, kMdMidEnd = 16, kMdMidStart = 32;
 struct MdStepArgs {
-  double* pos; double* vel; const double* forces; const double* inv_mass; int n;
-  double hdt, dt; int mode; double* partial; int* flags;
-  const double* fslow = nullptr;   // multiple time stepping: slow forces and their half-kick factor
+  gptr<double> pos; gptr<double> vel; gptr<const double> forces; gptr<const double> inv_mass; int n;
+  double hdt, dt; int mode; gptr<double> partial; gptr<int> flags;
+  gptr<const double> fslow = nullptr;   // multiple time stepping: slow forces and their half-kick factor
   double hslow = 0.0;
-  const double* fmid = nullptr;    // three time scales: the level-1 grid forces and their factor
+  gptr<const double> fmid = nullptr;    // three time scales: the level-1 grid forces and their factor
   double hmid = 0.0;
 };
 struct LocalOutArgs {
-  const double4* xs; const int* perm; int n; const double* e0; const double* floc; const double* frep;
-  double* forces; double* partial;
+  gptr<const double4> xs; gptr<const int> perm; int n; gptr<const double> e0; gptr<const double> floc; gptr<const double> frep;
+  gptr<double> forces; gptr<double> partial;
 };
 struct LocalEnergyArgs {
-  const double* partial; int nb; const double* rep_partial; int rep_nb; double* energy;
+  gptr<const double> partial; int nb; gptr<const double> rep_partial; int rep_nb; gptr<double> energy;
 };
-struct AddForcesArgs { double* forces; const double* add; int n3; };
-struct MdKineticArgs { const double* partial; int npartial; double* out; };
-struct LbGatherArgs { const int* perm; int n; const double* sigma; double* sig_s; int* flags; float* sig_f; };
+struct AddForcesArgs { gptr<double> forces; gptr<const double> add; int n3; };
+struct MdKineticArgs { gptr<const double> partial; int npartial; gptr<double> out; };
+struct LbGatherArgs { gptr<const int> perm; int n; gptr<const double> sigma; gptr<double> sig_s; gptr<int> flags; gptr<float> sig_f; };
 // partial: if set, per-block sums of the charges (the mean the mixed stencil
 // subtracts)
-struct LbChargeArgs { const double4* xs; const double* sig_s; int n; int k; double* charge; double* partial; };
-struct ScanArgs { int* count; int m; int* start; int* bsum; int* bmax; int* max_count; const int* cond = nullptr; };
+struct LbChargeArgs { gptr<const double4> xs; gptr<const double> sig_s; int n; int k; gptr<double> charge; gptr<double> partial; };
+struct ScanArgs { gptr<int> count; int m; gptr<int> start; gptr<int> bsum; gptr<int> bmax; gptr<int> max_count; gptr<const int> cond = nullptr; };
 // Bucketed binning (single plans): a bucket is a run of 2^shift consecutive
 // cell ids; hist[bucket * nblk + blk] counts the atoms of block blk in the
 // bucket, then (scanned in place, per scan block; bsum: the scan blocks'
 // totals) gives where they start in tmp.
 struct BinBucketArgs {
-  const double* pos; const double* c6; int n; CellGeom g; int* cid; double4* xw; int* flags; double c6_scale;
-  double* xi_partial; const int* cond; double* xref;
-  int shift; int nbucket; int nblk; int* hist;
+  gptr<const double> pos; gptr<const double> c6; int n; CellGeom g; gptr<int> cid; gptr<double4> xw; gptr<int> flags; double c6_scale;
+  gptr<double> xi_partial; gptr<const int> cond; gptr<double> xref;
+  int shift; int nbucket; int nblk; gptr<int> hist;
 };
 struct BucketScatterArgs {
-  const int* cid; int n; int shift; int nbucket; int nblk; const int* hist; const int* bsum; int2* tmp;
-  const int* cond;
+  gptr<const int> cid; int n; int shift; int nbucket; int nblk; gptr<const int> hist; gptr<const int> bsum; gptr<int2> tmp;
+  gptr<const int> cond;
 };
 struct BucketSortArgs {
-  const int* hist; const int* bsum; int nblk; int shift; int nbucket; const int2* tmp; int2* tmp2; int n; int* start;
-  int* perm; const double4* xw; double4* xs; int* cell_s; float4* xr; float* xif; CellGeom g; const int* cond;
-  float* xf; int xf_stride;
+  gptr<const int> hist; gptr<const int> bsum; int nblk; int shift; int nbucket; gptr<const int2> tmp; gptr<int2> tmp2; int n; gptr<int> start;
+  gptr<int> perm; gptr<const double4> xw; gptr<double4> xs; gptr<int> cell_s; gptr<float4> xr; gptr<float> xif; CellGeom g; gptr<const int> cond;
+  gptr<float> xf; int xf_stride;
 };
-struct ScatterArgs { const int* cid; const int* slot; int n; const int* start; int2* perm_tmp; const int* cond = nullptr; };
-struct RankArgs { const int* start; const int2* perm_tmp; int n; int* perm; };
+struct ScatterArgs { gptr<const int> cid; gptr<const int> slot; int n; gptr<const int> start; gptr<int2> perm_tmp; gptr<const int> cond = nullptr; };
+struct RankArgs { gptr<const int> start; gptr<const int2> perm_tmp; int n; gptr<int> perm; };
 // Rank of each atom among its cell's atoms by original index, fused with the
 // gather of the sorted arrays (single plans).
 struct RankGatherArgs {
-  const int* start; const int2* perm_tmp; int n; int* perm; const double4* xw;
-  double4* xs; int* cell_s; float4* xr; float* xif; CellGeom g;
-  const int* cond = nullptr;
-  float* xf = nullptr;    // mixed precision: filter coordinates x, y, z (absolute x, cell-relative y, z), SoA
+  gptr<const int> start; gptr<const int2> perm_tmp; int n; gptr<int> perm; gptr<const double4> xw;
+  gptr<double4> xs; gptr<int> cell_s; gptr<float4> xr; gptr<float> xif; CellGeom g;
+  gptr<const int> cond = nullptr;
+  gptr<float> xf = nullptr;    // mixed precision: filter coordinates x, y, z (absolute x, cell-relative y, z), SoA
   int xf_stride = 0;      // floats per coordinate array of xf
 };
 struct GatherArgs {
-  const int* perm; int n; const double4* xw;
-  double4* xs; int* cell_s; float4* xr; float* xif; CellGeom g;
-  double* xi_partial;   // mixed precision: per-block sums of xi (else null)
-  float* xf = nullptr;  // mixed precision: filter coordinates, SoA
+  gptr<const int> perm; int n; gptr<const double4> xw;
+  gptr<double4> xs; gptr<int> cell_s; gptr<float4> xr; gptr<float> xif; CellGeom g;
+  gptr<double> xi_partial;   // mixed precision: per-block sums of xi (else null)
+  gptr<float> xf = nullptr;  // mixed precision: filter coordinates, SoA
   int xf_stride = 0;
 };
-struct SumXiArgs { int rows; const double* partial; double* out; };   // partials of ceil(rows / 256) gather blocks
+struct SumXiArgs { int rows; gptr<const double> partial; gptr<double> out; };   // partials of ceil(rows / 256) gather blocks
 // The repulsive term of the MD entry points, evaluated by the pair kernels on
 // the pairs they already hold (rc <= a): sorted sqrt(C12) in FP64 (and FP32
 // for the mixed kernel), the cutoff, the sorted (n,3) forces and one energy
 // sum per block.
 struct PairRep {
-  const double* x12; const float* x12f; double rc2; double* frep; double* partial;
+  gptr<const double> x12; gptr<const float> x12f; double rc2; gptr<double> frep; gptr<double> partial;
 };
 struct PairArgs {
-  const double4* xs; const int* cell_s; const int* cstart; int n; CellGeom g; PairConst pc;
-  double* e0; double* floc;
-  const double* sig;      // Lorentz-Berthelot: sorted sigma (source weight e_j s_ij^6)
+  gptr<const double4> xs; gptr<const int> cell_s; gptr<const int> cstart; int n; CellGeom g; PairConst pc;
+  gptr<double> e0; gptr<double> floc;
+  gptr<const double> sig;      // Lorentz-Berthelot: sorted sigma (source weight e_j s_ij^6)
   PairRep rep{};
-  const float* xf = nullptr;   // FP32 filter coordinates (three arrays of xf_stride floats)
+  gptr<const float> xf = nullptr;   // FP32 filter coordinates (three arrays of xf_stride floats)
   int xf_stride = 0;
 };
 struct PairArgsF {
-  const float4* xr; const float* xif; const double4* xs; const int* cell_s; const int* cstart;
-  int n; CellGeom g; PairConstF pc; double* e0; double* floc;
+  gptr<const float4> xr; gptr<const float> xif; gptr<const double4> xs; gptr<const int> cell_s; gptr<const int> cstart;
+  int n; CellGeom g; PairConstF pc; gptr<double> e0; gptr<double> floc;
   PairRep rep{};
-  const float* sig = nullptr;   // Lorentz-Berthelot: sorted sigma in FP32
-  const float* xf = nullptr;    // filter coordinates: x (absolute), y, z (cell-relative) arrays
+  gptr<const float> sig = nullptr;   // Lorentz-Berthelot: sorted sigma in FP32
+  gptr<const float> xf = nullptr;    // filter coordinates: x (absolute), y, z (cell-relative) arrays
   int xf_stride = 0;            // floats per array
 };
 struct AnterpArgs {
-  const double4* xs; const int* cstart; int n; CellGeom cg; GridGeom gg; AntGeom ag; double* q;
-  const double* charge;   // sorted charges (else the xi in xs.w)
+  gptr<const double4> xs; gptr<const int> cstart; int n; CellGeom cg; GridGeom gg; AntGeom ag; gptr<double> q;
+  gptr<const double> charge;   // sorted charges (else the xi in xs.w)
 };
 // Two-phase anterpolation of single plans: blocks of linked cells, each with
 // the range of finest points its atoms reach (unwrapped), laid side by side in
@@ -243,55 +263,55 @@ struct AntTiles {
   int off_cov[3];   // n int4: covering expanded coordinates (-1: none); 16-byte aligned
 };
 struct AnterpTileArgs {
-  const double4* xs; const int* cstart; CellGeom cg; GridGeom gg; AntTiles t; const int* tab;
-  double* scratch; const double* charge; int* flags;
+  gptr<const double4> xs; gptr<const int> cstart; CellGeom cg; GridGeom gg; AntTiles t; gptr<const int> tab;
+  gptr<double> scratch; gptr<const double> charge; gptr<int> flags;
 };
-struct AnterpCollectArgs { AntTiles t; const int* tab; const double* scratch; double* q; GridDims g; };
+struct AnterpCollectArgs { AntTiles t; gptr<const int> tab; gptr<const double> scratch; gptr<double> q; GridDims g; };
 struct TransferArgs {              // restriction (fine -> coarse) and prolongation (coarse -> fine)
-  const double* src; GridDims gs;  // q^{k-1} (restriction) or E^{k+1} (prolongation)
-  const double* add;               // prolongation: e^k added to the interpolated values
-  double* dst; GridDims gd;
+  gptr<const double> src; GridDims gs;  // q^{k-1} (restriction) or E^{k+1} (prolongation)
+  gptr<const double> add;               // prolongation: e^k added to the interpolated values
+  gptr<double> dst; GridDims gd;
 };
 struct InterpArgs {
-  const double4* xs; const int* perm; int n; GridGeom gg; const double* E1; const double* e0;
-  const double* floc; double cself; OutPtrs out; double* partial;
-  const double* frep = nullptr;   // sorted (n,3) repulsive forces added to the output, or null
+  gptr<const double4> xs; gptr<const int> perm; int n; GridGeom gg; gptr<const double> E1; gptr<const double> e0;
+  gptr<const double> floc; double cself; OutPtrs out; gptr<double> partial;
+  gptr<const double> frep = nullptr;   // sorted (n,3) repulsive forces added to the output, or null
   int grid_only = 0;              // 1: the grid part alone (no e0, no local forces)
 };
 // Interpolation over the anterpolation's blocks of linked cells: each block
 // stages the finest-grid values its atoms reach in LDS.
 struct InterpTileArgs {
-  InterpArgs a; const int* cstart; CellGeom cg; AntTiles t; const int* tab; int* flags;
+  InterpArgs a; gptr<const int> cstart; CellGeom cg; AntTiles t; gptr<const int> tab; gptr<int> flags;
 };
 struct EnergyArgs {
-  const double* partial; int nb; double cself; double* energy;
-  const double* rep_partial = nullptr;  // block sums of the repulsive energy (twice E_rep), or null
+  gptr<const double> partial; int nb; double cself; gptr<double> energy;
+  gptr<const double> rep_partial = nullptr;  // block sums of the repulsive energy (twice E_rep), or null
   int rep_nb = 0;
   int add = 0;                          // 1: add to *energy instead of overwriting it
 };
 struct InterpLbArgs {
-  const double4* xs; const double* sig; const int* perm; int n; GridGeom gg; const double* E1[7];
-  const double* e0; const double* floc; double* forces; double* partial;
+  gptr<const double4> xs; gptr<const double> sig; gptr<const int> perm; int n; GridGeom gg; gptr<const double> E1[7];
+  gptr<const double> e0; gptr<const double> floc; gptr<double> forces; gptr<double> partial;
 };
 // outs: points per wave of the wave-per-point form; rows: the level's x
 // extent when the register-row form runs (coarsest_rows_form), else 0
-struct CoarsestArgs { const double* q; GridDims g; const double* K; double* e; int outs; int rows; };
+struct CoarsestArgs { gptr<const double> q; GridDims g; gptr<const double> K; gptr<double> e; int outs; int rows; };
 constexpr int kCoarsestThreads = 512;   // threads per block of the coarsest-level kernel
 constexpr int kCoarsestWaves = kCoarsestThreads / 64;
 
 // One level of the tiled stencil: grids, scale, and the tap tables of its plan.
 struct StencilLevel {
-  const double* q;
-  double* e;
+  gptr<const double> q;
+  gptr<double> e;
   int n[3];
   int tiles_z;                 // z chunks
   int tile0;                   // first tile index of this level
   double scale;                // 2^(-6(k-1))
   double inv_size;             // 1 / points of the level
-  const StencilRow* rows;
-  const int* wave_rows;
-  const void* wts;             // tile weights (double, or float in mixed precision)
-  const double* sum_xi;        // mixed precision: sum of xi (mean of the charges)
+  gptr<const StencilRow> rows;
+  gptr<const int> wave_rows;
+  gptr<const void> wts;             // tile weights (double, or float in mixed precision)
+  gptr<const double> sum_xi;        // mixed precision: sum of xi (mean of the charges)
   double wsum;                 // sum of the level-1 weights
 };
 
@@ -341,7 +361,8 @@ __global__ void __launch_bounds__(K::kThreads) k_batched(const typename K::Args*
   // round by round, each XCD takes one contiguous stretch of the work list
   for (int w = xcd_block(blockIdx.x, gridDim.x); w < nwork; w += gridDim.x) {
     const int2 it = work[w];
-    K::run(args[it.x], it.y);
+    const typename K::Args a = args[it.x];
+    K::run(a, it.y);
     __syncthreads();   // LDS of the item is free before the next one
   }
 }

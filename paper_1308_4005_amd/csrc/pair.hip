@@ -252,6 +252,11 @@ __device__ __forceinline__ const T& at32(const T* base, int j) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (unsigned)j * (unsigned)sizeof(T));
 }
 
+template <class T>
+__device__ __forceinline__ const T& at32(const gptr<const T>& base, int j) {
+  return at32((const T*)base, j);
+}
+
 __device__ __forceinline__ float4 load4f(const float* p) {
   float4 v;
   __builtin_memcpy(&v, p, sizeof(v));   // 4-byte aligned 16-byte load
