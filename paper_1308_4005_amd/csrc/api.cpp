@@ -5,7 +5,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <utility>
 
 #include "mls_internal.h"
 
@@ -578,26 +577,15 @@ mls_status mls_evaluate_lb(mls_plan_t P, int64_t n, const double* pos, const dou
   // the local part, and meet it at interpolation
   hipStream_t g;
   HIP_TRY(fork_chain(P, ni, s, g), "fork");
+  // the grid part of the seven charge vectors, all of them in each launch
+  HIP_TRY(launch_lb_charges(P, ni, g), "charges");
+  HIP_TRY(launch_anterpolate(P, ni, g), "anterpolation");
+  // submitted after the anterpolation, as in evaluate_geometric
   HIP_TRY(launch_pair_lb(P, ni, s, g == s), "pair kernel");
-  // grid part once per charge vector (their grids in turn become the plan's
-  // working levels; the vectors share one charge buffer, in stream order)
-  for (int k = 0; k < 7; ++k) {
-    HIP_TRY(launch_lb_charge(P, ni, k, g), "charges");
-    std::swap(P->lv, P->lb_lv[k]);
-    P->charge = lb_charge_buf(P, k);
-    P->ant_scratch = lb_ant_scratch(P, k);
-    if (P->precision == MLS_MIXED) P->sum_q = lb_sum_buf(P, k);
-    hipError_t e = launch_anterpolate(P, ni, g);
-    if (e == hipSuccess) e = launch_restrictions(P, g);
-    if (e == hipSuccess) e = launch_stencils(P, g);
-    if (e == hipSuccess) e = launch_coarsest(P, g);
-    if (e == hipSuccess) e = launch_prolongations(P, g);
-    P->charge = nullptr;
-    P->ant_scratch = nullptr;
-    P->sum_q = nullptr;
-    std::swap(P->lv, P->lb_lv[k]);
-    if (e != hipSuccess) return hip_fail(e, "grid part");
-  }
+  HIP_TRY(launch_restrictions(P, g), "restriction");
+  HIP_TRY(launch_stencils(P, g), "level stencils");
+  HIP_TRY(launch_coarsest(P, g), "coarsest grid");
+  HIP_TRY(launch_prolongations(P, g), "prolongation");
   if (g != s) {
     HIP_TRY(hipEventRecord(P->ev_join, g), "join");
     HIP_TRY(hipStreamWaitEvent(s, P->ev_join, 0), "join");

@@ -784,18 +784,21 @@ hipError_t launch_lb_gather(mls_plan_s* P, int n, const double* sigma, hipStream
                               nblocks(n + kSortedPad, kBlock), s);
 }
 
-hipError_t launch_lb_charge(mls_plan_s* P, int n, int k, hipStream_t s) {
+hipError_t launch_lb_charges(mls_plan_s* P, int n, hipStream_t s) {
   const bool mixed = P->precision == MLS_MIXED;
+  ChainArgs<LbCharge> c;
+  ChainArgs<SumXiFinal> sum;
+  for (int k = 0; k < kLbVectors; ++k) {
+    c.add(LbChargeArgs{P->d_xs, P->d_sig, n, k, lb_charge_buf(P, k), mixed ? lb_partial_buf(P, k) : nullptr});
+    sum.add(SumXiArgs{n > 0 ? n + kSortedPad : 0, lb_partial_buf(P, k), lb_sum_buf(P, k)});
+  }
   if (n > 0) {
-    hipError_t e = launch_one<LbCharge>(
-        LbChargeArgs{P->d_xs, P->d_sig, n, k, lb_charge_buf(P, k), mixed ? lb_partial_buf(P, k) : nullptr},
-        nblocks(n + kSortedPad, kBlock), s);
+    const hipError_t e = launch_chains(c, nblocks(n + kSortedPad, kBlock), s);
     if (e != hipSuccess) return e;
   }
-  // mixed precision: the sum of this vector's charges, the mean the stencil
+  // mixed precision: the sum of each vector's charges, the mean the stencil
   // subtracts (0 without atoms)
-  if (!mixed) return hipSuccess;
-  return launch_one<SumXiFinal>(SumXiArgs{n > 0 ? n + kSortedPad : 0, lb_partial_buf(P, k), lb_sum_buf(P, k)}, 1, s);
+  return mixed ? launch_chains(sum, 1, s) : hipSuccess;
 }
 
 // The binning kernels; with `cond` they all do nothing when *cond == 0, and

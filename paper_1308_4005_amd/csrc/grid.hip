@@ -1130,100 +1130,112 @@ bool ant_tiles_build(const mls_plan_s* P, AntTiles& T, std::vector<int>& tab, si
 }
 
 template <int CAP>
-hipError_t launch_ant_tile(int order, bool mixed, const AnterpTileArgs& t, int nb, hipStream_t s) {
-  if (order == 4)
-    return mixed ? launch_one<AnterpTile<4, float, CAP>>(t, nb, s) : launch_one<AnterpTile<4, double, CAP>>(t, nb, s);
-  return mixed ? launch_one<AnterpTile<6, float, CAP>>(t, nb, s) : launch_one<AnterpTile<6, double, CAP>>(t, nb, s);
-}
-
-template <int CAP>
 hipError_t launch_interp_tile(int order, bool mixed, const InterpTileArgs& t, int nb, hipStream_t s) {
   if (order == 4)
     return mixed ? launch_one<InterpTile<4, float, CAP>>(t, nb, s) : launch_one<InterpTile<4, double, CAP>>(t, nb, s);
   return mixed ? launch_one<InterpTile<6, float, CAP>>(t, nb, s) : launch_one<InterpTile<6, double, CAP>>(t, nb, s);
 }
 
-hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s) {
-  Level& L1 = P->lv[0];
-  if (P->ant_tiles) {
-    double* scratch = P->ant_scratch ? P->ant_scratch : P->d_ant_scratch;
-    AnterpTileArgs t{P->d_xs, P->d_cell_start, P->cg, finest_geom(P), P->ant, P->d_ant_tab, scratch, P->charge,
-                     P->d_flags};
-    const int nb = P->ant.nb[0] * P->ant.nb[1] * P->ant.nb[2];
-    const bool mixed = P->precision == MLS_MIXED;
-    hipError_t e;
-    if (P->ant_cap == kAntTileSmall) e = launch_ant_tile<kAntTileSmall>(P->order, mixed, t, nb, s);
-    else e = launch_ant_tile<kAntTileMax>(P->order, mixed, t, nb, s);
-    if (e != hipSuccess) return e;
-    AnterpCollectArgs c{P->ant, P->d_ant_tab, scratch, L1.q, L1.g};
-    return launch_one<AnterpCollect>(c, nblocks(L1.g.size, kBlock), s);
+namespace {
+
+template <int P, class W, int CAP>
+hipError_t launch_ant_tile(const mls_plan_s* Pl, const ChainSet& cs, hipStream_t s) {
+  ChainArgs<AnterpTile<P, W, CAP>> t;
+  ChainArgs<AnterpCollect> c;
+  for (int k = 0; k < cs.n; ++k) {
+    const Level& L1 = (*cs.lv[k])[0];
+    t.add(AnterpTileArgs{Pl->d_xs, Pl->d_cell_start, Pl->cg, finest_geom(Pl), Pl->ant, Pl->d_ant_tab, cs.scratch[k],
+                         cs.charge[k], Pl->d_flags});
+    c.add(AnterpCollectArgs{Pl->ant, Pl->d_ant_tab, cs.scratch[k], L1.q, L1.g});
   }
-  AnterpArgs a{P->d_xs, P->d_cell_start, n, P->cg, finest_geom(P), AntGeom{}, L1.q, P->charge};
-  if (anterp_owned_geom(P, a.ag)) {
-    // every owned point is written, so no zero fill is needed
-    const int nb = a.ag.nb[0] * a.ag.nb[1] * a.ag.nb[2];
-    const bool mixed = P->precision == MLS_MIXED;
-    if (P->order == 4 && !mixed) return launch_one<AnterpOwned<4, double>>(a, nb, s);
-    if (P->order == 4) return launch_one<AnterpOwned<4, float>>(a, nb, s);
-    if (!mixed) return launch_one<AnterpOwned<6, double>>(a, nb, s);
-    return launch_one<AnterpOwned<6, float>>(a, nb, s);
-  }
-  hipError_t e = launch_zero(L1.q, L1.g.size, s);
-  if (e != hipSuccess || n == 0) return e;
-  if (P->order == 4) return launch_one<AnterpAtomic<4>>(a, nblocks(n, kBlock), s);
-  return launch_one<AnterpAtomic<6>>(a, nblocks(n, kBlock), s);
+  const hipError_t e = launch_chains(t, Pl->ant.nb[0] * Pl->ant.nb[1] * Pl->ant.nb[2], s);
+  return e != hipSuccess ? e : launch_chains(c, nblocks(Pl->lv[0].g.size, kBlock), s);
 }
 
-hipError_t launch_prolong_into(mls_plan_s* P, const TransferArgs& a, hipStream_t s);
+template <int P, class W>
+hipError_t launch_anterpolate_k(mls_plan_s* Pl, int n, hipStream_t s) {
+  const ChainSet cs = chains(Pl);
+  if (Pl->ant_tiles)
+    return Pl->ant_cap == kAntTileSmall ? launch_ant_tile<P, W, kAntTileSmall>(Pl, cs, s)
+                                        : launch_ant_tile<P, W, kAntTileMax>(Pl, cs, s);
+  ChainArgs<AnterpOwned<P, W>> own;
+  ChainArgs<AnterpAtomic<P>> atom;
+  AntGeom ag;
+  const bool owned = anterp_owned_geom(Pl, ag);
+  for (int k = 0; k < cs.n; ++k) {
+    AnterpArgs a{Pl->d_xs, Pl->d_cell_start, n, Pl->cg, finest_geom(Pl), ag, (*cs.lv[k])[0].q, cs.charge[k]};
+    own.add(a);
+    atom.add(a);
+  }
+  // owner-computes: every owned point is written, so no zero fill is needed
+  if (owned) return launch_chains(own, ag.nb[0] * ag.nb[1] * ag.nb[2], s);
+  for (int k = 0; k < cs.n; ++k) {
+    const hipError_t e = launch_zero((*cs.lv[k])[0].q, Pl->lv[0].g.size, s);
+    if (e != hipSuccess) return e;
+  }
+  return n == 0 ? hipSuccess : launch_chains(atom, nblocks(n, kBlock), s);
+}
+
+// One transfer of every chain; `blocks` of kernel K.
+template <class K>
+hipError_t launch_transfer(const TransferArgs* a, int n, int blocks, hipStream_t s) {
+  ChainArgs<K> c;
+  for (int k = 0; k < n; ++k) c.add(a[k]);
+  return launch_chains(c, blocks, s);
+}
+
+template <int P>
+hipError_t launch_restrict(mls_plan_s* Pl, const TransferArgs* a, int n, hipStream_t s) {
+  const int size = a[0].gd.size;
+  // small levels: counted over the chains, which share the launch
+  if ((int64_t)size * n <= Pl->split_restrict)
+    return launch_transfer<RestrictSplit<P>>(a, n, nblocks((int64_t)size * kRestrictGroup, kBlock), s);
+  return launch_transfer<Restrict<P>>(a, n, nblocks(size, kBlock), s);
+}
+
+template <int P>
+hipError_t launch_prolong(mls_plan_s* Pl, const TransferArgs* a, int n, hipStream_t s) {
+  const int size = a[0].gs.size;
+  if (size <= Pl->split_prolong)
+    return launch_transfer<ProlongSplit<P>>(a, n, nblocks((int64_t)size * ProlongSplit<P>::G, kBlock), s);
+  return launch_transfer<Prolong<P, P == 6>>(a, n, nblocks(size, kBlock), s);
+}
+
+}  // namespace
+
+hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s) {
+  const bool mixed = P->precision == MLS_MIXED;
+  if (P->order == 4)
+    return mixed ? launch_anterpolate_k<4, float>(P, n, s) : launch_anterpolate_k<4, double>(P, n, s);
+  return mixed ? launch_anterpolate_k<6, float>(P, n, s) : launch_anterpolate_k<6, double>(P, n, s);
+}
 
 hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s) {
+  const ChainSet cs = chains(P);
   for (int k = 2; k <= P->levels; ++k) {
-    hipError_t e = launch_restrict(P, k - 1, s);
+    TransferArgs a[kLbVectors];
+    for (int v = 0; v < cs.n; ++v) {
+      const Level &F = (*cs.lv[v])[k - 2], &C = (*cs.lv[v])[k - 1];
+      a[v] = TransferArgs{F.q, F.g, nullptr, C.q, C.g};
+    }
+    const hipError_t e = P->order == 4 ? launch_restrict<4>(P, a, cs.n, s) : launch_restrict<6>(P, a, cs.n, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
 hipError_t launch_prolongations(mls_plan_s* P, hipStream_t s, bool drop_e1) {
+  const ChainSet cs = chains(P);
   for (int k = P->levels - 1; k >= 1; --k) {
-    hipError_t e;
-    if (k == 1 && drop_e1) {
-      Level& F = P->lv[0];
-      Level& C = P->lv[1];
-      e = launch_prolong_into(P, TransferArgs{C.E, C.g, nullptr, F.E, F.g}, s);
-    } else {
-      e = launch_prolong(P, k, s);
+    TransferArgs a[kLbVectors];
+    for (int v = 0; v < cs.n; ++v) {
+      const Level &F = (*cs.lv[v])[k - 1], &C = (*cs.lv[v])[k];
+      a[v] = TransferArgs{C.E, C.g, k == 1 && drop_e1 ? nullptr : F.e, F.E, F.g};
     }
+    const hipError_t e = P->order == 4 ? launch_prolong<4>(P, a, cs.n, s) : launch_prolong<6>(P, a, cs.n, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t launch_restrict(mls_plan_s* P, int k_fine, hipStream_t s) {
-  Level& F = P->lv[k_fine - 1];
-  Level& C = P->lv[k_fine];
-  TransferArgs a{F.q, F.g, nullptr, C.q, C.g};
-  if (C.g.size <= P->split_restrict) {
-    const int nb = nblocks((int64_t)C.g.size * kRestrictGroup, kBlock);
-    return P->order == 4 ? launch_one<RestrictSplit<4>>(a, nb, s) : launch_one<RestrictSplit<6>>(a, nb, s);
-  }
-  if (P->order == 4) return launch_one<Restrict<4>>(a, nblocks(C.g.size, kBlock), s);
-  return launch_one<Restrict<6>>(a, nblocks(C.g.size, kBlock), s);
-}
-
-hipError_t launch_prolong_into(mls_plan_s* P, const TransferArgs& a, hipStream_t s) {
-  if (a.gs.size <= P->split_prolong) {
-    if (P->order == 4) return launch_one<ProlongSplit<4>>(a, nblocks((int64_t)a.gs.size * ProlongSplit<4>::G, kBlock), s);
-    return launch_one<ProlongSplit<6>>(a, nblocks((int64_t)a.gs.size * ProlongSplit<6>::G, kBlock), s);
-  }
-  if (P->order == 4) return launch_one<Prolong<4>>(a, nblocks(a.gs.size, kBlock), s);
-  return launch_one<Prolong<6, true>>(a, nblocks(a.gs.size, kBlock), s);
-}
-
-hipError_t launch_prolong(mls_plan_s* P, int k_fine, hipStream_t s) {
-  Level& F = P->lv[k_fine - 1];
-  Level& C = P->lv[k_fine];
-  return launch_prolong_into(P, TransferArgs{C.E, C.g, F.e, F.E, F.g}, s);
 }
 
 hipError_t launch_interpolate(mls_plan_s* P, int n, double* energy, double* forces, double* potential,

@@ -374,6 +374,35 @@ hipError_t launch_one(const typename K::Args& a, int blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One kernel over the seven charge vectors of a Lorentz-Berthelot plan: the
+// vectors' argument records by value, `blocks` blocks each.
+constexpr int kLbVectors = 7;
+template <class K>
+struct SevenArgs {
+  typename K::Args a[kLbVectors];
+};
+template <class K>
+__global__ void __launch_bounds__(K::kThreads) k_seven(SevenArgs<K> s, int blocks) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int v = b / blocks;
+  K::run(s.a[v], b - v * blocks);
+}
+
+// The records of one grid chain or of seven.
+template <class K>
+struct ChainArgs : SevenArgs<K> {
+  int n = 0;
+  void add(const typename K::Args& x) { this->a[n++] = x; }
+};
+template <class K>
+hipError_t launch_chains(const ChainArgs<K>& c, int blocks, hipStream_t s) {
+  static_assert(sizeof(SevenArgs<K>) <= 3840, "kernel arguments");
+  if (blocks <= 0) return hipSuccess;
+  if (c.n == 1) return launch_one<K>(c.a[0], blocks, s);
+  k_seven<K><<<kLbVectors * blocks, K::kThreads, 0, s>>>(c, blocks);
+  return hipGetLastError();
+}
+
 // Persistent form of k_one for a kernel that should not fill the chip: the
 // grid holds a fixed number of blocks, and block b (on XCD b mod 8) walks the
 // items of its XCD's contiguous share of [0, nwork) with the stride of the
@@ -418,22 +447,17 @@ struct mls_plan_s {
   double a = 0, a2 = 0, inv_a2 = 0, inv_a6 = 0, inv_a8 = 0, cself = 0;
   int continuity = 2;              // k of the smoothing function gamma_k
   int mixing = 0;                  // mls_mixing
-  std::vector<mls::Level> lb_lv[7];  // Lorentz-Berthelot: grids of charge vector k
+  std::vector<mls::Level> lb_lv[mls::kLbVectors];  // Lorentz-Berthelot: grids of charge vector k
   double* d_sig = nullptr;         // Lorentz-Berthelot: sorted sigma (n_max + pad)
   float* d_sigf = nullptr;         // Lorentz-Berthelot, mixed precision: the same in FP32
-  // Lorentz-Berthelot work slots: the single-plan path runs the seven charge
-  // vectors one after another through slot 0; the batched form gives each
-  // vector its own slot (charges, partial sums, their sum, expanded
-  // anterpolation grid) so one launch covers all seven.
-  int lb_slots = 1;
+  // Lorentz-Berthelot: each charge vector has its own slot (charges, partial
+  // sums, their sum, expanded anterpolation grid), so one launch covers all
+  // seven.
   size_t lb_stride = 0;            // doubles per slot of d_charge (n_max + pad)
   int lb_npart = 0;                // partial sums per slot of d_lb_partial
   size_t ant_scratch_n = 0;        // doubles of one expanded anterpolation grid
-  double* d_charge = nullptr;      // Lorentz-Berthelot: sorted charges, lb_slots x lb_stride
+  double* d_charge = nullptr;      // Lorentz-Berthelot: sorted charges, 7 x lb_stride
   double* d_lb_partial = nullptr;  // Lorentz-Berthelot, mixed: per-block charge sums per slot
-  const double* charge = nullptr;  // charges the anterpolation reads (null: xi)
-  double* ant_scratch = nullptr;   // expanded grid the anterpolation uses (null: d_ant_scratch)
-  const double* sum_q = nullptr;   // mixed: sum of the charges the stencils read (null: Sigma xi)
   double gamma_c[5]{};             // gamma_k inside the unit ball: sum_j gamma_c[j] rho^(12 j)
   mls::CellGeom cg{};
   double invh1[3]{};               // n_1 / L
@@ -597,12 +621,10 @@ hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep =
                        bool alone = false);
 hipError_t launch_scan(mls_plan_s* P, int* count, int m, int* start, hipStream_t s);
 hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s);
-hipError_t launch_restrict(mls_plan_s* P, int k_fine, hipStream_t s);
 // Level stencils of levels 1..kmax (kmax = 0: all levels below the coarsest).
 hipError_t launch_stencils(mls_plan_s* P, hipStream_t s, int kmax = 0);
 int stencil_path(const mls_plan_s* P);   // mls_stencil_path of the plan
 hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s);
-hipError_t launch_prolong(mls_plan_s* P, int k_fine, hipStream_t s);
 // All restrictions (levels 2..l) and all prolongations (l-1..1) of an evaluation.
 hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s);
 // drop_e1: the last prolongation writes E^1 = prolongated E^2 without e^1
@@ -615,11 +637,11 @@ hipError_t launch_prolongations(mls_plan_s* P, hipStream_t s, bool drop_e1 = fal
 constexpr int kInterpRep = 1, kInterpGridOnly = 2, kInterpLevel1 = 4, kInterpNoSelf = 8;
 hipError_t launch_interpolate(mls_plan_s* P, int n, double* energy, double* forces,
                               double* potential, double* dE_dc6, hipStream_t s, int mode = 0);
-// Lorentz-Berthelot pieces: sorted sigma and flags, the sorted charges of
-// vector k, and the interpolation of all seven vectors with the energy
+// Lorentz-Berthelot pieces: sorted sigma and flags, the sorted charges of the
+// seven vectors (and their sums), and the interpolation of all seven vectors with the energy
 hipError_t launch_lb_gather(mls_plan_s* P, int n, const double* sigma, hipStream_t s);
 hipError_t launch_pair_lb(mls_plan_s* P, int n, hipStream_t s, bool alone = false);
-hipError_t launch_lb_charge(mls_plan_s* P, int n, int k, hipStream_t s);
+hipError_t launch_lb_charges(mls_plan_s* P, int n, hipStream_t s);
 hipError_t launch_interpolate_lb(mls_plan_s* P, int n, double* energy, double* forces, hipStream_t s);
 hipError_t launch_binning_scaled(mls_plan_s* P, int n, const double* pos, const double* c6, double scale,
                                  hipStream_t s);
@@ -646,16 +668,43 @@ bool anterp_owned_geom(const mls_plan_s* P, AntGeom& ag);
 // tables of the two-phase anterpolation; false when no blocking fits
 bool ant_tiles_build(const mls_plan_s* P, AntTiles& t, std::vector<int>& tab, size_t& scratch, int cap);
 
-// Lorentz-Berthelot slot of charge vector k and its buffers.
-inline int lb_slot(const mls_plan_s* P, int k) { return P->lb_slots > 1 ? k : 0; }
-inline double* lb_charge_buf(const mls_plan_s* P, int k) { return P->d_charge + (size_t)lb_slot(P, k) * P->lb_stride; }
+// Lorentz-Berthelot: the buffers of charge vector k.
+inline double* lb_charge_buf(const mls_plan_s* P, int k) { return P->d_charge + (size_t)k * P->lb_stride; }
 inline double* lb_partial_buf(const mls_plan_s* P, int k) {
-  return P->d_lb_partial ? P->d_lb_partial + (size_t)lb_slot(P, k) * P->lb_npart : nullptr;
+  return P->d_lb_partial ? P->d_lb_partial + (size_t)k * P->lb_npart : nullptr;
 }
 // the sum of the charges of vector k (mixed precision; after Sigma xi in slot 0)
-inline double* lb_sum_buf(const mls_plan_s* P, int k) { return P->d_scratch + 8 + lb_slot(P, k); }
+inline double* lb_sum_buf(const mls_plan_s* P, int k) { return P->d_scratch + 8 + k; }
 inline double* lb_ant_scratch(const mls_plan_s* P, int k) {
-  return P->d_ant_scratch ? P->d_ant_scratch + (size_t)lb_slot(P, k) * P->ant_scratch_n : nullptr;
+  return P->d_ant_scratch ? P->d_ant_scratch + (size_t)k * P->ant_scratch_n : nullptr;
+}
+
+// The grid chains of one evaluation: one, or under Lorentz-Berthelot mixing
+// one per charge vector, each with its grids, charges (null: xi), expanded
+// anterpolation grid and (mixed precision) the sum of its charges.
+struct ChainSet {
+  int n = 1;
+  const std::vector<Level>* lv[kLbVectors] = {};
+  const double* charge[kLbVectors] = {};
+  double* scratch[kLbVectors] = {};
+  const double* sum[kLbVectors] = {};
+};
+inline ChainSet chains(const mls_plan_s* P) {
+  ChainSet c;
+  if (P->mixing != MLS_LORENTZ_BERTHELOT) {
+    c.lv[0] = &P->lv;
+    c.scratch[0] = P->d_ant_scratch;
+    c.sum[0] = P->d_scratch;
+    return c;
+  }
+  c.n = kLbVectors;
+  for (int k = 0; k < kLbVectors; ++k) {
+    c.lv[k] = &P->lb_lv[k];
+    c.charge[k] = lb_charge_buf(P, k);
+    c.scratch[k] = lb_ant_scratch(P, k);
+    c.sum[k] = lb_sum_buf(P, k);
+  }
+  return c;
 }
 // z extent candidates of a stencil tile for window R
 bool stencil_tile_ok(int R, int zc, bool f64);

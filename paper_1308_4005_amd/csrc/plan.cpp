@@ -509,14 +509,12 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
   if (P->mixing == MLS_LORENTZ_BERTHELOT) {
     // seven charge vectors: one set of grids each (Sec. II.D)
     ALLOC(P->d_sig, N + kSortedPad);
-    const int slots = P->lb_slots > 1 ? 7 : 1;
-    P->lb_slots = slots;
     P->lb_stride = N + kSortedPad;
-    ALLOC(P->d_charge, (size_t)slots * P->lb_stride);
+    ALLOC(P->d_charge, (size_t)kLbVectors * P->lb_stride);
     if (P->precision == MLS_MIXED) {
       ALLOC(P->d_sigf, N + kSortedPad);
       P->lb_npart = (int)((P->lb_stride + 255) / 256);
-      ALLOC(P->d_lb_partial, (size_t)slots * P->lb_npart);
+      ALLOC(P->d_lb_partial, (size_t)kLbVectors * P->lb_npart);
     }
     for (int r = 0; r < 7; ++r) {
       P->lb_lv[r] = P->lv;
@@ -548,7 +546,7 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
   if (P->ant_tiles) {
     ALLOC(P->d_ant_tab, ant_tab.size());
     P->ant_scratch_n = ant_scratch;
-    ALLOC(P->d_ant_scratch, ant_scratch * (P->mixing == MLS_LORENTZ_BERTHELOT ? P->lb_slots : 1));
+    ALLOC(P->d_ant_scratch, ant_scratch * (P->mixing == MLS_LORENTZ_BERTHELOT ? kLbVectors : 1));
   }
 #undef ALLOC
   hipError_t e;

@@ -71,10 +71,29 @@ int stencil_tile_zc(int R, bool f64, int64_t tiles16) {
 
 namespace {
 
+// The level stencils of one grid chain, or of the seven of a Lorentz-Berthelot
+// plan: the chains share the levels' geometry and tables, and block b takes
+// tile b mod ntiles of chain b / ntiles.
 struct StencilLaunch {
-  StencilLevel lv[16];
+  StencilLevel lv[16];   // q, e and sum_xi per chain:
+  gptr<const double> q[kLbVectors][16];
+  gptr<double> e[kLbVectors][16];
+  gptr<const double> sum[kLbVectors];
   int nlev;
+  int ntiles;
 };
+
+__device__ __forceinline__ StencilLevel stencil_level(const StencilLaunch& L, const int4* __restrict__ tiles,
+                                                      int4& tinfo) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int c = b / L.ntiles;
+  tinfo = tiles[b - c * L.ntiles];
+  StencilLevel V = L.lv[tinfo.x];
+  V.q = L.q[c][tinfo.x];
+  V.e = L.e[c][tinfo.x];
+  V.sum_xi = L.sum[c];
+  return V;
+}
 
 template <class T, int HZ, int ZC>
 __device__ __forceinline__ void tile_column(T (&acc)[ZC], const T* __restrict__ c, int o0, int o1, int o2, int o3,
@@ -185,8 +204,9 @@ __device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 t
 // One plan: all levels of the plan in one launch, level descriptors by value.
 template <class T, int R, int ZC, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_tile(StencilLaunch L, const int4* __restrict__ tiles) {
-  const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
-  stencil_tile<T, R, ZC, W>(L.lv[tinfo.x], tinfo);
+  int4 tinfo;
+  const StencilLevel V = stencil_level(L, tiles, tinfo);
+  stencil_tile<T, R, ZC, W>(V, tinfo);
 }
 
 // FP64 tile read in NCH slabs of z planes: the same columns, weights and
@@ -332,8 +352,9 @@ __global__ void __launch_bounds__(64 * W) k_stencil_tile_each(const StencilLevel
 
 template <int R, int ZC, int NCH, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_slab(StencilLaunch L, const int4* __restrict__ tiles) {
-  const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
-  stencil_slab<R, ZC, NCH, W>(L.lv[tinfo.x], tinfo);
+  int4 tinfo;
+  const StencilLevel V = stencil_level(L, tiles, tinfo);
+  stencil_slab<R, ZC, NCH, W>(V, tinfo);
 }
 
 template <int R, int ZC, int NCH, int W>
@@ -406,8 +427,8 @@ __global__ void __launch_bounds__(64 * W) k_stencil_mfma(StencilLaunch L, const 
   constexpr int NL = NP > W * ZC * 64 ? NP : W * ZC * 64;
   __shared__ float tile[NL];
   __shared__ int wrapx[SX], wrapy[SY], wrapz[SZH];
-  const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
-  const StencilLevel& V = L.lv[tinfo.x];
+  int4 tinfo;
+  const StencilLevel V = stencil_level(L, tiles, tinfo);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x0 = tinfo.y * 8, y0 = tinfo.z * 8, z0 = tinfo.w * ZC;
@@ -680,38 +701,42 @@ int stencil_window(const mls_plan_s* P) {
   return std::max(P->stencil_R[0], std::max(P->stencil_R[1], P->stencil_R[2]));
 }
 
-// Level descriptors of levels 1..kmax of a plan (the head of its tile table)
-// and their number of tiles.
-int stencil_levels(const mls_plan_s* P, const void* wts, int kmax, StencilLaunch& L) {
+// Descriptors of levels 1..kmax of a plan's chains; returns the blocks of a
+// launch over them (kmax = l - 1: all; the tile table lists the levels in
+// order, so levels 1..kmax are its head).
+int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts, int kmax, StencilLaunch& L) {
+  static_assert(sizeof(StencilLaunch) <= 3840, "kernel arguments");
   const int zc = P->stencil_zc;
-  L = StencilLaunch{};
+  const ChainSet cs = chains(P);
   L.nlev = P->levels - 1;
   int t = 0;
-  for (int k = 1; k < P->levels; ++k) {
+  for (int k = 1; k <= kmax; ++k) {
     const Level& Lv = P->lv[k - 1];
     StencilLevel& V = L.lv[k - 1];
-    V.q = Lv.q;
-    V.e = Lv.e;
     for (int d = 0; d < 3; ++d) V.n[d] = Lv.g.n[d];
     V.tiles_z = nblocks(Lv.g.n[2], zc);
     V.tile0 = t;
     V.scale = std::ldexp(1.0, -6 * (k - 1));
     V.inv_size = 1.0 / (double)Lv.g.size;
-    V.rows = P->d_rows;
+    V.rows = rows;
     V.wave_rows = P->d_wave_rows;
     V.wts = wts;
-    V.sum_xi = P->sum_q ? P->sum_q : P->d_scratch;
     V.wsum = P->taps_wsum;
     t += nblocks(Lv.g.n[0], 8) * nblocks(Lv.g.n[1], 8) * V.tiles_z;
-    if (k == kmax) break;
+    for (int v = 0; v < cs.n; ++v) {
+      L.q[v][k - 1] = (*cs.lv[v])[k - 1].q;
+      L.e[v][k - 1] = (*cs.lv[v])[k - 1].e;
+    }
   }
-  return t;
+  for (int v = 0; v < cs.n; ++v) L.sum[v] = cs.sum[v];
+  L.ntiles = t;
+  return t * cs.n;
 }
 
 template <class T, int R, int ZC = tile_zc(R, sizeof(T) == 8)>
 hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
   StencilLaunch L;
-  const int t = stencil_levels(P, wts, kmax, L);
+  const int t = stencil_levels(P, P->d_rows, wts, kmax, L);
   k_stencil_tile<T, R, ZC, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
@@ -719,7 +744,7 @@ hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
 template <int R, int ZC, int NCH>
 hipError_t launch_slab(mls_plan_s* P, hipStream_t s, int kmax) {
   StencilLaunch L;
-  const int t = stencil_levels(P, P->d_row_w_tile, kmax, L);
+  const int t = stencil_levels(P, P->d_rows, P->d_row_w_tile, kmax, L);
   k_stencil_slab<R, ZC, NCH, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
@@ -760,27 +785,8 @@ hipError_t launch_tile_f32(mls_plan_s* P, int R, hipStream_t s, int kmax) {
 
 template <int R>
 hipError_t launch_mfma(mls_plan_s* P, hipStream_t s, int kmax) {
-  StencilLaunch L{};
-  L.nlev = P->levels - 1;
-  int t = 0;
-  for (int k = 1; k < P->levels; ++k) {
-    Level& Lv = P->lv[k - 1];
-    StencilLevel& V = L.lv[k - 1];
-    V.q = Lv.q;
-    V.e = Lv.e;
-    for (int d = 0; d < 3; ++d) V.n[d] = Lv.g.n[d];
-    V.tiles_z = nblocks(Lv.g.n[2], 16);
-    V.tile0 = t;
-    V.scale = std::ldexp(1.0, -6 * (k - 1));
-    V.inv_size = 1.0 / (double)Lv.g.size;
-    V.rows = P->d_rows_mfma;
-    V.wave_rows = P->d_wave_rows;
-    V.wts = P->d_mfma_a;
-    V.sum_xi = P->sum_q ? P->sum_q : P->d_scratch;
-    V.wsum = P->taps_wsum;
-    t += nblocks(Lv.g.n[0], 8) * nblocks(Lv.g.n[1], 8) * V.tiles_z;
-    if (k == kmax) break;
-  }
+  StencilLaunch L;
+  const int t = stencil_levels(P, P->d_rows_mfma, P->d_mfma_a, kmax, L);
   k_stencil_mfma<R, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
@@ -813,19 +819,26 @@ hipError_t launch_stencils(mls_plan_s* P, hipStream_t s, int kmax) {
   if (path == MLS_STENCIL_STREAM_F64) return launch_slab_f64(P, R, s, kmax);
   if (path == MLS_STENCIL_TILE_F64) return launch_tile_f64(P, R, s, kmax);
   const int ntaps = (int)P->taps.size();
-  for (int k = 1; k <= kmax; ++k) {
-    Level& L = P->lv[k - 1];
-    const double scale = std::ldexp(1.0, -6 * (k - 1));
-    k_stencil_taps_f64<<<nblocks(L.g.size, kBlock), kBlock, 0, s>>>(L.q, L.g, P->d_taps, ntaps, scale, L.e);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  const ChainSet cs = chains(P);
+  for (int v = 0; v < cs.n; ++v)
+    for (int k = 1; k <= kmax; ++k) {
+      const Level& L = (*cs.lv[v])[k - 1];
+      const double scale = std::ldexp(1.0, -6 * (k - 1));
+      k_stencil_taps_f64<<<nblocks(L.g.size, kBlock), kBlock, 0, s>>>(L.q, L.g, P->d_taps, ntaps, scale, L.e);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 
 hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s) {
-  Level& L = P->lv[P->levels - 1];
-  return launch_one<Coarsest>(CoarsestArgs{L.q, L.g, P->d_Kl, L.e, 1, 0}, coarsest_blocks(L.g, 1, 0), s);
+  const ChainSet cs = chains(P);
+  ChainArgs<Coarsest> c;
+  for (int v = 0; v < cs.n; ++v) {
+    const Level& L = (*cs.lv[v])[P->levels - 1];
+    c.add(CoarsestArgs{L.q, L.g, P->d_Kl, L.e, 1, 0});
+  }
+  return launch_chains(c, coarsest_blocks(P->lv[P->levels - 1].g, 1, 0), s);
 }
 
 bool stencil_tile_ok(int R, int zc, bool f64) {
