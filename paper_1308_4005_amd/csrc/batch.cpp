@@ -381,25 +381,34 @@ mls_status build_phases(mls_batch_s* B) {
   {
     HostPhase in = make_phase<InterpArgs>(BK_INTERP, MLS_T_INTERP, gvar, nb);
     HostPhase il = make_phase<InterpLbArgs>(BK_INTERP_LB, MLS_T_INTERP, gvar, nb);
+    HostPhase it = make_phase<InterpLbTileArgs>(BK_INTERP_LB_TILE, MLS_T_INTERP, gvar, nb);
     HostPhase en = make_phase<EnergyArgs>(BK_ENERGY, MLS_T_INTERP, 0, nb);
     for (int b : order) {
       mls_plan_s* P = B->plans[b];
       const int n = n_of(b);
       const int64_t o = B->off[b];
+      int ne = nblk(n, 256);   // energy partials
       if (lb) {
         InterpLbArgs a{P->d_xs, P->d_sig, P->d_perm, n, finest(P), {}, P->d_e0, P->d_floc,
                        B->forces ? B->forces + 3 * o : nullptr, P->d_partial};
         for (int k = 0; k < 7; ++k) a.E1[k] = P->lb_lv[k][0].E;
-        set_box(il, b, a, nblk(n, 256));
+        const int nt = P->ant.nb[0] * P->ant.nb[1] * P->ant.nb[2];
+        if (P->ant_tiles && n > 0 && nt <= P->lb_interp_blocks) {
+          ne = nt;
+          set_box(it, b, InterpLbTileArgs{a, P->d_cell_start, P->cg, P->ant, P->d_ant_tab, P->d_flags}, nt);
+        } else {
+          set_box(il, b, a, nblk(n, 256));
+        }
       } else {
         OutPtrs out{B->forces ? B->forces + 3 * o : nullptr, nullptr, B->dE_dc6 ? B->dE_dc6 + o : nullptr};
         set_box(in, b, InterpArgs{P->d_xs, P->d_perm, n, finest(P), P->lv[0].E, P->d_e0, P->d_floc, P->cself, out,
                                   P->d_partial}, nblk(n, 256));
       }
-      set_box(en, b, EnergyArgs{P->d_partial, nblk(n, 256), P->cself, B->energies + b}, 1);
+      set_box(en, b, EnergyArgs{P->d_partial, ne, P->cself, B->energies + b}, 1);
     }
     hp.push_back(std::move(in));
     hp.push_back(std::move(il));
+    hp.push_back(std::move(it));
     hp.push_back(std::move(en));
   }
 
@@ -464,6 +473,7 @@ hipError_t launch_phase(const BatchPhase& ph, hipStream_t s) {
     case BK_PROLONG:
     case BK_INTERP:
     case BK_INTERP_LB:
+    case BK_INTERP_LB_TILE:
     case BK_ENERGY: return launch_batched_grid(ph, s);
     case BK_STENCIL:
     case BK_COARSEST: return launch_batched_stencil(ph, s);

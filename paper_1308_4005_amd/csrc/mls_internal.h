@@ -293,6 +293,9 @@ struct InterpLbArgs {
   gptr<const double4> xs; gptr<const double> sig; gptr<const int> perm; int n; GridGeom gg; gptr<const double> E1[7];
   gptr<const double> e0; gptr<const double> floc; gptr<double> forces; gptr<double> partial;
 };
+struct InterpLbTileArgs {
+  InterpLbArgs a; gptr<const int> cstart; CellGeom cg; AntTiles t; gptr<const int> tab; gptr<int> flags;
+};
 // outs: points per wave of the wave-per-point form; rows: the level's x
 // extent when the register-row form runs (coarsest_rows_form), else 0
 struct CoarsestArgs { gptr<const double> q; GridDims g; gptr<const double> K; gptr<double> e; int outs; int rows; };
@@ -324,7 +327,7 @@ enum BatchKernel {
   BK_PAIR_GENERIC, BK_PAIR_WAVE, BK_PAIR_TRIM_F64, BK_PAIR_TRIM_F32,
   BK_ANT_ATOMIC, BK_ANT_OWNED, BK_ANT_TILE, BK_ANT_COLLECT, BK_RESTRICT, BK_PROLONG, BK_INTERP, BK_ENERGY,
   BK_STENCIL, BK_COARSEST,
-  BK_LB_GATHER, BK_LB_CHARGE, BK_INTERP_LB
+  BK_LB_GATHER, BK_LB_CHARGE, BK_INTERP_LB, BK_INTERP_LB_TILE
 };
 
 struct BatchPhase {
@@ -365,6 +368,32 @@ __global__ void __launch_bounds__(K::kThreads) k_batched(const typename K::Args*
     K::run(a, it.y);
     __syncthreads();   // LDS of the item is free before the next one
   }
+}
+
+// k_batched with one block per item.  Without the loop the compiler keeps fewer
+// values in registers across an item (the FP32 pair kernel 69 VGPRs against
+// 79, the tiled Lorentz-Berthelot interpolation 162 against 236).
+template <class K>
+__global__ void __launch_bounds__(K::kThreads) k_batched_each(const typename K::Args* __restrict__ args,
+                                                              const int2* __restrict__ work) {
+  const int2 it = work[xcd_block(blockIdx.x, gridDim.x)];
+  const typename K::Args a = args[it.x];
+  K::run(a, it.y);
+}
+
+// k_one and k_batched_each for a kernel that has to leave registers for four
+// waves per SIMD (the compiler would take more for its rare path).
+template <class K>
+__global__ void __launch_bounds__(K::kThreads, 4) k_one_dense(typename K::Args a) {
+  K::run(a, xcd_block(blockIdx.x, gridDim.x));
+}
+
+template <class K>
+__global__ void __launch_bounds__(K::kThreads, 4) k_batched_dense(const typename K::Args* __restrict__ args,
+                                                                  const int2* __restrict__ work) {
+  const int2 it = work[xcd_block(blockIdx.x, gridDim.x)];
+  const typename K::Args a = args[it.x];
+  K::run(a, it.y);
 }
 
 template <class K>
@@ -432,8 +461,10 @@ hipError_t launch_persist(const typename K::Args& a, int nwork, int blocks, hipS
 template <class K>
 hipError_t launch_batched_phase(const BatchPhase& ph, hipStream_t s) {
   if (ph.nwork == 0) return hipSuccess;
-  const int grid = ph.grid > 0 ? (ph.grid < ph.nwork ? ph.grid : ph.nwork) : ph.nwork;
-  k_batched<K><<<grid, K::kThreads, 0, s>>>((const typename K::Args*)ph.args, (const int2*)ph.work, ph.nwork);
+  const auto* args = (const typename K::Args*)ph.args;
+  const int2* work = (const int2*)ph.work;
+  if (ph.grid > 0 && ph.grid < ph.nwork) k_batched<K><<<ph.grid, K::kThreads, 0, s>>>(args, work, ph.nwork);
+  else k_batched_each<K><<<ph.nwork, K::kThreads, 0, s>>>(args, work);
   return hipGetLastError();
 }
 
@@ -523,6 +554,7 @@ struct mls_plan_s {
   double* d_floc = nullptr;        // 3 n_max sorted local force / (xi_i)
   double* d_partial = nullptr;     // energy partial sums
   int n_partial = 0;
+  int lb_interp_blocks = 0;        // Lorentz-Berthelot: blocks d_partial has room for in the tiled interpolation
   double* d_scratch = nullptr;     // small reductions (grid means)
   int* d_flags = nullptr;          // [0]: input flags (1 position, 2 C6, 4 anterpolation tile overrun,
                                    //      8 C12 / inverse mass / velocity of the MD entry points)

@@ -477,7 +477,13 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
   P->xf_stride = (int)(N + kSortedPad);
   ALLOC(P->d_xf, 3 * (size_t)P->xf_stride);
   P->n_partial = (int)((N + 255) / 256);
-  ALLOC(P->d_partial, 2 * (size_t)P->n_partial + 2);
+  if (P->mixing == MLS_LORENTZ_BERTHELOT && P->ant_tiles) {
+    // the tiled interpolation: beyond 16 blocks per 256 atoms (a gas) each
+    // block's tiles serve too few atoms
+    const int64_t nt = (int64_t)P->ant.nb[0] * P->ant.nb[1] * P->ant.nb[2];
+    if (nt <= 16 * (int64_t)P->n_partial) P->lb_interp_blocks = (int)nt;
+  }
+  ALLOC(P->d_partial, 2 * (size_t)std::max(P->n_partial, P->lb_interp_blocks) + 2);
   ALLOC(P->d_scratch, 64);
   ALLOC(P->d_flags, 4);
   ALLOC(P->d_ncell_max, 4);
