@@ -388,9 +388,9 @@ mls_status mls_plan_destroy(mls_plan_t plan);
  * forces (n,3) and dE_dc6 (n), off being the exclusive prefix sum of
  * n_per_box; energies is device (nbox).  All arrays are device FP64 owned by
  * the caller; forces and dE_dc6 may be NULL.  Outputs are overwritten.
- * Changing any of the five pointers between calls rebuilds the launch tables
- * and the graph, which synchronises the device; calls with the same pointers
- * are enqueue-only.  Errors: as mls_evaluate; mls_batch_create returns
+ * Calls are enqueue-only, with new pointers too, except the first, the one
+ * after mls_batch_set_tuning, and one with new pointers on another stream than
+ * the call before (they synchronise the device).  Errors: as mls_evaluate; mls_batch_create returns
  * MLS_ERR_UNSUPPORTED for a box whose level-stencil window 2a/h exceeds 8
  * grid points.  A batch is not thread-safe.
  * ------------------------------------------------------------------------- */
@@ -412,7 +412,6 @@ mls_status mls_batch_evaluate(mls_batch_t batch, const double* pos, const double
  * vectors of every box in one launch.
  *   eps, sigma  device (n) FP64 in the batch's row layout, finite and >= 0
  *   energies    device (nbox); forces device (n,3) or NULL
- * Changing any of the six pointers rebuilds the launch tables as above.
  * Errors: as mls_batch_evaluate; MLS_ERR_INVALID_ARG on a geometric batch
  * (and mls_batch_evaluate on a Lorentz-Berthelot batch). */
 mls_status mls_batch_evaluate_lb(mls_batch_t batch, const double* pos, const double* eps, const double* sigma,

@@ -43,13 +43,12 @@ struct mls_batch_s {
   void* arena = nullptr;
   bool built = false;
 
-  // caller buffers the phases were built for
-  const double* pos = nullptr;
-  const double* c6 = nullptr;        // C6, or epsilon under Lorentz-Berthelot mixing
-  const double* sigma = nullptr;     // Lorentz-Berthelot: sigma
-  double* energies = nullptr;
-  double* forces = nullptr;
-  double* dE_dc6 = nullptr;
+  // the caller's arrays of the last evaluation, and their device copy, which
+  // the kernels read
+  BatchIO io{};
+  BatchIO* d_io = nullptr;
+  bool ran = false;                  // some evaluation was enqueued
+  bool always_set_io = false;        // an evaluation was captured: its replays write d_io too
 
   mls_batch_tuning tune{};
   bool tune_pending = false;
@@ -135,8 +134,8 @@ struct Chain {
   const double* sum;      // mixed precision: sum of the charges
 };
 
-// Build the phase list of one evaluation for the current caller buffers and
-// tuning, and upload it (one arena).  Boxes are visited largest first so the
+// Build the phase list of one evaluation for the current tuning, and upload it
+// (one arena).  Boxes are visited largest first so the
 // work lists start with the longest items.
 mls_status build_phases(mls_batch_s* B) {
   drop_phases(B);
@@ -184,7 +183,7 @@ mls_status build_phases(mls_batch_s* B) {
       const int64_t o = B->off[b];
       set_box(fill, b, FillArgs{P->d_count, nc}, nblk(nc, 256));
       // xi = sqrt(C6), or e = sqrt(2 eps) under Lorentz-Berthelot mixing
-      set_box(cnt, b, BinCountArgs{B->pos + 3 * o, B->c6 + o, n, P->cg, P->d_cid, P->d_slot, P->d_count, P->d_xw,
+      set_box(cnt, b, BinCountArgs{io_offset<const double>(3 * o), io_offset<const double>(o), n, P->cg, P->d_cid, P->d_slot, P->d_count, P->d_xw,
                                    P->d_flags, lb ? 2.0 : 1.0}, nblk(n, 256));
       ScanArgs sa{P->d_count, nc, P->d_cell_start, P->d_bsum, P->d_bmax, P->d_ncell_max};
       set_box(s1, b, sa, scan_blocks(nc));
@@ -198,7 +197,7 @@ mls_status build_phases(mls_batch_s* B) {
               nblk(n + kSortedPad, 256));
       if (xi_sum) set_box(x2, b, SumXiArgs{n + kSortedPad, P->d_partial, P->d_scratch}, 1);
       if (lb)
-        set_box(sg, b, LbGatherArgs{P->d_perm, n, B->sigma + o, P->d_sig, P->d_flags, P->d_sigf},
+        set_box(sg, b, LbGatherArgs{P->d_perm, n, io_offset<const double>(o), P->d_sig, P->d_flags, P->d_sigf},
                 nblk(n + kSortedPad, 256));
     }
     for (HostPhase* h : {&fill, &cnt, &s1, &s2, &s3, &sc, &rk, &ga, &x2, &sg})
@@ -390,7 +389,7 @@ mls_status build_phases(mls_batch_s* B) {
       int ne = nblk(n, 256);   // energy partials
       if (lb) {
         InterpLbArgs a{P->d_xs, P->d_sig, P->d_perm, n, finest(P), {}, P->d_e0, P->d_floc,
-                       B->forces ? B->forces + 3 * o : nullptr, P->d_partial};
+                       io_offset<double>(3 * o), P->d_partial};
         for (int k = 0; k < 7; ++k) a.E1[k] = P->lb_lv[k][0].E;
         const int nt = P->ant.nb[0] * P->ant.nb[1] * P->ant.nb[2];
         if (P->ant_tiles && n > 0 && nt <= P->lb_interp_blocks) {
@@ -400,11 +399,11 @@ mls_status build_phases(mls_batch_s* B) {
           set_box(il, b, a, nblk(n, 256));
         }
       } else {
-        OutPtrs out{B->forces ? B->forces + 3 * o : nullptr, nullptr, B->dE_dc6 ? B->dE_dc6 + o : nullptr};
+        OutPtrs out{io_offset<double>(3 * o), nullptr, io_offset<double>(o)};
         set_box(in, b, InterpArgs{P->d_xs, P->d_perm, n, finest(P), P->lv[0].E, P->d_e0, P->d_floc, P->cself, out,
                                   P->d_partial}, nblk(n, 256));
       }
-      set_box(en, b, EnergyArgs{P->d_partial, ne, P->cself, B->energies + b}, 1);
+      set_box(en, b, EnergyArgs{P->d_partial, ne, P->cself, io_offset<double>(b)}, 1);
     }
     hp.push_back(std::move(in));
     hp.push_back(std::move(il));
@@ -452,6 +451,7 @@ mls_status build_phases(mls_batch_s* B) {
       at += align(h->work.size() * sizeof(int2));
     }
     ph.grid = B->tune.blocks[ph.stage];
+    ph.io = B->d_io;
     B->phases.push_back(ph);
   }
   if (total > 0) HIP_TRY(hipMemcpy(dev, host.data(), total, hipMemcpyHostToDevice), "batch: upload phase tables");
@@ -672,6 +672,11 @@ mls_status mls_batch_create(int nbox, const mls_params* per_box, const int64_t* 
   if (e == hipSuccess) e = hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming);
   if (e != hipSuccess) return fail(hip_fail(e, "batch: streams and events"));
+  if (hipMalloc((void**)&B->d_io, sizeof(BatchIO)) != hipSuccess) {
+    (void)hipGetLastError();
+    set_error("batch: allocation of the pointer record failed");
+    return fail(MLS_ERR_OOM);
+  }
   *out = B;
   return MLS_OK;
 }
@@ -694,25 +699,26 @@ mls_status batch_evaluate(mls_batch_t B, const double* pos, const double* c6, co
   if (dev != B->device) { set_error(w + ": current device differs from the batch's device"); return MLS_ERR_INVALID_ARG; }
   hipStream_t s = (hipStream_t)stream;
   mls_status st;
-  const bool same_io = B->built && pos == B->pos && c6 == B->c6 && sigma == B->sigma && energies == B->energies &&
-                       forces == B->forces && dE_dc6 == B->dE_dc6;
-  if (!same_io) {
-    // the phase tables hold the caller's pointers: wait for work that may
-    // still read the old tables before replacing them
-    if (B->built) HIP_TRY(hipDeviceSynchronize(), "batch: synchronise");
-    B->pos = pos;
-    B->c6 = c6;
-    B->sigma = sigma;
-    B->energies = energies;
-    B->forces = forces;
-    B->dE_dc6 = dE_dc6;
-    if ((st = build_phases(B)) != MLS_OK) return st;
+  if (!B->built && (st = build_phases(B)) != MLS_OK) return st;
+  const bool same_io = B->io.pos == pos && B->io.c6 == c6 && B->io.sigma == sigma && B->io.energies == energies &&
+                       B->io.forces == forces && B->io.dE_dc6 == dE_dc6;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &capture), "batch: capture status");
+  B->always_set_io |= capture != hipStreamCaptureStatusNone;
+  if (!same_io || B->always_set_io) {
+    // in stream order after the evaluations before it; work of another
+    // stream that may still read the old pointers is waited for
+    if (B->ran && B->last_stream != s && capture == hipStreamCaptureStatusNone)
+      HIP_TRY(hipDeviceSynchronize(), "batch: synchronise");
+    B->io = BatchIO{pos, c6, sigma, energies, forces, dE_dc6};
+    HIP_TRY(launch_set_io(B->d_io, B->io, s), "batch: launch");
   }
   if (B->tune_pending) {
     B->tune_pending = false;
     if ((st = autotune(B, s)) != MLS_OK) return st;
   }
   B->last_stream = s;
+  B->ran = true;
   if (!B->use_graph) return run_phases(B, s, nullptr);
   if (!B->exec) {
     HIP_TRY(hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeRelaxed), "batch: begin capture");
@@ -810,6 +816,7 @@ mls_status mls_batch_destroy(mls_batch_t B) {
   if (!B) return MLS_OK;
   if (B->built) (void)hipDeviceSynchronize();
   drop_phases(B);
+  if (B->d_io) (void)hipFree(B->d_io);
   for (auto& e : B->events) (void)hipEventDestroy(e);
   if (B->cap_stream) (void)hipStreamDestroy(B->cap_stream);
   if (B->side) {

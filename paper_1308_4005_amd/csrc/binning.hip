@@ -740,9 +740,16 @@ __global__ void k_zero_i(int* __restrict__ p, int64_t n) {
   for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
+__global__ void k_set_io(BatchIO* to, BatchIO io) { *to = io; }
+
 inline int nblocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
 }  // namespace
+
+hipError_t launch_set_io(BatchIO* to, const BatchIO& io, hipStream_t s) {
+  k_set_io<<<1, 1, 0, s>>>(to, io);
+  return hipGetLastError();
+}
 
 int scan_blocks(int ncell) { return nblocks(ncell, kScanItems); }
 

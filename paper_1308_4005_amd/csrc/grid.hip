@@ -1499,7 +1499,7 @@ template <int P>
 hipError_t launch_batched_interp_lb(const BatchPhase& ph, hipStream_t s) {
   using K = InterpLbTile<P, kAntTileMax>;
   if (ph.nwork == 0 || (ph.grid > 0 && ph.grid < ph.nwork)) return launch_batched_phase<K>(ph, s);
-  k_batched_dense<K><<<ph.nwork, K::kThreads, 0, s>>>((const typename K::Args*)ph.args, (const int2*)ph.work);
+  k_batched_dense<K><<<ph.nwork, K::kThreads, 0, s>>>((const typename K::Args*)ph.args, (const int2*)ph.work, ph.io);
   return hipGetLastError();
 }
 

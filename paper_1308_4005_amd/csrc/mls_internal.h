@@ -330,6 +330,36 @@ enum BatchKernel {
   BK_LB_GATHER, BK_LB_CHARGE, BK_INTERP_LB, BK_INTERP_LB_TILE
 };
 
+// The caller's arrays of a batched evaluation, in device memory: written by a
+// small kernel on the caller's stream (launch_set_io) when they change, so the
+// launch tables and the graph do not depend on them.  The batch's argument
+// records hold byte offsets into them in their place; bind_io adds the base (a
+// null base stays null).
+struct BatchIO {
+  gptr<const double> pos, c6, sigma;   // c6: C6, or epsilon under Lorentz-Berthelot mixing
+  gptr<double> energies, forces, dE_dc6;
+};
+template <class T>
+__device__ __forceinline__ void io_at(gptr<T>& p, T* base) {
+  p = base ? (T*)((const char*)base + (size_t)(T*)p) : (T*)nullptr;
+}
+template <class T>
+inline T* io_offset(int64_t elements) { return (T*)(sizeof(T) * (size_t)elements); }
+template <class A>
+__device__ __forceinline__ void bind_io(A&, const BatchIO*) {}
+__device__ __forceinline__ void bind_io(BinCountArgs& a, const BatchIO* io) {
+  io_at<const double>(a.pos, io->pos);
+  io_at<const double>(a.c6, io->c6);
+}
+__device__ __forceinline__ void bind_io(LbGatherArgs& a, const BatchIO* io) { io_at<const double>(a.sigma, io->sigma); }
+__device__ __forceinline__ void bind_io(InterpArgs& a, const BatchIO* io) {
+  io_at<double>(a.out.forces, io->forces);
+  io_at<double>(a.out.dE_dc6, io->dE_dc6);
+}
+__device__ __forceinline__ void bind_io(InterpLbArgs& a, const BatchIO* io) { io_at<double>(a.forces, io->forces); }
+__device__ __forceinline__ void bind_io(InterpLbTileArgs& a, const BatchIO* io) { bind_io(a.a, io); }
+__device__ __forceinline__ void bind_io(EnergyArgs& a, const BatchIO* io) { io_at<double>(a.energy, io->energies); }
+
 struct BatchPhase {
   int kernel = 0;              // BatchKernel
   int stage = 0;               // MLS_T_* stage it belongs to (timing and tuning)
@@ -338,6 +368,7 @@ struct BatchPhase {
   void* work = nullptr;        // device int2 (box, blk) items, or int4 tiles for BK_STENCIL
   int nwork = 0;
   int grid = 0;                // persistent grid in blocks (0: one block per item)
+  const BatchIO* io = nullptr; // the caller's arrays (device)
 };
 
 // Workgroups of a launch go to the chip's eight XCDs in turn (hardware block
@@ -360,11 +391,13 @@ __global__ void __launch_bounds__(K::kThreads) k_one(typename K::Args a) {
 
 template <class K>
 __global__ void __launch_bounds__(K::kThreads) k_batched(const typename K::Args* __restrict__ args,
-                                                         const int2* __restrict__ work, int nwork) {
+                                                         const int2* __restrict__ work, int nwork,
+                                                         const BatchIO* __restrict__ io) {
   // round by round, each XCD takes one contiguous stretch of the work list
   for (int w = xcd_block(blockIdx.x, gridDim.x); w < nwork; w += gridDim.x) {
     const int2 it = work[w];
-    const typename K::Args a = args[it.x];
+    typename K::Args a = args[it.x];
+    bind_io(a, io);
     K::run(a, it.y);
     __syncthreads();   // LDS of the item is free before the next one
   }
@@ -375,9 +408,11 @@ __global__ void __launch_bounds__(K::kThreads) k_batched(const typename K::Args*
 // 79, the tiled Lorentz-Berthelot interpolation 162 against 236).
 template <class K>
 __global__ void __launch_bounds__(K::kThreads) k_batched_each(const typename K::Args* __restrict__ args,
-                                                              const int2* __restrict__ work) {
+                                                              const int2* __restrict__ work,
+                                                              const BatchIO* __restrict__ io) {
   const int2 it = work[xcd_block(blockIdx.x, gridDim.x)];
-  const typename K::Args a = args[it.x];
+  typename K::Args a = args[it.x];
+  bind_io(a, io);
   K::run(a, it.y);
 }
 
@@ -390,9 +425,11 @@ __global__ void __launch_bounds__(K::kThreads, 4) k_one_dense(typename K::Args a
 
 template <class K>
 __global__ void __launch_bounds__(K::kThreads, 4) k_batched_dense(const typename K::Args* __restrict__ args,
-                                                                  const int2* __restrict__ work) {
+                                                                  const int2* __restrict__ work,
+                                                                  const BatchIO* __restrict__ io) {
   const int2 it = work[xcd_block(blockIdx.x, gridDim.x)];
-  const typename K::Args a = args[it.x];
+  typename K::Args a = args[it.x];
+  bind_io(a, io);
   K::run(a, it.y);
 }
 
@@ -463,8 +500,8 @@ hipError_t launch_batched_phase(const BatchPhase& ph, hipStream_t s) {
   if (ph.nwork == 0) return hipSuccess;
   const auto* args = (const typename K::Args*)ph.args;
   const int2* work = (const int2*)ph.work;
-  if (ph.grid > 0 && ph.grid < ph.nwork) k_batched<K><<<ph.grid, K::kThreads, 0, s>>>(args, work, ph.nwork);
-  else k_batched_each<K><<<ph.nwork, K::kThreads, 0, s>>>(args, work);
+  if (ph.grid > 0 && ph.grid < ph.nwork) k_batched<K><<<ph.grid, K::kThreads, 0, s>>>(args, work, ph.nwork, ph.io);
+  else k_batched_each<K><<<ph.nwork, K::kThreads, 0, s>>>(args, work, ph.io);
   return hipGetLastError();
 }
 
@@ -755,6 +792,7 @@ constexpr int kSplitGroupsF = 512;
 
 // batched launchers: one phase of a batched evaluation (per kernel file)
 hipError_t launch_batched_binning(const BatchPhase& ph, hipStream_t s);
+hipError_t launch_set_io(BatchIO* to, const BatchIO& io, hipStream_t s);
 hipError_t launch_batched_pair(const BatchPhase& ph, hipStream_t s);
 hipError_t launch_batched_grid(const BatchPhase& ph, hipStream_t s);
 hipError_t launch_batched_stencil(const BatchPhase& ph, hipStream_t s);
