@@ -209,10 +209,11 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   HIP_TRY(launch_restrictions(P, g), "restriction");
   HIP_TRY(mark(1 + MLS_T_RESTRICT), "timing event");
   if (after == 2 && (st = pair()) != MLS_OK) return st;
-  HIP_TRY(launch_stencils(P, g), "level stencils");
+  // (one launch; two with per-stage timing)
+  HIP_TRY(launch_stencils(P, ni, g, 0, !ev), "level stencils");
   HIP_TRY(mark(1 + MLS_T_STENCIL), "timing event");
   if (after == 3 && (st = pair()) != MLS_OK) return st;
-  HIP_TRY(launch_coarsest(P, g), "coarsest grid");
+  if (ev) HIP_TRY(launch_coarsest(P, g), "coarsest grid");
   HIP_TRY(mark(1 + MLS_T_COARSEST), "timing event");
   if (after == 4 && (st = pair()) != MLS_OK) return st;
   HIP_TRY(launch_prolongations(P, g), "prolongation");
@@ -257,8 +258,7 @@ hipError_t evaluate_split(mls_plan_t P, int n, const double* pos, const double* 
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
   if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
-  if ((e = launch_stencils(P, g)) != hipSuccess) return e;
-  if ((e = launch_coarsest(P, g)) != hipSuccess) return e;
+  if ((e = launch_stencils(P, n, g, 0, true)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g)) != hipSuccess) return e;
   if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
@@ -288,7 +288,7 @@ hipError_t evaluate_fast_mid(mls_plan_s* P, int n, const double* pos, const doub
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
-  if ((e = launch_stencils(P, g, 1)) != hipSuccess) return e;
+  if ((e = launch_stencils(P, n, g, 1)) != hipSuccess) return e;
   if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
   if (g != s && (e = hipStreamWaitEvent(s, P->ev_join, 0)) != hipSuccess) return e;
@@ -314,8 +314,7 @@ hipError_t evaluate_split3(mls_plan_s* P, int n, const double* pos, const double
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
   if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
-  if ((e = launch_stencils(P, g)) != hipSuccess) return e;
-  if ((e = launch_coarsest(P, g)) != hipSuccess) return e;
+  if ((e = launch_stencils(P, n, g, 0, true)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g, two)) != hipSuccess) return e;
   if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
   if ((e = launch_local_out(P, n, energy, forces, s)) != hipSuccess) return e;
@@ -583,8 +582,7 @@ mls_status mls_evaluate_lb(mls_plan_t P, int64_t n, const double* pos, const dou
   // submitted after the anterpolation, as in evaluate_geometric
   HIP_TRY(launch_pair_lb(P, ni, s, g == s), "pair kernel");
   HIP_TRY(launch_restrictions(P, g), "restriction");
-  HIP_TRY(launch_stencils(P, g), "level stencils");
-  HIP_TRY(launch_coarsest(P, g), "coarsest grid");
+  HIP_TRY(launch_stencils(P, ni, g, 0, true), "level stencils");
   HIP_TRY(launch_prolongations(P, g), "prolongation");
   if (g != s) {
     HIP_TRY(hipEventRecord(P->ev_join, g), "join");

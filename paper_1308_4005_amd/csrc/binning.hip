@@ -805,7 +805,7 @@ hipError_t launch_lb_charges(mls_plan_s* P, int n, hipStream_t s) {
   }
   // mixed precision: the sum of each vector's charges, the mean the stencil
   // subtracts (0 without atoms)
-  return mixed ? launch_chains(sum, 1, s) : hipSuccess;
+  return mixed && !stencil_adds_sum(P, n) ? launch_chains(sum, 1, s) : hipSuccess;
 }
 
 // The binning kernels; with `cond` they all do nothing when *cond == 0, and
@@ -881,7 +881,7 @@ hipError_t launch_binning_reuse(mls_plan_s* P, int n, const double* pos, const d
 }
 
 hipError_t launch_sum_xi(mls_plan_s* P, int n, hipStream_t s) {
-  if (P->precision != MLS_MIXED || n == 0) return hipSuccess;
+  if (P->precision != MLS_MIXED || n == 0 || stencil_adds_sum(P, n)) return hipSuccess;
   // sum of xi: the mean of every grid level's charges (partition of unity),
   // from the binning's per-block partial sums
   SumXiArgs sa{n, P->d_partial, P->d_scratch};

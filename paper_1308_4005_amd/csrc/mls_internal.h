@@ -690,8 +690,12 @@ hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep =
                        bool alone = false);
 hipError_t launch_scan(mls_plan_s* P, int* count, int m, int* start, hipStream_t s);
 hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s);
-// Level stencils of levels 1..kmax (kmax = 0: all levels below the coarsest).
-hipError_t launch_stencils(mls_plan_s* P, hipStream_t s, int kmax = 0);
+// Level stencils of levels 1..kmax (kmax = 0: all levels below the coarsest),
+// and with `coarsest` the coarsest level in the same launch.
+hipError_t launch_stencils(mls_plan_s* P, int n, hipStream_t s, int kmax = 0, bool coarsest = false);
+// mixed precision: the stencils of n atoms take the partial sums of the charges
+// (launch_sum_xi and the sums of launch_lb_charges are then left out)
+bool stencil_adds_sum(const mls_plan_s* P, int64_t n);
 int stencil_path(const mls_plan_s* P);   // mls_stencil_path of the plan
 hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s);
 // All restrictions (levels 2..l) and all prolongations (l-1..1) of an evaluation.

@@ -21,6 +21,25 @@ int stencil_window(const mls_plan_s* P);
 
 namespace {
 
+// The stencils' rows and weights, host-written tables read at uniform indexes,
+// through the constant address space: scalar loads whatever else the kernel
+// stores (the coarsest level's blocks made the compiler read them per lane).
+template <class T>
+using const_table = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ const_table<T> table(const void* p) {
+  return (const_table<T>)p;
+}
+
+// What a launch of the level stencils covers: levels 1..kmax, the coarsest
+// level too, and (mixed precision, sum_rows > 0) the sum of the charges.
+struct StencilOpts {
+  int kmax = 0;
+  bool coarsest = false;
+  int sum_rows = 0;
+};
+
+
 constexpr int kBlock = 256;
 
 // Reference-structured stencil: one thread per output point, taps from the
@@ -71,21 +90,220 @@ int stencil_tile_zc(int R, bool f64, int64_t tiles16) {
 
 namespace {
 
+// Coarsest level: all-to-all over the level (a periodic convolution of the
+// charges with the pre-summed kernel K), with K and the charges staged in LDS
+// when they fit (kCoarseLds points each).
+//
+// Rows path (batched launches), for a level whose x extent N is at most 8
+// and whose staging fits: a lane owns one output row (y, z) and keeps its N sums in
+// registers; the eight waves of the block split the source rows (y', z').
+// Per source row a lane reads the N values of the kernel row
+// ((y - y') mod n_y, (z - z') mod n_z) and the wave reads the N charges of
+// the row (the same address in every lane), then the x-direction convolution
+// of the two rows, N^2 FMAs with the (x - x') mod N offsets fixed at compile
+// time, runs in registers.  Each K value read from LDS serves N FMAs.  The
+// waves' partial rows are added in LDS in wave order (fixed order).  K rows
+// sit at an odd stride in LDS so that the 8-byte reads of one wave spread
+// over the banks.
+//
+// General path, for single plans and the levels the rows path does not
+// take: a wave per output point (a.outs
+// points per wave, one after another): the lanes split the source rows, each
+// lane takes its (y - y', z - z') offset once per row and walks x' with
+// (x - x') mod n_x, then the lanes add their partial sums across the wave
+// (fixed order).
+constexpr int kCoarseLds = 2048;
+constexpr int kCoarseRowsMaxX = 8;
+
+// Either path works in one LDS buffer of 2 kCoarseLds doubles, `lds`.
+
+// x extent of a level the rows path takes, else 0
+__host__ __device__ inline int coarse_rows_n(const GridDims& g) {
+  const int N = g.n[0], nrow = g.n[1] * g.n[2];
+  if (N < 1 || N > kCoarseRowsMaxX) return 0;
+  return (int64_t)nrow * (N | 1) <= kCoarseLds && (int64_t)nrow * N <= kCoarseLds ? N : 0;
+}
+
+template <int N>
+__device__ __forceinline__ void coarsest_rows(const CoarsestArgs& a, int blk, double* lds) {
+  constexpr int S = N | 1;   // LDS stride of a K row, in doubles
+  constexpr int kPer = kCoarseLds / kCoarsestThreads;
+  double* const sk = lds;
+  double* const sq = lds + kCoarseLds;
+  const int n1 = a.g.n[1], n2 = a.g.n[2], nrow = n1 * n2, npt = nrow * N;
+  {
+    // every load of the staging in flight before the first store
+    double vq[kPer], vk[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = min((int)threadIdx.x + u * kCoarsestThreads, npt - 1);
+      vq[u] = a.q[i];
+      vk[u] = a.K[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + u * kCoarsestThreads;
+      if (i < npt) {
+        const int r = i / N;
+        sk[r * S + (i - r * N)] = vk[u];
+        sq[i] = vq[u];
+      }
+    }
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int row = blk * 64 + lane;
+  const int y = row < nrow ? row % n1 : 0, z = row < nrow ? row / n1 : 0;
+  const int r0 = (nrow * wv) / kCoarsestWaves, r1 = (nrow * (wv + 1)) / kCoarsestWaves;
+  double acc[N];
+#pragma unroll
+  for (int x = 0; x < N; ++x) acc[x] = 0.0;
+  int ys = r0 % n1, zs = r0 / n1;
+  for (int r = r0; r < r1; ++r) {
+    const int ky = y - ys + (y < ys ? n1 : 0), kz = z - zs + (z < zs ? n2 : 0);
+    const int kb = (kz * n1 + ky) * S;
+    double k[N], q[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      k[j] = sk[kb + j];
+      q[j] = sq[r * N + j];
+    }
+#pragma unroll
+    for (int xs = 0; xs < N; ++xs)
+#pragma unroll
+      for (int x = 0; x < N; ++x) acc[x] = fma(k[(x - xs + N) % N], q[xs], acc[x]);
+    if (++ys == n1) {
+      ys = 0;
+      ++zs;
+    }
+  }
+  __syncthreads();   // staging no longer read: the buffer takes the partial rows
+  double* const red = lds;
+#pragma unroll
+  for (int x = 0; x < N; ++x) red[(wv * N + x) * 64 + lane] = acc[x];
+  __syncthreads();
+  if (threadIdx.x < 64 * N) {
+    const int x = threadIdx.x >> 6;
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kCoarsestWaves; ++w) v += red[(w * N + x) * 64 + lane];
+    if (row < nrow) a.e[row * N + x] = v;
+  }
+}
+
+template <bool STAGED>
+__device__ __forceinline__ void coarsest_sums(const CoarsestArgs& a, int blk, double* lds) {
+  const GridDims& g = a.g;
+  double* const sk = lds;
+  double* const sq = lds + kCoarseLds;
+  if constexpr (STAGED) {
+    constexpr int kPer = kCoarseLds / kCoarsestThreads;
+    double vq[kPer], vk[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = min((int)threadIdx.x + u * kCoarsestThreads, g.size - 1);
+      vq[u] = a.q[i];
+      vk[u] = a.K[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + u * kCoarsestThreads;
+      if (i < g.size) {
+        sq[i] = vq[u];
+        sk[i] = vk[u];
+      }
+    }
+    __syncthreads();
+  }
+  const double* __restrict__ gK = a.K;
+  const double* __restrict__ gq = a.q;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int n0 = g.n[0], n1 = g.n[1], n2 = g.n[2], n01 = n0 * n1, nrow = n1 * n2;
+  const int b1 = 64 % n1, b2 = 64 / n1, ys0 = lane % n1, zs0 = lane / n1;
+  for (int m = 0; m < a.outs; ++m) {
+    const int mu = (blk * a.outs + m) * kCoarsestWaves + wv;
+    if (mu >= g.size) break;
+    const int x = mu % n0, y = (mu / n0) % n1, z = mu / n01;
+    double acc = 0.0;
+    // (ys, zs) of row r = lane + 64 t, advanced with a carry (no division
+    // per row)
+    int ys = ys0, zs = zs0;
+    for (int r = lane; r < nrow; r += 64) {
+      const int ky = y - ys + (y < ys ? n1 : 0), kz = z - zs + (z < zs ? n2 : 0);
+      const int kr = kz * n01 + ky * n0, qr = r * n0;
+#pragma unroll 4
+      for (int xs = 0; xs < n0; ++xs) {
+        const int kx = x - xs + (x < xs ? n0 : 0);
+        if constexpr (STAGED) acc = fma(sk[kr + kx], sq[qr + xs], acc);
+        else acc = fma(gK[kr + kx], gq[qr + xs], acc);
+      }
+      ys += b1;
+      const int cy = ys >= n1;
+      ys -= cy ? n1 : 0;
+      zs += b2 + cy;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) a.e[mu] = acc;
+  }
+}
+
+struct Coarsest {
+  using Args = CoarsestArgs;
+  static constexpr int kThreads = kCoarsestThreads;
+  static __device__ void run(const Args& a, int blk) {
+    __shared__ double lds[2 * kCoarseLds];
+    switch (a.rows) {
+      case 1: coarsest_rows<1>(a, blk, lds); break;
+      case 2: coarsest_rows<2>(a, blk, lds); break;
+      case 3: coarsest_rows<3>(a, blk, lds); break;
+      case 4: coarsest_rows<4>(a, blk, lds); break;
+      case 5: coarsest_rows<5>(a, blk, lds); break;
+      case 6: coarsest_rows<6>(a, blk, lds); break;
+      case 7: coarsest_rows<7>(a, blk, lds); break;
+      case 8: coarsest_rows<8>(a, blk, lds); break;
+      default:
+        if (a.g.size <= kCoarseLds) coarsest_sums<true>(a, blk, lds);
+        else coarsest_sums<false>(a, blk, lds);
+    }
+  }
+};
 // The level stencils of one grid chain, or of the seven of a Lorentz-Berthelot
 // plan: the chains share the levels' geometry and tables, and block b takes
-// tile b mod ntiles of chain b / ntiles.
+// tile b mod ntiles of chain b / ntiles.  The blocks past the nchain * ntiles
+// tiles, if any, do the coarsest level (ncoarse each): it needs only the last
+// restriction, as the stencils do, and as a launch of its own it cost 4 us of an
+// evaluation's 79 (1000 atoms, FP64), 5 us of a mixed time step's 152 (32000).
 struct StencilLaunch {
   StencilLevel lv[16];   // q, e and sum_xi per chain:
   gptr<const double> q[kLbVectors][16];
   gptr<double> e[kLbVectors][16];
+  // mixed precision: the sum of the charges, or (sum_rows > 0) its partial sums
+  // over 256 rows each, which every block adds up itself
   gptr<const double> sum[kLbVectors];
-  int nlev;
+  int sum_rows;
+  int nchain;
   int ntiles;
+  int ncoarse;
+  gptr<const double> K;  // coarsest level
+  GridDims gc;
+  gptr<const double> qc[kLbVectors];
+  gptr<double> ec[kLbVectors];
 };
 
-__device__ __forceinline__ StencilLevel stencil_level(const StencilLaunch& L, const int4* __restrict__ tiles,
+// A block of the coarsest level: done here (true).
+__device__ __forceinline__ bool coarsest_block(const StencilLaunch& L, int b, double* lds) {
+  const int nt = L.nchain * L.ntiles;
+  if (b < nt) return false;
+  const int c = (b - nt) / L.ncoarse, blk = (b - nt) - c * L.ncoarse;
+  const CoarsestArgs a{L.qc[c], L.gc, L.K, L.ec[c], 1, 0};
+  if (L.gc.size <= kCoarseLds) coarsest_sums<true>(a, blk, lds);
+  else coarsest_sums<false>(a, blk, lds);
+  return true;
+}
+
+__device__ __forceinline__ StencilLevel stencil_level(const StencilLaunch& L, int b, const int4* __restrict__ tiles,
                                                       int4& tinfo) {
-  const int b = xcd_block(blockIdx.x, gridDim.x);
   const int c = b / L.ntiles;
   tinfo = tiles[b - c * L.ntiles];
   StencilLevel V = L.lv[tinfo.x];
@@ -95,9 +313,30 @@ __device__ __forceinline__ StencilLevel stencil_level(const StencilLaunch& L, co
   return V;
 }
 
+// The sum of the charges behind V.sum_xi: read, or added up from its partial
+// sums in the order of SumXiFinal (the same bits); lds is free afterwards.
+__device__ __forceinline__ double charge_sum(const StencilLevel& V, int rows, double* lds) {
+  if (rows <= 0) return *V.sum_xi;
+  constexpr int kRows = 256;
+  const int nb = (rows + kRows - 1) / kRows, t = threadIdx.x;
+  if (t < kRows) {
+    double v = 0.0;
+    for (int i = t; i < nb; i += kRows) v += V.sum_xi[i];
+    lds[t] = v;
+  }
+  __syncthreads();
+  for (int off = kRows / 2; off > 0; off >>= 1) {
+    if (t < off) lds[t] += lds[t + off];
+    __syncthreads();
+  }
+  const double sum = lds[0];
+  __syncthreads();
+  return sum;
+}
+
 template <class T, int HZ, int ZC>
 __device__ __forceinline__ void tile_column(T (&acc)[ZC], const T* __restrict__ c, int o0, int o1, int o2, int o3,
-                                            int pstride, const T* __restrict__ w) {
+                                            int pstride, const_table<T> w) {
   T wr[HZ + 1];
 #pragma unroll
   for (int d = 0; d <= HZ; ++d) wr[d] = w[d];
@@ -115,7 +354,7 @@ __device__ __forceinline__ void tile_column(T (&acc)[ZC], const T* __restrict__ 
 
 template <class T, int R, int ZC, int H = 0>
 __device__ __forceinline__ void tile_switch(int hz, T (&acc)[ZC], const T* c, int o0, int o1, int o2, int o3,
-                                            int pstride, const T* w) {
+                                            int pstride, const_table<T> w) {
   if constexpr (H <= R) {
     if (hz == H) {
       tile_column<T, H, ZC>(acc, c, o0, o1, o2, o3, pstride, w);
@@ -128,13 +367,19 @@ __device__ __forceinline__ void tile_switch(int hz, T (&acc)[ZC], const T* c, in
 // FP32 tiles hold q - mean (mean = sum_i xi / points, the exact mean by the
 // partition of unity); the constant part adds back as mean * sum of weights,
 // since a periodic convolution maps a constant c to c times the weight sum.
+// lds: the tile, then the reduction buffer of the W partial sums (TileShape).
 template <class T, int R, int ZC, int W>
-__device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 tinfo) {
+struct TileShape {
+  static constexpr int SX = 8 + 2 * R, NP = SX * SX * (ZC + 2 * R), NR = W * ZC * 64;
+  static constexpr int NL = NP > NR ? NP : NR;
+  static constexpr int kDoubles = (int)((NL * sizeof(T) + 7) / 8);
+};
+
+template <class T, int R, int ZC, int W>
+__device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 tinfo, double sum_xi, double* lds) {
   constexpr int SX = 8 + 2 * R, SY = 8 + 2 * R, SZ = ZC + 2 * R;
   constexpr int PS = SX * SY, NP = PS * SZ, NT = 64 * W;
-  // the tile doubles as the reduction buffer of the W partial sums
-  constexpr int NL = NP > W * ZC * 64 ? NP : W * ZC * 64;
-  __shared__ T tile[NL];
+  T* const tile = reinterpret_cast<T*>(lds);
   __shared__ int wrapx[SX], wrapy[SY], wrapz[SZ];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -145,7 +390,7 @@ __device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 t
   __syncthreads();
   const size_t gps = (size_t)V.n[0] * V.n[1];
   const double* __restrict__ q = V.q;
-  const double mean = sizeof(T) < sizeof(double) ? *V.sum_xi * V.inv_size : 0.0;
+  const double mean = sizeof(T) < sizeof(double) ? sum_xi * V.inv_size : 0.0;
   // the fill issues kFill global loads per thread before it waits for them
   // (one load per wait leaves the block waiting on memory latency NP / NT
   // times); indexes past the box are clamped, so every load is in range
@@ -174,11 +419,12 @@ __device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 t
   for (int k = 0; k < ZC; ++k) acc[k] = T(0);
   // the column index is wave-uniform, so the rows and weights are scalar
   // loads (staging them in LDS measured slower)
-  const StencilRow* __restrict__ rows = V.rows;
-  const T* __restrict__ wts = (const T*)(const void*)V.wts;
-  const int r0 = V.wave_rows[wv], r1 = V.wave_rows[wv + 1];
+  const const_table<StencilRow> rows = table<StencilRow>(V.rows);
+  const const_table<T> wts = table<T>(V.wts);
+  const const_table<int> wave_rows = table<int>(V.wave_rows);
+  const int r0 = wave_rows[wv], r1 = wave_rows[wv + 1];
   for (int r = r0; r < r1; ++r) {
-    const StencilRow row = rows[r];
+    const StencilRow row{rows[r].dx, rows[r].dy, rows[r].hz, rows[r].woff};
     const int o0 = -row.dy * SX - row.dx, o1 = -row.dy * SX + row.dx;
     const int o2 = row.dy * SX - row.dx, o3 = row.dy * SX + row.dx;
     tile_switch<T, R, ZC>(row.hz, acc, c, o0, o1, o2, o3, PS, wts + row.woff);
@@ -204,9 +450,14 @@ __device__ __forceinline__ void stencil_tile(const StencilLevel& V, const int4 t
 // One plan: all levels of the plan in one launch, level descriptors by value.
 template <class T, int R, int ZC, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_tile(StencilLaunch L, const int4* __restrict__ tiles) {
+  constexpr int kLds = TileShape<T, R, ZC, W>::kDoubles;
+  static_assert(kLds >= 2 * kCoarseLds, "the coarsest level works in the tile's LDS");
+  __shared__ double lds[kLds];
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  if (coarsest_block(L, b, lds)) return;
   int4 tinfo;
-  const StencilLevel V = stencil_level(L, tiles, tinfo);
-  stencil_tile<T, R, ZC, W>(V, tinfo);
+  const StencilLevel V = stencil_level(L, b, tiles, tinfo);
+  stencil_tile<T, R, ZC, W>(V, tinfo, sizeof(T) < sizeof(double) ? charge_sum(V, L.sum_rows, lds) : 0.0, lds);
 }
 
 // FP64 tile read in NCH slabs of z planes: the same columns, weights and
@@ -221,7 +472,7 @@ __global__ void __launch_bounds__(64 * W) k_stencil_tile(StencilLaunch L, const 
 // 82 us at 10^6 atoms in two slabs.
 template <int R, int ZC, int P0, int P1, int HZ>
 __device__ __forceinline__ void slab_column(double (&acc)[ZC], const double* __restrict__ c, int o0, int o1, int o2,
-                                            int o3, const double* __restrict__ w) {
+                                            int o3, const_table<double> w) {
   constexpr int PS = (8 + 2 * R) * (8 + 2 * R);
   double wr[HZ + 1];
 #pragma unroll
@@ -242,7 +493,7 @@ __device__ __forceinline__ void slab_column(double (&acc)[ZC], const double* __r
 
 template <int R, int ZC, int P0, int P1, int H = 0>
 __device__ __forceinline__ void slab_switch(int hz, double (&acc)[ZC], const double* c, int o0, int o1, int o2, int o3,
-                                            const double* w) {
+                                            const_table<double> w) {
   if constexpr (H <= R) {
     if (hz == H) {
       slab_column<R, ZC, P0, P1, H>(acc, c, o0, o1, o2, o3, w);
@@ -257,6 +508,7 @@ struct SlabShape {
   static constexpr int SX = 8 + 2 * R, PS = SX * SX, NZ = ZC + 2 * R, SP = (NZ + NCH - 1) / NCH, NT = 64 * W;
   static constexpr int RZ = 8;   // output planes added up at a time
   static constexpr int NL = PS * SP > W * RZ * 64 ? PS * SP : W * RZ * 64;
+  static_assert(NL >= 2 * kCoarseLds, "the coarsest level works in the slab's LDS");
 };
 
 // Slab CH and the ones after it: fill, then every column of the wave.
@@ -286,11 +538,12 @@ __device__ __forceinline__ void slab_pass(const StencilLevel& V, double* slab, c
       }
     }
     __syncthreads();
-    const StencilRow* __restrict__ rows = V.rows;
-    const double* __restrict__ wts = (const double*)(const void*)V.wts;
-    const int r0 = V.wave_rows[wv], r1 = V.wave_rows[wv + 1];
+    const const_table<StencilRow> rows = table<StencilRow>(V.rows);
+    const const_table<double> wts = table<double>(V.wts);
+    const const_table<int> wave_rows = table<int>(V.wave_rows);
+    const int r0 = wave_rows[wv], r1 = wave_rows[wv + 1];
     for (int r = r0; r < r1; ++r) {
-      const StencilRow row = rows[r];
+      const StencilRow row{rows[r].dx, rows[r].dy, rows[r].hz, rows[r].woff};
       const int o0 = -row.dy * S::SX - row.dx, o1 = -row.dy * S::SX + row.dx;
       const int o2 = row.dy * S::SX - row.dx, o3 = row.dy * S::SX + row.dx;
       slab_switch<R, ZC, P0, P1>(row.hz, acc, slab + c0, o0, o1, o2, o3, wts + row.woff);
@@ -299,11 +552,10 @@ __device__ __forceinline__ void slab_pass(const StencilLevel& V, double* slab, c
   }
 }
 
+// slab: the slab, then the reduction buffer of the W partial sums.
 template <int R, int ZC, int NCH, int W>
-__device__ __forceinline__ void stencil_slab(const StencilLevel& V, const int4 tinfo) {
+__device__ __forceinline__ void stencil_slab(const StencilLevel& V, const int4 tinfo, double* slab) {
   using S = SlabShape<R, ZC, NCH, W>;
-  // the slab doubles as the reduction buffer of the W partial sums
-  __shared__ double slab[S::NL];
   __shared__ int wrapx[S::SX], wrapy[S::SX], wrapz[S::NZ];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -347,23 +599,28 @@ __global__ void __launch_bounds__(64 * W) k_stencil_tile_each(const StencilLevel
                                                               const int4* __restrict__ tiles) {
   const int4 tinfo = tiles[xcd_block(blockIdx.x, gridDim.x)];
   const StencilLevel V = lv[tinfo.x];
-  stencil_tile<T, R, ZC, W>(V, tinfo);
+  __shared__ double lds[TileShape<T, R, ZC, W>::kDoubles];
+  stencil_tile<T, R, ZC, W>(V, tinfo, sizeof(T) < sizeof(double) ? (double)*V.sum_xi : 0.0, lds);
 }
 
 template <int R, int ZC, int NCH, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_slab(StencilLaunch L, const int4* __restrict__ tiles) {
+  __shared__ double slab[SlabShape<R, ZC, NCH, W>::NL];
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  if (coarsest_block(L, b, slab)) return;
   int4 tinfo;
-  const StencilLevel V = stencil_level(L, tiles, tinfo);
-  stencil_slab<R, ZC, NCH, W>(V, tinfo);
+  const StencilLevel V = stencil_level(L, b, tiles, tinfo);
+  stencil_slab<R, ZC, NCH, W>(V, tinfo, slab);
 }
 
 template <int R, int ZC, int NCH, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_slab_batched(const StencilLevel* __restrict__ lv,
                                                                  const int4* __restrict__ tiles, int ntiles) {
+  __shared__ double slab[SlabShape<R, ZC, NCH, W>::NL];
   for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x) {
     const int4 tinfo = tiles[t];
     const StencilLevel V = lv[tinfo.x];
-    stencil_slab<R, ZC, NCH, W>(V, tinfo);
+    stencil_slab<R, ZC, NCH, W>(V, tinfo, slab);
     __syncthreads();
   }
 }
@@ -428,7 +685,7 @@ __global__ void __launch_bounds__(64 * W) k_stencil_mfma(StencilLaunch L, const 
   __shared__ float tile[NL];
   __shared__ int wrapx[SX], wrapy[SY], wrapz[SZH];
   int4 tinfo;
-  const StencilLevel V = stencil_level(L, tiles, tinfo);
+  const StencilLevel V = stencil_level(L, xcd_block(blockIdx.x, gridDim.x), tiles, tinfo);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x0 = tinfo.y * 8, y0 = tinfo.z * 8, z0 = tinfo.w * ZC;
@@ -496,194 +753,15 @@ __global__ void __launch_bounds__(64 * W) k_stencil_mfma(StencilLaunch L, const 
 template <class T, int R, int ZC, int W>
 __global__ void __launch_bounds__(64 * W) k_stencil_tile_batched(const StencilLevel* __restrict__ lv,
                                                                  const int4* __restrict__ tiles, int ntiles) {
+  __shared__ double lds[TileShape<T, R, ZC, W>::kDoubles];
   for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x) {
     const int4 tinfo = tiles[t];
     const StencilLevel V = lv[tinfo.x];
-    stencil_tile<T, R, ZC, W>(V, tinfo);
+    stencil_tile<T, R, ZC, W>(V, tinfo, sizeof(T) < sizeof(double) ? (double)*V.sum_xi : 0.0, lds);
     __syncthreads();
   }
 }
 
-// Coarsest level: all-to-all over the level (a periodic convolution of the
-// charges with the pre-summed kernel K), with K and the charges staged in LDS
-// when they fit (kCoarseLds points each).
-//
-// Rows path (batched launches), for a level whose x extent N is at most 8
-// and whose staging fits: a lane owns one output row (y, z) and keeps its N sums in
-// registers; the eight waves of the block split the source rows (y', z').
-// Per source row a lane reads the N values of the kernel row
-// ((y - y') mod n_y, (z - z') mod n_z) and the wave reads the N charges of
-// the row (the same address in every lane), then the x-direction convolution
-// of the two rows, N^2 FMAs with the (x - x') mod N offsets fixed at compile
-// time, runs in registers.  Each K value read from LDS serves N FMAs.  The
-// waves' partial rows are added in LDS in wave order (fixed order).  K rows
-// sit at an odd stride in LDS so that the 8-byte reads of one wave spread
-// over the banks.
-//
-// General path, for single plans and the levels the rows path does not
-// take: a wave per output point (a.outs
-// points per wave, one after another): the lanes split the source rows, each
-// lane takes its (y - y', z - z') offset once per row and walks x' with
-// (x - x') mod n_x, then the lanes add their partial sums across the wave
-// (fixed order).
-constexpr int kCoarseLds = 2048;
-constexpr int kCoarseRowsMaxX = 8;
-
-// One LDS buffer for either path, declared at namespace scope so that every
-// access by name compiles to an LDS access (a pointer into it passed around
-// could be taken for a generic one and read with flat loads).
-__shared__ double coarse_lds[2 * kCoarseLds];
-
-// x extent of a level the rows path takes, else 0
-__host__ __device__ inline int coarse_rows_n(const GridDims& g) {
-  const int N = g.n[0], nrow = g.n[1] * g.n[2];
-  if (N < 1 || N > kCoarseRowsMaxX) return 0;
-  return (int64_t)nrow * (N | 1) <= kCoarseLds && (int64_t)nrow * N <= kCoarseLds ? N : 0;
-}
-
-template <int N>
-__device__ __forceinline__ void coarsest_rows(const CoarsestArgs& a, int blk) {
-  constexpr int S = N | 1;   // LDS stride of a K row, in doubles
-  constexpr int kPer = kCoarseLds / kCoarsestThreads;
-  double* const sk = coarse_lds;
-  double* const sq = coarse_lds + kCoarseLds;
-  const int n1 = a.g.n[1], n2 = a.g.n[2], nrow = n1 * n2, npt = nrow * N;
-  {
-    // every load of the staging in flight before the first store
-    double vq[kPer], vk[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = min((int)threadIdx.x + u * kCoarsestThreads, npt - 1);
-      vq[u] = a.q[i];
-      vk[u] = a.K[i];
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = threadIdx.x + u * kCoarsestThreads;
-      if (i < npt) {
-        const int r = i / N;
-        sk[r * S + (i - r * N)] = vk[u];
-        sq[i] = vq[u];
-      }
-    }
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int row = blk * 64 + lane;
-  const int y = row < nrow ? row % n1 : 0, z = row < nrow ? row / n1 : 0;
-  const int r0 = (nrow * wv) / kCoarsestWaves, r1 = (nrow * (wv + 1)) / kCoarsestWaves;
-  double acc[N];
-#pragma unroll
-  for (int x = 0; x < N; ++x) acc[x] = 0.0;
-  int ys = r0 % n1, zs = r0 / n1;
-  for (int r = r0; r < r1; ++r) {
-    const int ky = y - ys + (y < ys ? n1 : 0), kz = z - zs + (z < zs ? n2 : 0);
-    const int kb = (kz * n1 + ky) * S;
-    double k[N], q[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      k[j] = sk[kb + j];
-      q[j] = sq[r * N + j];
-    }
-#pragma unroll
-    for (int xs = 0; xs < N; ++xs)
-#pragma unroll
-      for (int x = 0; x < N; ++x) acc[x] = fma(k[(x - xs + N) % N], q[xs], acc[x]);
-    if (++ys == n1) {
-      ys = 0;
-      ++zs;
-    }
-  }
-  __syncthreads();   // staging no longer read: the buffer takes the partial rows
-  double* const red = coarse_lds;
-#pragma unroll
-  for (int x = 0; x < N; ++x) red[(wv * N + x) * 64 + lane] = acc[x];
-  __syncthreads();
-  if (threadIdx.x < 64 * N) {
-    const int x = threadIdx.x >> 6;
-    double v = 0.0;
-#pragma unroll
-    for (int w = 0; w < kCoarsestWaves; ++w) v += red[(w * N + x) * 64 + lane];
-    if (row < nrow) a.e[row * N + x] = v;
-  }
-}
-
-template <bool STAGED>
-__device__ __forceinline__ void coarsest_sums(const CoarsestArgs& a, int blk) {
-  const GridDims& g = a.g;
-  double* const sk = coarse_lds;
-  double* const sq = coarse_lds + kCoarseLds;
-  if constexpr (STAGED) {
-    constexpr int kPer = kCoarseLds / kCoarsestThreads;
-    double vq[kPer], vk[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = min((int)threadIdx.x + u * kCoarsestThreads, g.size - 1);
-      vq[u] = a.q[i];
-      vk[u] = a.K[i];
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = threadIdx.x + u * kCoarsestThreads;
-      if (i < g.size) {
-        sq[i] = vq[u];
-        sk[i] = vk[u];
-      }
-    }
-    __syncthreads();
-  }
-  const double* __restrict__ gK = a.K;
-  const double* __restrict__ gq = a.q;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int n0 = g.n[0], n1 = g.n[1], n2 = g.n[2], n01 = n0 * n1, nrow = n1 * n2;
-  const int b1 = 64 % n1, b2 = 64 / n1, ys0 = lane % n1, zs0 = lane / n1;
-  for (int m = 0; m < a.outs; ++m) {
-    const int mu = (blk * a.outs + m) * kCoarsestWaves + wv;
-    if (mu >= g.size) break;
-    const int x = mu % n0, y = (mu / n0) % n1, z = mu / n01;
-    double acc = 0.0;
-    // (ys, zs) of row r = lane + 64 t, advanced with a carry (no division
-    // per row)
-    int ys = ys0, zs = zs0;
-    for (int r = lane; r < nrow; r += 64) {
-      const int ky = y - ys + (y < ys ? n1 : 0), kz = z - zs + (z < zs ? n2 : 0);
-      const int kr = kz * n01 + ky * n0, qr = r * n0;
-#pragma unroll 4
-      for (int xs = 0; xs < n0; ++xs) {
-        const int kx = x - xs + (x < xs ? n0 : 0);
-        if constexpr (STAGED) acc = fma(sk[kr + kx], sq[qr + xs], acc);
-        else acc = fma(gK[kr + kx], gq[qr + xs], acc);
-      }
-      ys += b1;
-      const int cy = ys >= n1;
-      ys -= cy ? n1 : 0;
-      zs += b2 + cy;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) a.e[mu] = acc;
-  }
-}
-
-struct Coarsest {
-  using Args = CoarsestArgs;
-  static constexpr int kThreads = kCoarsestThreads;
-  static __device__ void run(const Args& a, int blk) {
-    switch (a.rows) {
-      case 1: coarsest_rows<1>(a, blk); break;
-      case 2: coarsest_rows<2>(a, blk); break;
-      case 3: coarsest_rows<3>(a, blk); break;
-      case 4: coarsest_rows<4>(a, blk); break;
-      case 5: coarsest_rows<5>(a, blk); break;
-      case 6: coarsest_rows<6>(a, blk); break;
-      case 7: coarsest_rows<7>(a, blk); break;
-      case 8: coarsest_rows<8>(a, blk); break;
-      default:
-        if (a.g.size <= kCoarseLds) coarsest_sums<true>(a, blk);
-        else coarsest_sums<false>(a, blk);
-    }
-  }
-};
 inline int nblocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
 }  // namespace
@@ -701,16 +779,16 @@ int stencil_window(const mls_plan_s* P) {
   return std::max(P->stencil_R[0], std::max(P->stencil_R[1], P->stencil_R[2]));
 }
 
-// Descriptors of levels 1..kmax of a plan's chains; returns the blocks of a
-// launch over them (kmax = l - 1: all; the tile table lists the levels in
-// order, so levels 1..kmax are its head).
-int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts, int kmax, StencilLaunch& L) {
+// Descriptors of levels 1..kmax of a plan's chains (kmax = l - 1: all; the tile
+// table lists the levels in order, so levels 1..kmax are its head), with the
+// coarsest level where asked for; returns the blocks of a launch over them.
+int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts, const StencilOpts& o,
+                   StencilLaunch& L) {
   static_assert(sizeof(StencilLaunch) <= 3840, "kernel arguments");
   const int zc = P->stencil_zc;
   const ChainSet cs = chains(P);
-  L.nlev = P->levels - 1;
   int t = 0;
-  for (int k = 1; k <= kmax; ++k) {
+  for (int k = 1; k <= o.kmax; ++k) {
     const Level& Lv = P->lv[k - 1];
     StencilLevel& V = L.lv[k - 1];
     for (int d = 0; d < 3; ++d) V.n[d] = Lv.g.n[d];
@@ -728,73 +806,83 @@ int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts,
       L.e[v][k - 1] = (*cs.lv[v])[k - 1].e;
     }
   }
-  for (int v = 0; v < cs.n; ++v) L.sum[v] = cs.sum[v];
+  const Level& C = P->lv[P->levels - 1];
+  L.nchain = cs.n;
   L.ntiles = t;
-  return t * cs.n;
+  L.ncoarse = o.coarsest ? coarsest_blocks(C.g, 1, 0) : 0;
+  L.K = P->d_Kl;
+  L.gc = C.g;
+  L.sum_rows = o.sum_rows;
+  for (int v = 0; v < cs.n; ++v) {
+    L.qc[v] = (*cs.lv[v])[P->levels - 1].q;
+    L.ec[v] = (*cs.lv[v])[P->levels - 1].e;
+    L.sum[v] = o.sum_rows > 0 ? (cs.n == 1 ? P->d_partial : lb_partial_buf(P, v)) : cs.sum[v];
+  }
+  return (t + L.ncoarse) * cs.n;
 }
 
 template <class T, int R, int ZC = tile_zc(R, sizeof(T) == 8)>
-hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, int kmax) {
+hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, const StencilOpts& o) {
   StencilLaunch L;
-  const int t = stencil_levels(P, P->d_rows, wts, kmax, L);
+  const int t = stencil_levels(P, P->d_rows, wts, o, L);
   k_stencil_tile<T, R, ZC, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
 
 template <int R, int ZC, int NCH>
-hipError_t launch_slab(mls_plan_s* P, hipStream_t s, int kmax) {
+hipError_t launch_slab(mls_plan_s* P, hipStream_t s, const StencilOpts& o) {
   StencilLaunch L;
-  const int t = stencil_levels(P, P->d_rows, P->d_row_w_tile, kmax, L);
+  const int t = stencil_levels(P, P->d_rows, P->d_row_w_tile, o, L);
   k_stencil_slab<R, ZC, NCH, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
 
-hipError_t launch_slab_f64(mls_plan_s* P, int R, hipStream_t s, int kmax) {
+hipError_t launch_slab_f64(mls_plan_s* P, int R, hipStream_t s, const StencilOpts& o) {
   const bool deep = P->stencil_zc == 16;
-  if (R <= 4) return launch_slab<4, 8, 1>(P, s, kmax);
-  if (R <= 6) return launch_slab<6, 8, 1>(P, s, kmax);
-  if (R <= 8) return deep ? launch_slab<8, 16, 2>(P, s, kmax) : launch_slab<8, 8, 2>(P, s, kmax);
-  if (R <= 10) return launch_slab<10, 8, 3>(P, s, kmax);
-  if (R <= 12) return deep ? launch_slab<12, 16, 5>(P, s, kmax) : launch_slab<12, 8, 4>(P, s, kmax);
+  if (R <= 4) return launch_slab<4, 8, 1>(P, s, o);
+  if (R <= 6) return launch_slab<6, 8, 1>(P, s, o);
+  if (R <= 8) return deep ? launch_slab<8, 16, 2>(P, s, o) : launch_slab<8, 8, 2>(P, s, o);
+  if (R <= 10) return launch_slab<10, 8, 3>(P, s, o);
+  if (R <= 12) return deep ? launch_slab<12, 16, 5>(P, s, o) : launch_slab<12, 8, 4>(P, s, o);
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_tile_f64(mls_plan_s* P, int R, hipStream_t s, int kmax) {
+hipError_t launch_tile_f64(mls_plan_s* P, int R, hipStream_t s, const StencilOpts& o) {
   const double* w = P->d_row_w_tile;
   switch (R) {
-    case 1: case 2: case 3: case 4: return launch_tile<double, 4>(P, w, s, kmax);
-    case 5: case 6: return launch_tile<double, 6>(P, w, s, kmax);
-    case 7: case 8: return launch_slab_f64(P, R, s, kmax);
+    case 1: case 2: case 3: case 4: return launch_tile<double, 4>(P, w, s, o);
+    case 5: case 6: return launch_tile<double, 6>(P, w, s, o);
+    case 7: case 8: return launch_slab_f64(P, R, s, o);
     default: return hipErrorInvalidValue;
   }
 }
 
 // FP32 tiles reach R = 12: (8 + 2R)^2 (8 + 2R) floats, 88 KB at R = 10 and
 // 128 KB at R = 12 (one block per CU; an FP64 tile of that size does not fit)
-hipError_t launch_tile_f32(mls_plan_s* P, int R, hipStream_t s, int kmax) {
+hipError_t launch_tile_f32(mls_plan_s* P, int R, hipStream_t s, const StencilOpts& o) {
   const float* w = P->d_row_wf_tile;
   switch (R) {
-    case 1: case 2: case 3: case 4: return launch_tile<float, 4>(P, w, s, kmax);
-    case 5: case 6: return launch_tile<float, 6>(P, w, s, kmax);
-    case 7: case 8: return launch_tile<float, 8>(P, w, s, kmax);
-    case 9: case 10: return launch_tile<float, 10>(P, w, s, kmax);
-    case 11: case 12: return launch_tile<float, 12>(P, w, s, kmax);
+    case 1: case 2: case 3: case 4: return launch_tile<float, 4>(P, w, s, o);
+    case 5: case 6: return launch_tile<float, 6>(P, w, s, o);
+    case 7: case 8: return launch_tile<float, 8>(P, w, s, o);
+    case 9: case 10: return launch_tile<float, 10>(P, w, s, o);
+    case 11: case 12: return launch_tile<float, 12>(P, w, s, o);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int R>
-hipError_t launch_mfma(mls_plan_s* P, hipStream_t s, int kmax) {
+hipError_t launch_mfma(mls_plan_s* P, hipStream_t s, const StencilOpts& o) {
   StencilLaunch L;
-  const int t = stencil_levels(P, P->d_rows_mfma, P->d_mfma_a, kmax, L);
+  const int t = stencil_levels(P, P->d_rows_mfma, P->d_mfma_a, o, L);
   k_stencil_mfma<R, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
   return hipGetLastError();
 }
 
-hipError_t launch_tile_mfma(mls_plan_s* P, int R, hipStream_t s, int kmax) {
+hipError_t launch_tile_mfma(mls_plan_s* P, int R, hipStream_t s, const StencilOpts& o) {
   switch (R) {
-    case 1: case 2: case 3: case 4: return launch_mfma<4>(P, s, kmax);
-    case 5: case 6: return launch_mfma<6>(P, s, kmax);
+    case 1: case 2: case 3: case 4: return launch_mfma<4>(P, s, o);
+    case 5: case 6: return launch_mfma<6>(P, s, o);
     default: return hipErrorInvalidValue;
   }
 }
@@ -809,26 +897,42 @@ int stencil_path(const mls_plan_s* P) {
   return MLS_STENCIL_TAPS_F64;
 }
 
-hipError_t launch_stencils(mls_plan_s* P, hipStream_t s, int kmax) {
-  if (P->levels < 2) return hipSuccess;
-  if (kmax <= 0 || kmax > P->levels - 1) kmax = P->levels - 1;
+// Atoms up to which the FP32 tiles add up the partial sums of the charges
+// themselves: one read per thread, against a launch of 4 us on the chain.  Beyond,
+// several reads per thread of every tile.
+constexpr int64_t kSumRows = 65536;
+
+bool stencil_adds_sum(const mls_plan_s* P, int64_t n) {
+  return n > 0 && n + kSortedPad <= kSumRows && stencil_path(P) == MLS_STENCIL_TILE_F32;
+}
+
+hipError_t launch_stencils(mls_plan_s* P, int n, hipStream_t s, int kmax, bool coarsest) {
+  if (P->levels < 2) return coarsest ? launch_coarsest(P, s) : hipSuccess;
   const int R = stencil_window(P);
   const int path = stencil_path(P);
-  if (path == MLS_STENCIL_TILE_MFMA_F32) return launch_tile_mfma(P, R, s, kmax);
-  if (path == MLS_STENCIL_TILE_F32) return launch_tile_f32(P, R, s, kmax);
-  if (path == MLS_STENCIL_STREAM_F64) return launch_slab_f64(P, R, s, kmax);
-  if (path == MLS_STENCIL_TILE_F64) return launch_tile_f64(P, R, s, kmax);
+  StencilOpts o;
+  o.kmax = kmax <= 0 || kmax > P->levels - 1 ? P->levels - 1 : kmax;
+  if (stencil_adds_sum(P, n)) o.sum_rows = n + (P->mixing == MLS_LORENTZ_BERTHELOT ? kSortedPad : 0);
+  o.coarsest = coarsest;
+  if (path == MLS_STENCIL_TILE_F32) return launch_tile_f32(P, R, s, o);
+  if (path == MLS_STENCIL_STREAM_F64) return launch_slab_f64(P, R, s, o);
+  if (path == MLS_STENCIL_TILE_F64) return launch_tile_f64(P, R, s, o);
+  if (path == MLS_STENCIL_TILE_MFMA_F32) {
+    o.coarsest = false;
+    const hipError_t e = launch_tile_mfma(P, R, s, o);
+    return e != hipSuccess || !coarsest ? e : launch_coarsest(P, s);
+  }
   const int ntaps = (int)P->taps.size();
   const ChainSet cs = chains(P);
   for (int v = 0; v < cs.n; ++v)
-    for (int k = 1; k <= kmax; ++k) {
+    for (int k = 1; k <= o.kmax; ++k) {
       const Level& L = (*cs.lv[v])[k - 1];
       const double scale = std::ldexp(1.0, -6 * (k - 1));
       k_stencil_taps_f64<<<nblocks(L.g.size, kBlock), kBlock, 0, s>>>(L.q, L.g, P->d_taps, ntaps, scale, L.e);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-  return hipSuccess;
+  return coarsest ? launch_coarsest(P, s) : hipSuccess;
 }
 
 hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s) {
