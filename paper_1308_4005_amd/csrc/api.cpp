@@ -169,12 +169,15 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   if (fork) HIP_TRY(ensure_side(P), "second stream");
   const hipStream_t g = fork ? P->side : s;
   HIP_TRY(mark(0), "timing event");
+  bool gathered = false;
   if (binmode == kBinRecord) {
     HIP_TRY(launch_binning_ref(P, ni, pos, c6, s), "binning");
   } else if (binmode == kBinReuse) {
     HIP_TRY(launch_binning_reuse(P, ni, pos, c6, s), "binning");
   } else {
-    HIP_TRY(launch_binning(P, ni, pos, c6, s), "binning");
+    // on one stream the binning also writes the sorted sqrt(C12); beside a
+    // grid chain it would hold that back
+    HIP_TRY(launch_binning(P, ni, pos, c6, s, rep && !fork ? rep->c12 : nullptr, &gathered), "binning");
   }
   HIP_TRY(mark(1 + MLS_T_BINNING), "timing event");
   if (fork) {
@@ -191,7 +194,7 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   // else runs as its own kernel right after it
   const PairRep prep{P->d_x12s, P->d_x12f, rep ? rep->rc * rep->rc : 0.0, P->d_frep, P->d_md_partial};
   auto pair = [&]() -> mls_status {
-    if (rep) HIP_TRY(launch_rep_gather(P, ni, rep->c12, s), "repulsion");
+    if (rep && !gathered) HIP_TRY(launch_rep_gather(P, ni, rep->c12, s), "repulsion");
     bool fused = false;
     HIP_TRY(launch_pair(P, ni, s, rep ? &prep : nullptr, &fused, !fork), "pair kernel");
     if (rep && !fused) HIP_TRY(launch_repulsion(P, ni, rep->rc, s), "repulsion");
@@ -230,8 +233,9 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
 // with k = 0 plus the repulsion), all on stream s.
 hipError_t evaluate_fast(mls_plan_t P, int n, const double* pos, const double* c6, const Repulsion& rep,
                          double* energy, double* forces, hipStream_t s) {
-  hipError_t e = launch_binning(P, n, pos, c6, s);
-  if (e == hipSuccess) e = launch_rep_gather(P, n, rep.c12, s);
+  bool gathered = false;
+  hipError_t e = launch_binning(P, n, pos, c6, s, rep.c12, &gathered);
+  if (e == hipSuccess && !gathered) e = launch_rep_gather(P, n, rep.c12, s);
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
   if (e == hipSuccess) e = launch_pair(P, n, s, &prep, &fused, true);
@@ -248,11 +252,12 @@ hipError_t evaluate_split(mls_plan_t P, int n, const double* pos, const double* 
                           double* energy, double* forces, double* fslow, hipStream_t s) {
   hipError_t e;
   hipStream_t g;
-  if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
+  bool gathered = false;
+  if ((e = launch_binning(P, n, pos, c6, s, forks(P, n) ? nullptr : rep.c12, &gathered)) != hipSuccess) return e;
   if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
-  if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
+  if (!gathered && (e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
@@ -279,11 +284,12 @@ hipError_t evaluate_fast_mid(mls_plan_s* P, int n, const double* pos, const doub
     return launch_zero(fmid, 3 * (int64_t)n, s);
   }
   hipStream_t g;
-  if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
+  bool gathered = false;
+  if ((e = launch_binning(P, n, pos, c6, s, forks(P, n) ? nullptr : rep.c12, &gathered)) != hipSuccess) return e;
   if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
-  if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
+  if (!gathered && (e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
@@ -304,11 +310,12 @@ hipError_t evaluate_split3(mls_plan_s* P, int n, const double* pos, const double
   hipError_t e;
   hipStream_t g;
   const bool two = P->levels >= 2;
-  if ((e = launch_binning(P, n, pos, c6, s)) != hipSuccess) return e;
+  bool gathered = false;
+  if ((e = launch_binning(P, n, pos, c6, s, forks(P, n) ? nullptr : rep.c12, &gathered)) != hipSuccess) return e;
   if ((e = fork_chain(P, n, s, g)) != hipSuccess) return e;
   if ((e = launch_sum_xi(P, n, g)) != hipSuccess) return e;
   if ((e = launch_anterpolate(P, n, g)) != hipSuccess) return e;
-  if ((e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
+  if (!gathered && (e = launch_rep_gather(P, n, rep.c12, s)) != hipSuccess) return e;
   const PairRep prep{P->d_x12s, P->d_x12f, rep.rc * rep.rc, P->d_frep, P->d_md_partial};
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;

@@ -326,6 +326,11 @@ constexpr int64_t kMaxHist = (int64_t)1 << 24;
 constexpr int kSortThreads = 1024;
 constexpr int kSortPer = 4;
 constexpr int kSortCap = kSortThreads * kSortPer;
+// Histogram entries up to which their readers add them up themselves: a few
+// reads per thread, against the scan's launch (32000 atoms in a slab: an
+// evaluation 122.1 -> 120.1 us; at the limit, 10^5 atoms in 141 buckets, the
+// scatter takes 8.8 us instead of 4.6 and a scan of 4.9).
+constexpr int kDirectHist = 8192;
 
 template <int T>
 __device__ __forceinline__ int block_sum_i(int v, int* ws) {
@@ -403,6 +408,16 @@ struct BucketScatter {
   using Args = BucketScatterArgs;
   static constexpr int kThreads = kBinThreads;
   static constexpr int kMaxScanBlocks = (int)(kMaxHist / kScanItems);
+  static __device__ void scatter(const Args& a, int blk, const int (&c)[kBinPer], int* next) {
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u) {
+      const int i = blk * kBinItems + u * kBinThreads + threadIdx.x;
+      if (i < a.n) {
+        const int p = atomicAdd(&next[c[u] >> a.shift], 1);
+        a.tmp[p] = make_int2(i, c[u]);
+      }
+    }
+  }
   static __device__ void run(const Args& a, int blk) {
     __shared__ int next[kMaxBuckets];
     __shared__ int sbo[kMaxScanBlocks];
@@ -411,8 +426,30 @@ struct BucketScatter {
     int c[kBinPer];
 #pragma unroll
     for (int u = 0; u < kBinPer; ++u) c[u] = a.cid[min(blk * kBinItems + u * kBinThreads + (int)threadIdx.x, a.n - 1)];
-    // exclusive prefix of the scan blocks' totals
     const int m = a.nbucket * a.nblk, nsb = (m + kScanItems - 1) / kScanItems;
+    if (a.direct) {
+      // the counts of everything before this block's atoms of each bucket
+      constexpr int kPer = kDirectHist / kBinThreads;
+      int v[kPer], sum = 0;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x * kPer + u;
+        v[u] = i < m ? a.hist[i] : 0;
+        sum += v[u];
+      }
+      int total;
+      int run = block_scan_excl<kBinThreads>(sum, ws, total);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x * kPer + u, b = i / a.nblk;
+        if (i < m && i - b * a.nblk == blk) next[b] = run;
+        run += v[u];
+      }
+      __syncthreads();
+      scatter(a, blk, c, next);
+      return;
+    }
+    // exclusive prefix of the scan blocks' totals
     int carry = 0;
     for (int k0 = 0; k0 < nsb; k0 += kBinThreads) {
       const int k = k0 + threadIdx.x;
@@ -428,14 +465,7 @@ struct BucketScatter {
       next[b] = a.hist[i] + sbo[i / kScanItems];
     }
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kBinPer; ++u) {
-      const int i = blk * kBinItems + u * kBinThreads + threadIdx.x;
-      if (i < a.n) {
-        const int p = atomicAdd(&next[c[u] >> a.shift], 1);
-        a.tmp[p] = make_int2(i, c[u]);
-      }
-    }
+    scatter(a, blk, c, next);
   }
 };
 
@@ -469,6 +499,25 @@ struct BucketSort {
     a.xs[d] = p;
     a.cell_s[d] = c;
     store_fp32_rows(a.xr, a.xif, a.xf, a.xf_stride, a.g, d, p);
+    if (a.c12) store_rep(a, d, a.c12[v]);
+  }
+
+  // sorted sqrt(C12); non-finite and negative values become 0 and raise a flag
+  __device__ static void store_rep(const Args& a, int d, double c) {
+    double x = 0.0;
+    if (isfinite(c) && c >= 0.0) x = sqrt(c);
+    else atomicOr(a.flags, 8);
+    a.x12s[d] = x;
+    if (a.x12f) a.x12f[d] = (float)x;
+  }
+
+  // padding rows: far outside any cutoff, zero weight
+  __device__ static void pad(const Args& a) {
+    for (int s = a.n + threadIdx.x; s < a.n + kSortedPad; s += kSortThreads) {
+      a.xs[s] = make_double4(1e300, 1e300, 1e300, 0.0);
+      store_fp32_pad(a.xr, a.xif, a.xf, a.xf_stride, s);
+      if (a.c12) store_rep(a, s, 0.0);
+    }
   }
 
   static __device__ void run(const Args& a, int b) {
@@ -483,15 +532,23 @@ struct BucketSort {
     const int m = a.nbucket * a.nblk;
     const int i0 = b * a.nblk, i1 = (b + 1) * a.nblk;
     int s0 = 0, s1 = 0;
-    for (int k = threadIdx.x; k < i1 / kScanItems; k += kSortThreads) {
-      const int v = a.bsum[k];
-      s1 += v;
-      if (k < i0 / kScanItems) s0 += v;
+    if (a.direct) {
+      for (int k = threadIdx.x; k < i1; k += kSortThreads) {
+        const int v = a.hist[k];
+        s1 += v;
+        if (k < i0) s0 += v;
+      }
+    } else {
+      for (int k = threadIdx.x; k < i1 / kScanItems; k += kSortThreads) {
+        const int v = a.bsum[k];
+        s1 += v;
+        if (k < i0 / kScanItems) s0 += v;
+      }
     }
     s0 = block_sum_i<kSortThreads>(s0, ws);
     s1 = block_sum_i<kSortThreads>(s1, ws);
-    const int lo = i0 < m ? s0 + a.hist[i0] : a.n;
-    const int hi = i1 < m ? s1 + a.hist[i1] : a.n;
+    const int lo = i0 < m ? s0 + (a.direct ? 0 : a.hist[i0]) : a.n;
+    const int hi = i1 < m ? s1 + (a.direct ? 0 : a.hist[i1]) : a.n;
     const int cnt = hi - lo;
     for (int c = threadIdx.x; c < nc; c += kSortThreads) cur[c] = 0;
     __syncthreads();
@@ -552,13 +609,88 @@ struct BucketSort {
         emit(a, vc.x, vc.y, cb + rank, a.xw[vc.x]);
       }
     }
-    if (b == a.nbucket - 1) {
-      // padding rows: far outside any cutoff, zero weight
-      for (int s = a.n + threadIdx.x; s < a.n + kSortedPad; s += kSortThreads) {
-        a.xs[s] = make_double4(1e300, 1e300, 1e300, 0.0);
-        store_fp32_pad(a.xr, a.xif, a.xf, a.xf_stride, s);
+    if (b == a.nbucket - 1) pad(a);
+  }
+};
+
+// Up to kSortCap atoms in up to 2^kBucketShiftMax cells: the steps of BinBucket
+// and BucketSort in one block, the atoms in registers from their positions to
+// their sorted rows (1000 atoms: one kernel of 8.2 us instead of four of 19.5,
+// an evaluation 75.6 -> 67.0 us).  The same permutation and the same partial sums of xi.
+struct BinSmall {
+  using Args = BinSmallArgs;
+  static constexpr int kThreads = kSortThreads;
+  static __device__ void run(const Args& ar, int) {
+    __shared__ int cst[BucketSort::kCells + 1], cur[BucketSort::kCells];
+    __shared__ int srt[kSortCap];
+    __shared__ int ws[kSortThreads / 64];
+    __shared__ double sh[2 * kSortThreads / 64];
+    const BinBucketArgs& a = ar.b;
+    if (a.cond && *a.cond == 0) return;
+    const int nc = a.g.ncell;
+    for (int c = threadIdx.x; c < nc; c += kSortThreads) cur[c] = 0;
+    double x[kSortPer], y[kSortPer], z[kSortPer], c6[kSortPer];
+#pragma unroll
+    for (int u = 0; u < kSortPer; ++u) {
+      const size_t i = min(u * kSortThreads + (int)threadIdx.x, a.n - 1);
+      x[u] = a.pos[3 * i];
+      y[u] = a.pos[3 * i + 1];
+      z[u] = a.pos[3 * i + 2];
+      c6[u] = a.c6[i];
+    }
+    __syncthreads();
+    double4 p[kSortPer];
+    int id[kSortPer];
+#pragma unroll
+    for (int u = 0; u < kSortPer; ++u) {
+      const int i = u * kSortThreads + threadIdx.x;
+      p[u] = make_double4(0.0, 0.0, 0.0, 0.0);
+      id[u] = 0;
+      if (i < a.n) {
+        if (a.xref) {
+          a.xref[3 * (size_t)i] = x[u];
+          a.xref[3 * (size_t)i + 1] = y[u];
+          a.xref[3 * (size_t)i + 2] = z[u];
+        }
+        int bad;
+        p[u] = wrap_values(x[u], y[u], z[u], c6[u], a.g, a.c6_scale, bad);
+        if (bad) atomicOr(a.flags, bad);
+        id[u] = cell_of(p[u], a.g);
+        atomicAdd(&cur[id[u]], 1);
+      }
+      if (a.xi_partial) {
+        // per 256 consecutive atoms, in the order of BinBucket
+        double v = p[u].w;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        double* const w0 = sh + (u & 1) * (kSortThreads / 64);
+        if ((threadIdx.x & 63) == 0) w0[threadIdx.x >> 6] = v;
+        __syncthreads();
+        const int base = u * kSortThreads + (threadIdx.x & ~255);
+        if ((threadIdx.x & 255) == 0 && base < a.n) {
+          const double* w = w0 + (threadIdx.x >> 6);
+          a.xi_partial[base >> 8] = ((w[0] + w[1]) + w[2]) + w[3];
+        }
       }
     }
+    __syncthreads();
+    BucketSort::cell_starts(ar.s, 0, 0, nc, 0, cst, cur, ws);
+#pragma unroll
+    for (int u = 0; u < kSortPer; ++u) {
+      const int i = u * kSortThreads + threadIdx.x;
+      if (i < a.n) srt[atomicAdd(&cur[id[u]], 1)] = i;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSortPer; ++u) {
+      const int i = u * kSortThreads + threadIdx.x;
+      if (i >= a.n) continue;
+      const int cb = cst[id[u]], ce = cst[id[u] + 1];
+      int rank = 0;
+      for (int j = cb; j < ce; ++j) rank += srt[j] < i;
+      BucketSort::emit(ar.s, i, id[u], cb + rank, p[u]);
+    }
+    BucketSort::pad(ar.s);
   }
 };
 
@@ -781,10 +913,6 @@ hipError_t launch_zero_i(int* p, int64_t count, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_binning(mls_plan_s* P, int n, const double* pos, const double* c6, hipStream_t s) {
-  return launch_binning_scaled(P, n, pos, c6, 1.0, s);
-}
-
 hipError_t launch_lb_gather(mls_plan_s* P, int n, const double* sigma, hipStream_t s) {
   if (n == 0) return hipSuccess;
   return launch_one<LbGather>(LbGatherArgs{P->d_perm, n, sigma, P->d_sig, P->d_flags, P->d_sigf},
@@ -811,7 +939,7 @@ hipError_t launch_lb_charges(mls_plan_s* P, int n, hipStream_t s) {
 // The binning kernels; with `cond` they all do nothing when *cond == 0, and
 // with `xref` the count kernel records the positions.
 static hipError_t binning_core(mls_plan_s* P, int n, const double* pos, const double* c6, double scale,
-                               const int* cond, double* xref, hipStream_t s) {
+                               const int* cond, double* xref, hipStream_t s, const double* c12 = nullptr) {
   // The cell counts start at zero: cleared once at plan creation, then by
   // every scan after it has read them.
   const CellGeom& g = P->cg;
@@ -819,23 +947,28 @@ static hipError_t binning_core(mls_plan_s* P, int n, const double* pos, const do
   hipError_t e;
   if (P->bin_nbucket) {
     const int nblk = nblocks(n, kBinItems), m = P->bin_nbucket * nblk;
-    if (n > 0) {
-      BinBucketArgs a{pos, c6, n, g, P->d_cid, P->d_xw, P->d_flags, scale, mixed ? P->d_partial : nullptr, cond,
-                      xref, P->bin_shift, P->bin_nbucket, nblk, P->d_bin_hist};
-      if ((e = launch_one<BinBucket>(a, nblk, s)) != hipSuccess) return e;
-    }
-    // in place, per scan block: the histograms become the start of each
-    // (bucket, block) run within its scan block
-    ScanArgs sa{P->d_bin_hist, m, P->d_bin_hist, P->d_bsum, P->d_bmax, P->d_ncell_max, cond};
-    if ((e = launch_one<ScanBlocks>(sa, scan_blocks(m), s)) != hipSuccess) return e;
-    if (n > 0) {
-      BucketScatterArgs ca{P->d_cid, n, P->bin_shift, P->bin_nbucket, nblk, P->d_bin_hist, P->d_bsum,
-                           P->d_perm_tmp, cond};
-      if ((e = launch_one<BucketScatter>(ca, nblk, s)) != hipSuccess) return e;
-    }
+    const int direct = m <= kDirectHist;
+    BinBucketArgs a{pos, c6, n, g, P->d_cid, P->d_xw, P->d_flags, scale, mixed ? P->d_partial : nullptr, cond,
+                    xref, P->bin_shift, P->bin_nbucket, nblk, P->d_bin_hist};
     BucketSortArgs da{P->d_bin_hist, P->d_bsum, nblk, P->bin_shift, P->bin_nbucket, P->d_perm_tmp, P->d_perm_tmp2, n,
                       P->d_cell_start, P->d_perm, P->d_xw, P->d_xs, P->d_cell_s, P->d_xr, P->d_xif, g, cond,
-                      P->d_xf, P->xf_stride};
+                      P->d_xf, P->xf_stride, direct, c12, P->d_x12s, P->d_x12f, P->d_flags};
+    if (n > 0 && n <= kSortCap && g.ncell <= BucketSort::kCells) {
+      da.nbucket = 1;
+      return launch_one<BinSmall>(BinSmallArgs{a, da}, 1, s);
+    }
+    if (n > 0 && (e = launch_one<BinBucket>(a, nblk, s)) != hipSuccess) return e;
+    if (!direct) {
+      // in place, per scan block: the histograms become the start of each
+      // (bucket, block) run within its scan block
+      ScanArgs sa{P->d_bin_hist, m, P->d_bin_hist, P->d_bsum, P->d_bmax, P->d_ncell_max, cond};
+      if ((e = launch_one<ScanBlocks>(sa, scan_blocks(m), s)) != hipSuccess) return e;
+    }
+    if (n > 0) {
+      BucketScatterArgs ca{P->d_cid, n, P->bin_shift, P->bin_nbucket, nblk, P->d_bin_hist, P->d_bsum,
+                           P->d_perm_tmp, cond, direct};
+      if ((e = launch_one<BucketScatter>(ca, nblk, s)) != hipSuccess) return e;
+    }
     return launch_one<BucketSort>(da, P->bin_nbucket, s);
   }
   if (n > 0) {
@@ -854,6 +987,13 @@ static hipError_t binning_core(mls_plan_s* P, int n, const double* pos, const do
   RankGatherArgs ra{P->d_cell_start, P->d_perm_tmp, n, P->d_perm, P->d_xw, P->d_xs, P->d_cell_s, P->d_xr,
                     P->d_xif, g, cond, P->d_xf, P->xf_stride};
   return launch_one<RankGather>(ra, nblocks(n + kSortedPad, kBlock), s);
+}
+
+hipError_t launch_binning(mls_plan_s* P, int n, const double* pos, const double* c6, hipStream_t s, const double* c12,
+                          bool* gathered) {
+  const bool with = c12 && P->bin_nbucket;
+  if (gathered) *gathered = with;
+  return binning_core(P, n, pos, c6, 1.0, nullptr, nullptr, s, with ? c12 : nullptr);
 }
 
 hipError_t launch_binning_scaled(mls_plan_s* P, int n, const double* pos, const double* c6, double scale,

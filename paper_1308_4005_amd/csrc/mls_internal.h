@@ -177,7 +177,8 @@ struct ScanArgs { gptr<int> count; int m; gptr<int> start; gptr<int> bsum; gptr<
 // Bucketed binning (single plans): a bucket is a run of 2^shift consecutive
 // cell ids; hist[bucket * nblk + blk] counts the atoms of block blk in the
 // bucket, then (scanned in place, per scan block; bsum: the scan blocks'
-// totals) gives where they start in tmp.
+// totals) gives where they start in tmp.  direct: hist keeps the counts, its
+// readers add up what lies before their entries.
 struct BinBucketArgs {
   gptr<const double> pos; gptr<const double> c6; int n; CellGeom g; gptr<int> cid; gptr<double4> xw; gptr<int> flags; double c6_scale;
   gptr<double> xi_partial; gptr<const int> cond; gptr<double> xref;
@@ -185,13 +186,17 @@ struct BinBucketArgs {
 };
 struct BucketScatterArgs {
   gptr<const int> cid; int n; int shift; int nbucket; int nblk; gptr<const int> hist; gptr<const int> bsum; gptr<int2> tmp;
-  gptr<const int> cond;
+  gptr<const int> cond; int direct;
 };
 struct BucketSortArgs {
   gptr<const int> hist; gptr<const int> bsum; int nblk; int shift; int nbucket; gptr<const int2> tmp; gptr<int2> tmp2; int n; gptr<int> start;
   gptr<int> perm; gptr<const double4> xw; gptr<double4> xs; gptr<int> cell_s; gptr<float4> xr; gptr<float> xif; CellGeom g; gptr<const int> cond;
-  gptr<float> xf; int xf_stride;
+  gptr<float> xf; int xf_stride; int direct;
+  // molecular dynamics: sqrt(C12) in sorted order too (null: not asked for)
+  gptr<const double> c12; gptr<double> x12s; gptr<float> x12f; gptr<int> flags;
 };
+// The whole binning of a small system in one block.
+struct BinSmallArgs { BinBucketArgs b; BucketSortArgs s; };
 struct ScatterArgs { gptr<const int> cid; gptr<const int> slot; int n; gptr<const int> start; gptr<int2> perm_tmp; gptr<const int> cond = nullptr; };
 struct RankArgs { gptr<const int> start; gptr<const int2> perm_tmp; int n; gptr<int> perm; };
 // Rank of each atom among its cell's atoms by original index, fused with the
@@ -674,7 +679,10 @@ int coarsest_blocks(const GridDims& g, int outs, int rows);
 int stencil_tile_zc(int R, bool f64, int64_t tiles16);
 
 // kernel launchers (one per file); all enqueue on `s` and return the launch status
-hipError_t launch_binning(mls_plan_s* P, int n, const double* pos, const double* c6, hipStream_t s);
+// With c12 (molecular dynamics), *gathered tells whether the binning also wrote
+// the sorted sqrt(C12); else launch_rep_gather does.
+hipError_t launch_binning(mls_plan_s* P, int n, const double* pos, const double* c6, hipStream_t s,
+                          const double* c12 = nullptr, bool* gathered = nullptr);
 // Neighbour reuse (plans with a skin): binning that records the positions
 // (first evaluation of an MD run), and the per-step alternative: check the
 // displacements since then and either bin again or re-gather.
