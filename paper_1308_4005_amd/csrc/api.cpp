@@ -230,7 +230,7 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
 }
 
 // Multiple time stepping: the fast force alone (local part of eq:evaluation
-// with k = 0 plus the repulsion), all on stream s.
+// with k = 0 plus the repulsion), all on stream s; its energy too, if asked for.
 hipError_t evaluate_fast(mls_plan_t P, int n, const double* pos, const double* c6, const Repulsion& rep,
                          double* energy, double* forces, hipStream_t s) {
   bool gathered = false;
@@ -351,6 +351,15 @@ mls_status mls_evaluate(mls_plan_t P, int64_t n, const double* pos, const double
   return evaluate_geometric(P, n, pos, c6, energy, forces, potential, dE_dc6, stream, nullptr);
 }
 
+// The kinetic sums that an MD entry point left to its next energy reduction
+// (launch_md_step) do not outlive the call, whichever way it ends.
+struct KineticScope {
+  mls_plan_s* P;
+  ~KineticScope() {
+    if (P) P->kin_out = nullptr;
+  }
+};
+
 static mls_status check_rep(mls_plan_t P, int64_t n, const double* c12, double rc, const char* who) {
   if (!P) { set_error(std::string(who) + ": null plan"); return MLS_ERR_INVALID_ARG; }
   if (n > 0 && !c12) { set_error(std::string(who) + ": null c12"); return MLS_ERR_INVALID_ARG; }
@@ -380,6 +389,7 @@ mls_status mls_md_run(mls_plan_t P, int64_t n, double* pos, double* vel, const d
     return MLS_ERR_INVALID_ARG;
   }
   const Repulsion rep{c12, rc};
+  const KineticScope scope{P};
   const hipStream_t s = (hipStream_t)stream;
   const int ni = (int)std::min<int64_t>(std::max<int64_t>(n, 0), P->n_max);
   // with a skin the binning of the first evaluation is kept while no atom
@@ -392,12 +402,12 @@ mls_status mls_md_run(mls_plan_t P, int64_t n, double* pos, double* vel, const d
     // end of step k-1 (k > 1): second half-kick, E_kin(k-1); step k: first
     // half-kick and drift
     const int mode = (k > 1 ? kMdEnd : 0) | kMdStart;
-    HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, ekin + (k - 1), s), "integrator");
+    HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, ekin + (k - 1), true, s), "integrator");
     if ((st = evaluate_geometric(P, n, pos, c6, epot + k, forces, nullptr, nullptr, stream, &rep,
                                  reuse ? kBinReuse : kBinFresh)) != MLS_OK)
       return st;
   }
-  HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, nsteps > 0 ? kMdEnd : 0, ekin + nsteps, s),
+  HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, nsteps > 0 ? kMdEnd : 0, ekin + nsteps, false, s),
           "integrator");
   return MLS_OK;
 }
@@ -434,6 +444,7 @@ mls_status mls_md_run_mts(mls_plan_t P, int64_t n, double* pos, double* vel, con
   P->last_n = n;
   const int ni = (int)std::max<int64_t>(n, 0);
   const Repulsion rep{c12, rc};
+  const KineticScope scope{P};
   const double hslow = 0.5 * k_slow * dt;
   double* fs = P->d_fslow;
   // outer step o: slow half-kick, k_slow inner velocity-Verlet steps with the
@@ -453,15 +464,15 @@ mls_status mls_md_run_mts(mls_plan_t P, int64_t n, double* pos, double* vel, con
       } else {
         mode |= kMdEnd;
       }
-      HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, kin, s, fs, hslow), "integrator");
+      HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, kin, true, s, fs, hslow), "integrator");
       if (i < k_slow) {
-        HIP_TRY(evaluate_fast(P, ni, pos, c6, rep, P->d_efast, forces, s), "fast force");
+        HIP_TRY(evaluate_fast(P, ni, pos, c6, rep, nullptr, forces, s), "fast force");
       } else {
         HIP_TRY(evaluate_split(P, ni, pos, c6, rep, epot + o, forces, fs, s), "forces");
       }
     }
   }
-  HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, nout > 0 ? (kMdEnd | kMdSlowEnd) : 0, ekin + nout, s,
+  HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, nout > 0 ? (kMdEnd | kMdSlowEnd) : 0, ekin + nout, false, s,
                          fs, hslow),
           "integrator");
   // the total force at the final positions
@@ -502,6 +513,7 @@ mls_status mls_md_run_mts_levels(mls_plan_t P, int64_t n, double* pos, double* v
   P->last_n = n;
   const int ni = (int)std::max<int64_t>(n, 0);
   const Repulsion rep{c12, rc};
+  const KineticScope scope{P};
   const double hslow = 0.5 * k_mid * k_slow * dt, hmid = 0.5 * k_mid * dt;
   double* fs = P->d_fslow;
   double* fm = P->d_fmid;
@@ -527,11 +539,11 @@ mls_status mls_md_run_mts_levels(mls_plan_t P, int64_t n, double* pos, double* v
         } else {
           mode |= kMdEnd;
         }
-        HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, kin, s, fs, hslow, fm, hmid),
+        HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, mode, kin, true, s, fs, hslow, fm, hmid),
                 "integrator");
         hipError_t e;
         if (i < k_mid) {
-          e = evaluate_fast(P, ni, pos, c6, rep, P->d_efast, forces, s);
+          e = evaluate_fast(P, ni, pos, c6, rep, nullptr, forces, s);
         } else if (m < k_slow) {
           e = evaluate_fast_mid(P, ni, pos, c6, rep, P->d_efast, forces, fm, s);
         } else {
@@ -542,7 +554,7 @@ mls_status mls_md_run_mts_levels(mls_plan_t P, int64_t n, double* pos, double* v
     }
   }
   HIP_TRY(launch_md_step(P, ni, pos, vel, forces, inv_mass, dt, nout > 0 ? (kMdEnd | kMdMidEnd | kMdSlowEnd) : 0,
-                         ekin + nout, s, fs, hslow, fm, hmid),
+                         ekin + nout, false, s, fs, hslow, fm, hmid),
           "integrator");
   // the total force at the final positions
   if (ni > 0) {

@@ -1162,8 +1162,8 @@ struct EnergyFinal {
   using Args = EnergyArgs;
   static constexpr int kThreads = kBlock;
   static __device__ void run(const Args& a, int) {
-    __shared__ double r1[kBlock], r2[kBlock], r3[kBlock];
-    double x = 0.0, y = 0.0, z = 0.0;
+    __shared__ double r1[kBlock], r2[kBlock], r3[kBlock], r4[kBlock];
+    double x = 0.0, y = 0.0, z = 0.0, k = 0.0;
     for (int i = threadIdx.x; i < a.nb; i += kBlock) {
       x += a.partial[2 * i];
       y += a.partial[2 * i + 1];
@@ -1181,12 +1181,15 @@ struct EnergyFinal {
     r1[threadIdx.x] = x;
     r2[threadIdx.x] = y;
     r3[threadIdx.x] = z;
+    for (int i = threadIdx.x; i < a.kin_nb; i += kBlock) k += a.kin_partial[i];
+    r4[threadIdx.x] = k;
     __syncthreads();
     for (int off = kBlock / 2; off > 0; off >>= 1) {
       if ((int)threadIdx.x < off) {
         r1[threadIdx.x] += r1[threadIdx.x + off];
         r2[threadIdx.x] += r2[threadIdx.x + off];
         r3[threadIdx.x] += r3[threadIdx.x + off];
+        r4[threadIdx.x] += r4[threadIdx.x + off];
       }
       __syncthreads();
     }
@@ -1194,6 +1197,7 @@ struct EnergyFinal {
     if (threadIdx.x == 0) {
       const double E = -0.5 * (r1[0] - a.cself * r2[0]) + 0.5 * r3[0];
       *a.energy = a.add ? *a.energy + E : E;
+      if (a.kin_out) *a.kin_out = 0.5 * r4[0];
     }
   }
 };
@@ -1461,6 +1465,12 @@ hipError_t launch_interpolate(mls_plan_s* P, int n, double* energy, double* forc
     ea.rep_nb = n > 0 ? P->rep_nb : 0;
   }
   ea.add = (mode & kInterpGridOnly) ? 1 : 0;
+  if (P->kin_out) {
+    ea.kin_partial = P->kin_partial;
+    ea.kin_nb = P->kin_nb;
+    ea.kin_out = P->kin_out;
+    P->kin_out = nullptr;
+  }
   return launch_one<EnergyFinal>(ea, 1, s);
 }
 

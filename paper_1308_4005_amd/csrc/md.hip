@@ -202,6 +202,7 @@ struct MdStep {
       if (a.mode & (kMdEnd | kMdStart | kMdSlowEnd | kMdSlowStart | kMdMidEnd | kMdMidStart))
         for (int d = 0; d < 3; ++d) a.vel[3 * (size_t)i + d] = v[d];
     }
+    if (!a.partial) return;   // no kinetic energy asked for
     const double t = block_sum(k, sh);
     if (threadIdx.x == 0) a.partial[blk] = t;
   }
@@ -289,15 +290,21 @@ hipError_t launch_repulsion(mls_plan_s* P, int n, double rc, hipStream_t s) {
 }
 
 hipError_t launch_md_step(mls_plan_s* P, int n, double* pos, double* vel, const double* forces,
-                          const double* inv_mass, double dt, int mode, double* kinetic, hipStream_t s,
+                          const double* inv_mass, double dt, int mode, double* kinetic, bool defer, hipStream_t s,
                           const double* fslow, double hslow, const double* fmid, double hmid) {
   double* part = P->d_md_partial + P->rep_cap;
   if (n > 0) {
-    MdStepArgs ma{pos, vel, forces, inv_mass, n, 0.5 * dt, dt, mode, part, P->d_flags, fslow, hslow, fmid, hmid};
+    MdStepArgs ma{pos, vel, forces, inv_mass, n, 0.5 * dt, dt, mode, kinetic ? part : nullptr, P->d_flags, fslow, hslow, fmid, hmid};
     hipError_t e = launch_one<MdStep>(ma, nblocks(n, kBlock), s);
     if (e != hipSuccess) return e;
   }
   if (!kinetic) return hipSuccess;
+  if (defer) {
+    P->kin_partial = part;
+    P->kin_nb = nblocks(n, kBlock);
+    P->kin_out = kinetic;
+    return hipSuccess;
+  }
   return launch_one<MdKinetic>(MdKineticArgs{part, nblocks(n, kBlock), kinetic}, 1, s);
 }
 
@@ -309,6 +316,7 @@ hipError_t launch_local_out(mls_plan_s* P, int n, double* energy, double* forces
     hipError_t e = launch_one<LocalOut>(la, nb, s);
     if (e != hipSuccess) return e;
   }
+  if (!energy) return hipSuccess;
   return launch_one<LocalEnergy>(LocalEnergyArgs{part, nb, P->d_md_partial, n > 0 ? P->rep_nb : 0, energy}, 1, s);
 }
 

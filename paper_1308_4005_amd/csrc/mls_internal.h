@@ -293,6 +293,9 @@ struct EnergyArgs {
   gptr<const double> rep_partial = nullptr;  // block sums of the repulsive energy (twice E_rep), or null
   int rep_nb = 0;
   int add = 0;                          // 1: add to *energy instead of overwriting it
+  gptr<const double> kin_partial = nullptr;  // molecular dynamics: kinetic block sums and where E_kin goes, or null
+  int kin_nb = 0;
+  gptr<double> kin_out = nullptr;
 };
 struct InterpLbArgs {
   gptr<const double4> xs; gptr<const double> sig; gptr<const int> perm; int n; GridGeom gg; gptr<const double> E1[7];
@@ -612,6 +615,10 @@ struct mls_plan_s {
   double skin = 0.0;               // neighbour reuse: see mls_params.skin
   double* d_xref = nullptr;        // positions of the last binning (n_max,3), plans with a skin
   int* d_rebin = nullptr;          // 1: the next conditional binning runs
+  // kinetic block sums waiting for the next energy reduction (kin_out null: none)
+  const double* kin_partial = nullptr;
+  int kin_nb = 0;
+  double* kin_out = nullptr;
   double* d_efast = nullptr;       // geometric mixing: energy of an inner step's fast evaluation
   bool ant_tiles = false;          // two-phase anterpolation tables built
   bool ant_large_tiles = false;    // set before building: tables for kAntTileMax tiles only
@@ -732,11 +739,12 @@ hipError_t launch_copy_stage(mls_plan_s* P, int what, int level, void* dst, hipS
 // molecular dynamics (md.hip): repulsion over the sorted atoms of the current
 // evaluation (its forces and energy join the outputs in the interpolation,
 // launch_interpolate with with_repulsion), and one velocity-Verlet
-// kernel (mode kMdEnd / kMdStart) with the kinetic energy written to *kinetic
+// kernel (mode kMdEnd / kMdStart) with the kinetic energy written to *kinetic:
+// by a kernel of its own, or (defer) by the next interpolation's energy reduction
 hipError_t launch_rep_gather(mls_plan_s* P, int n, const double* c12, hipStream_t s);
 hipError_t launch_repulsion(mls_plan_s* P, int n, double rc, hipStream_t s);
 hipError_t launch_md_step(mls_plan_s* P, int n, double* pos, double* vel, const double* forces,
-                          const double* inv_mass, double dt, int mode, double* kinetic, hipStream_t s,
+                          const double* inv_mass, double dt, int mode, double* kinetic, bool defer, hipStream_t s,
                           const double* fslow = nullptr, double hslow = 0.0, const double* fmid = nullptr,
                           double hmid = 0.0);
 // the local part alone as MD's fast force: forces = local + repulsive forces,
