@@ -91,6 +91,7 @@ struct PairConst {
   // FP32 candidate filter of the FP64 kernel: threshold (a^2 widened by the
   // FP32 rounding of the filter coordinates), cell widths, box
   float a2f, wf[3], Lf[3];
+  double k2[5];   // eq:gamma's own constants (k = 2) times a^-6 or a^-8
 };
 
 struct PairConstF {
@@ -392,8 +393,14 @@ __device__ __forceinline__ int xcd_block(int b, int nblk) {
   return x * q + (x < r ? x : r) + i;
 }
 
+// A kernel's second launch bound: K::kWavesPerSimd where it asks for one.
+template <class K, class = void>
+struct WavesPerSimd { static constexpr int value = 1; };
 template <class K>
-__global__ void __launch_bounds__(K::kThreads) k_one(typename K::Args a) {
+struct WavesPerSimd<K, decltype((void)K::kWavesPerSimd)> { static constexpr int value = K::kWavesPerSimd; };
+
+template <class K>
+__global__ void __launch_bounds__(K::kThreads, WavesPerSimd<K>::value) k_one(typename K::Args a) {
   K::run(a, xcd_block(blockIdx.x, gridDim.x));
 }
 
@@ -415,7 +422,7 @@ __global__ void __launch_bounds__(K::kThreads) k_batched(const typename K::Args*
 // values in registers across an item (the FP32 pair kernel 69 VGPRs against
 // 79, the tiled Lorentz-Berthelot interpolation 162 against 236).
 template <class K>
-__global__ void __launch_bounds__(K::kThreads) k_batched_each(const typename K::Args* __restrict__ args,
+__global__ void __launch_bounds__(K::kThreads, WavesPerSimd<K>::value) k_batched_each(const typename K::Args* __restrict__ args,
                                                               const int2* __restrict__ work,
                                                               const BatchIO* __restrict__ io) {
   const int2 it = work[xcd_block(blockIdx.x, gridDim.x)];
@@ -483,7 +490,7 @@ hipError_t launch_chains(const ChainArgs<K>& c, int blocks, hipStream_t s) {
 // blocks on that XCD.  The wave slots it leaves free on every CU serve the
 // kernels of other streams.
 template <class K>
-__global__ void __launch_bounds__(K::kThreads) k_persist(typename K::Args a, int nwork) {
+__global__ void __launch_bounds__(K::kThreads, WavesPerSimd<K>::value) k_persist(typename K::Args a, int nwork) {
   const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
   const int q = nwork / kXcds, r = nwork % kXcds;
   const int lo = x * q + (x < r ? x : r), cnt = q + (x < r ? 1 : 0);

@@ -44,9 +44,21 @@ __device__ __forceinline__ void g0_pair(T s, const C& pc, T& g, T& fr) {
     // gamma'(rho)/rho = -15 rho^10 + 9 rho^22 = rho^10 (9 v - 15)
     const T u3 = u2 * u;
     const T v = u3 * u3;
-    const T c0 = T(-15.0 / 8.0) * pc.inv_a6, c1 = T(5.0 / 4.0) * pc.inv_a6, c2 = T(-3.0 / 8.0) * pc.inv_a6;
-    g = ir6 + fma(v, fma(v, c2, c1), c0);
-    const T t = fma(v, T(-9) * pc.inv_a8, T(15) * pc.inv_a8);
+    // FP64 takes the constants from the arguments (scalar registers: computed
+    // here they held ten vector registers, two more than five waves per SIMD
+    // leave); FP32 has room for them
+    T c[5];
+    if constexpr (sizeof(T) == 8) {
+      for (int k = 0; k < 5; ++k) c[k] = pc.k2[k];
+    } else {
+      c[0] = T(-15.0 / 8.0) * pc.inv_a6;
+      c[1] = T(5.0 / 4.0) * pc.inv_a6;
+      c[2] = T(-3.0 / 8.0) * pc.inv_a6;
+      c[3] = T(-9) * pc.inv_a8;
+      c[4] = T(15) * pc.inv_a8;
+    }
+    g = ir6 + fma(v, fma(v, c[2], c[1]), c[0]);
+    const T t = fma(v, c[3], c[4]);
     fr = fma(T(-6) * ir6, ir2, (u3 * u2) * t);
   } else {
     T u4 = u2 * u2;
@@ -228,18 +240,27 @@ struct PairWave {
 // is at least a, and trims every other row to the cells the cutoff sphere
 // can reach along x (at most two runs of cells: one per periodic image).  A
 // cheap FP32 distance test (both precisions; see pair_scan_f32) appends
-// sources inside the cutoff to the lane's LDS queue (a ring), four
-// candidates per step; whenever a queue may overflow all lanes drain up to
-// kDrain of their oldest entries through the full g_0 evaluation, and at the
+// sources inside the cutoff to the lane's LDS queue, four candidates per step;
+// whenever a queue may overflow all lanes drain up to kDrain of their entries
+// through the full g_0 evaluation (FP64: the newest, so the slot of the next
+// entry is its count alone; FP32: the oldest, the rest moves up), and at the
 // end everything left, so the expensive arithmetic runs on nearly full waves
 // instead of being masked per candidate.  An FP64 entry packs the source
 // index (< 2^25) with two bits per dimension for its image.
+//
+// At 10^6 atoms the vector ALU issues 80 (FP64) to 97 % (FP32) of the time and
+// the L1 serves a line in three of four cycles, so what counts is the number
+// of instructions: of a filter step (47 vector ones for four candidates), of a
+// drained entry (FP64 51, FP32 43) and of a row's set-up (about 75); idle lanes
+// load nothing.  With 57, 67, 57 and 130 the kernel took 516 us in FP64
+// instead of 454 (10^6 atoms at density 0.8, a = 3), in FP32 392 instead of 376.
 constexpr int kWaveQ = 64;    // lanes per block (one wave)
-constexpr int kQueue = 32;    // entries per lane
-// The FP32 kernel's ring is half as long: 4 KB of LDS per wave lets 24 waves
-// share a CU (its VGPRs allow 24; 8 KB queues capped it at 20): pair kernel
-// 0.46 -> 0.44 ms at 10^6 atoms.  The FP64 kernel is held to 16 waves per CU
-// by its VGPRs, and a 16-entry ring only drains it more often (0.53 -> 0.64 ms).
+// Entries per lane: with the sums' 2 KB, 8 KB of LDS per wave, and held to 96
+// VGPRs (kWavesPerSimd), 20 waves share a CU.  32 entries and 16 waves: fewer
+// and fuller drains, but an evaluation of 10^6 atoms 777 us instead of 745.
+constexpr int kQueue = 24;
+// The FP32 kernel's queue and its table of shifts: 5.2 KB of LDS, 28 waves per
+// CU (its VGPRs allow as many).
 constexpr int kQueueF = 16;   // entries per lane of the FP32 kernel
 constexpr int kBatchF = 4;    // candidates per filter step
 
@@ -257,18 +278,30 @@ __device__ __forceinline__ const T& at32(const gptr<const T>& base, int j) {
   return at32((const T*)base, j);
 }
 
+// the same for the element that the low 24 bits of ent name
+template <class T>
+__device__ __forceinline__ const T& at24(const T* base, int ent) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + __umul24((unsigned)ent, (unsigned)sizeof(T)));
+}
+
+template <class T>
+__device__ __forceinline__ const T& at24(const gptr<const T>& base, int ent) {
+  return at24((const T*)base, ent);
+}
+
 __device__ __forceinline__ float4 load4f(const float* p) {
   float4 v;
   __builtin_memcpy(&v, p, sizeof(v));   // 4-byte aligned 16-byte load
   return v;
 }
 
-__device__ __forceinline__ int image_bits(int ix, int iy, int iz) { return (ix + 1) | ((iy + 1) << 2) | ((iz + 1) << 4); }
+// image indices -1, 0, 1 as two's-complement fields
+__device__ __forceinline__ int image_bits(int ix, int iy, int iz) { return (ix & 3) | ((iy & 3) << 2) | ((iz & 3) << 4); }
 
-// Four FP64 sums of one lane (energy, force x, y, z), kept in LDS at stride
-// kWaveQ while the lane's rows are scanned: only the drains read and write
-// them, so the filter loop carries none of them (held in registers, the four
-// were copied on every filter step, 11 of the loop's 70 instructions).
+// Four FP64 sums of one lane (energy, force x, y, z) of the FP64 kernel, kept in
+// LDS at stride kWaveQ while the lane's rows are scanned: only the drains read and write
+// them, so the filter loop carries none of them (their eight registers would
+// cost the fifth wave per SIMD).
 // Each drain starts with a compiler memory barrier (sums_fence): without it
 // the sums were hoisted out of the loop into registers again (the queue and
 // the sums are distinct LDS arrays), and volatile accesses instead made every
@@ -284,14 +317,12 @@ __device__ __forceinline__ void sums_fence() { asm volatile("" ::: "memory"); }
 // registers
 struct PairAcc {
   LaneSums a;
-  int cnt;
-  int head;   // the lane's queue is a ring of kQueue slots
+  int cnt;   // entries in the lane's queue
 };
 
 // Per-lane sums of the repulsive term (MD entry points): sum_j sqrt(C12_j)
 // r^-12 and sum_j 12 sqrt(C12_j) r^-14 d over the pairs with r < rc.  Kept in
-// registers: 2 KB more LDS per wave would cost these kernels occupancy (the
-// FP64 one 16 -> 13 waves per CU, the FP32 one its last wave of 20).
+// registers: 2 KB more LDS per wave would cost the kernels occupancy.
 struct RepAcc {
   double v[4];
   __device__ __forceinline__ double& operator[](int k) { return v[k]; }
@@ -304,19 +335,20 @@ constexpr int kSumSlots = 4 * kWaveQ;
 // A drain during the scan consumes at most this many entries per lane: the
 // lane that forced it is then well below the limit, and lanes with few
 // entries idle for fewer steps than in a drain to empty.
-constexpr int kDrain = 16;
+constexpr int kDrain = 8;
 
-// Full g_0 evaluation of up to `limit` queued sources per lane, oldest first.
+// Full g_0 evaluation of the newest queued sources of each lane, up to `limit`.
 // The loop body has no branches: slots past a lane's count (and the target
 // itself) evaluate a harmless pair with zero weight, adding exactly 0.
 template <int K, bool LB, bool R>
-__device__ __forceinline__ void pair_drain_f64(const int* __restrict__ queue, int limit, int lane, int self_ent,
-                                               int safe_j, const double4& xi, const double4* __restrict__ xs,
+__device__ __forceinline__ void pair_drain_f64(const int* queue, int limit, int lane, int self_ent,
+                                               int safe_ent, const double4& xi, const double4* __restrict__ xs,
                                                const CellGeom& g, const PairConst& pc, const double* __restrict__ sig,
                                                double sig_i, PairAcc& A, const PairRep& rp, RepAcc& B) {
   sums_fence();
   const double r2_idle = 0.25 * pc.a2;
-  const int cnt = A.cnt;
+  const int done = min(A.cnt, limit);
+  const int* q0 = queue + (A.cnt - done) * kWaveQ + lane;
   // the lane's running sums, added to pair by pair as if held throughout
   double ae = A.a[0], afx = A.a[1], afy = A.a[2], afz = A.a[3];
   double be = 0.0, bfx = 0.0, bfy = 0.0, bfz = 0.0;
@@ -326,18 +358,17 @@ __device__ __forceinline__ void pair_drain_f64(const int* __restrict__ queue, in
     bfy = B[2];
     bfz = B[3];
   }
-  for (int t = 0; t < limit && __any(t < cnt); ++t) {
-    const int q = queue[((A.head + t) & (kQueue - 1)) * kWaveQ + lane];
-    const bool ok = (t < cnt) & (q != self_ent);
-    const int ent = ok ? q : image_bits(0, 0, 0);
-    const int j = ok ? (ent >> 6) : safe_j;
-    const double sx = (double)((ent & 3) - 1) * g.L[0];
-    const double sy = (double)(((ent >> 2) & 3) - 1) * g.L[1];
-    const double sz = (double)(((ent >> 4) & 3) - 1) * g.L[2];
-    const double4 xj = at32(xs, j);
-    const double dx = (xi.x - sx) - xj.x;
-    const double dy = (xi.y - sy) - xj.y;
-    const double dz = (xi.z - sz) - xj.z;
+  // loop-carried: an idle lane keeps what it read last (at first its own row)
+  double4 xj = xi;
+  for (int t = 0; t < limit && __any(t < done); ++t, q0 += kWaveQ) {
+    const int q = *q0;
+    const bool ok = (t < done) & (q != self_ent);
+    const int ent = ok ? q : safe_ent;
+    const int j = (int)((unsigned)ent >> 6);
+    if (ok) xj = at32(xs, j);
+    const double dx = fma((double)((ent << 30) >> 30), -g.L[0], xi.x) - xj.x;
+    const double dy = fma((double)((ent << 28) >> 30), -g.L[1], xi.y) - xj.y;
+    const double dz = fma((double)((ent << 26) >> 30), -g.L[2], xi.z) - xj.z;
     const double d2 = dx * dx + dy * dy + dz * dz;
     // the FP32 filter passes a superset: the pair set is decided here, in
     // FP64, by r^2 < a^2 (rejected entries add exactly 0)
@@ -372,76 +403,181 @@ __device__ __forceinline__ void pair_drain_f64(const int* __restrict__ queue, in
     B[2] = bfy;
     B[3] = bfz;
   }
-  const int done = min(cnt, limit);
-  A.head = (A.head + done) & (kQueue - 1);
-  A.cnt = cnt - done;
+  A.cnt -= done;
 }
 
-// Scan sources [j, j1) seen through image bits `img`, row offsets dy, dz
-// (convergent: every lane calls it; lanes with an empty range just take part
-// in the votes).  Candidates are tested by the FP32 filter of the mixed
-// kernel (absolute x, cell-relative y and z, one 16-byte load per coordinate
-// and batch of four, threshold a2f widened for FP32 rounding): it passes a
-// superset of the pairs inside the cutoff, and the drain decides each pair
-// in FP64.  Reads may run up to three rows past j1 (padded array); lanes
-// past their range load nothing.  The filter loop touches no accumulator: it
-// stops when a queue may overflow, the queues are partly drained, and the
-// filter resumes.
+// Four registers whatever they hold: what lanes without a load of their own
+// pass on, where a mask then discards it.  (Kept live instead, the last
+// candidates took twelve registers through every drain.)
+__device__ __forceinline__ float4 any4() {
+  float4 v;
+  asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
+  return v;
+}
+
+// The filter's three coordinate arrays (absolute x, cell-relative y and z).
+struct FilterRows {
+  const float *x, *y, *z;
+  __device__ __forceinline__ FilterRows(const float* xf, int stride) : x(xf), y(xf + stride), z(xf + 2 * (size_t)stride) {}
+};
+
+// One filter step: the four candidates at byte offset `off` of the arrays
+// against the target's ax, ay, az, those past `off1` left out.  Every
+// candidate writes its entry to the lane's next free queue slot, which the
+// count passes only on a hit.  Few and cheap instructions are the point: the
+// byte offset serves the loads, the entries and the tests of the run's end
+// (against limits set once per run), and the slot follows from the count by
+// one shift and add.  IB: bits below the source index in an entry (0: the
+// run's bits lie above it).
+template <int IB>
+struct FilterRun {
+  int off, lim[4];
+  float ax, ay, az;
+  int bits;
+  __device__ __forceinline__ FilterRun(int j0, int j1, float ax_, float ay_, float az_, int bits_)
+      : off(4 * j0), ax(ax_), ay(ay_), az(az_), bits(bits_) {
+    // candidate b of a step counts while off < 4 (j1 - b); an empty run: never
+#pragma unroll
+    for (int b = 0; b < 4; ++b) lim[b] = 4 * j1 - 4 * b;
+  }
+  __device__ __forceinline__ bool more() const { return off < lim[0]; }
+  __device__ __forceinline__ void load(const FilterRows& f, float4& X, float4& Y, float4& Z) const {
+    X = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.x) + (unsigned)off));
+    Y = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.y) + (unsigned)off));
+    Z = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.z) + (unsigned)off));
+  }
+  __device__ __forceinline__ int test(const float4& X, const float4& Y, const float4& Z, float a2f, int* qlane, int cnt) {
+    const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
+    const int ent0 = (IB ? off << (IB - 2) : off >> 2) | bits;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const float dx = ax - xb[b], dy = ay - yb[b], dz = az - zb[b];
+      const float r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+      const bool hit = (off < lim[b]) & (r2 < a2f);
+      qlane[kWaveQ * cnt] = ent0 + (b << IB);
+      cnt += hit ? 1 : 0;
+    }
+    off += 16;
+    return cnt;
+  }
+};
+
+// Scan sources [j, j1) seen through image bits `img` (convergent: every lane
+// calls it; lanes with an empty range just take part in the votes).
+// Candidates are tested by the FP32 filter of the mixed kernel (threshold a2f
+// widened for FP32 rounding): it passes a superset of the pairs inside the
+// cutoff, and the drain decides each pair in FP64.  Reads may run up to three
+// rows past j1 (padded array); lanes past their range load nothing, and the end
+// test masks what they hold.  One loop level, the drain inside it: the
+// accumulators change only on the drain path.
 template <int K, bool LB, bool R>
-__device__ __forceinline__ void pair_scan_f64(int j, int j1, int img, int dy, int dz, int* __restrict__ queue,
-                                              int lane, int self_ent, int safe_j, const double4& xi, const float3& xf_i,
-                                              const double4* __restrict__ xs, const float* __restrict__ xf, int xfs,
-                                              const CellGeom& g, const PairConst& pc,
+__device__ __forceinline__ void pair_scan_f64(FilterRun<6> r, int* __restrict__ queue, int lane, int self_ent,
+                                              int safe_ent, const double4& xi, const double4* __restrict__ xs,
+                                              const FilterRows& f, const CellGeom& g, const PairConst& pc,
                                               const double* __restrict__ sig, double sig_i, PairAcc& A,
                                               const PairRep& rp, RepAcc& B) {
-  const float ax = fmaf((float)-((img & 3) - 1), pc.Lf[0], xf_i.x);
-  const float ay = fmaf((float)-dy, pc.wf[1], xf_i.y);
-  const float az = fmaf((float)-dz, pc.wf[2], xf_i.z);
   int* const qlane = queue + lane;
-  const float* const xf1 = xf + xfs;
-  const float* const xf2 = xf1 + xfs;
-  // loop-carried, so a finished lane keeps stale values; b < rem masks them
-  float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X;
-  for (;;) {
-    int cnt = A.cnt;
-    const int head = A.head;
-    bool full = false;
-    while (__any(j < j1)) {
-      const int rem = j1 - j;   // sources left in the run (<= 0: none)
-      if (j < j1) {
-        // a 32-bit byte offset from the uniform array bases
-        const unsigned off = (unsigned)j * 4u;
-        X = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf) + off));
-        Y = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf1) + off));
-        Z = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf2) + off));
-      }
-      const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
-      const int ent0 = (j << 6) | img;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
-        const float r2 = dxv * dxv + dyv * dyv + dzv * dzv;
-        const bool hit = (b < rem) & (r2 < pc.a2f);
-        // the next free slot: write unconditionally, keep on a hit
-        qlane[kWaveQ * ((head + cnt) & (kQueue - 1))] = ent0 + (b << 6);
-        cnt += hit ? 1 : 0;
-      }
-      // finished lanes advance too: rem <= 0 masks them and the loads stay
-      // guarded by j < j1 (j grows by at most 4 per step of the slowest lane)
-      j += 4;
-      if (__any(cnt > kQueue - 4)) {
-        full = true;
-        break;
-      }
+  int cnt = A.cnt;
+  while (__any(r.more())) {
+    float4 X = any4(), Y = any4(), Z = any4();
+    if (r.more()) r.load(f, X, Y, Z);
+    cnt = r.test(X, Y, Z, pc.a2f, qlane, cnt);
+    if (__builtin_expect(__any(cnt > kQueue - 4), 0)) {
+      A.cnt = cnt;
+      pair_drain_f64<K, LB, R>(queue, kDrain, lane, self_ent, safe_ent, xi, xs, g, pc, sig, sig_i, A, rp, B);
+      cnt = A.cnt;
     }
-    A.cnt = cnt;
-    if (!full) break;
-    pair_drain_f64<K, LB, R>(queue, kDrain, lane, self_ent, safe_j, xi, xs, g, pc, sig, sig_i, A, rp, B);
   }
+  A.cnt = cnt;
 }
 
-__device__ __forceinline__ double gap1(double x, double lo, double w, double eps) {
-  return fmax(0.0, fmax(lo - x, x - (lo + w)) - eps);
+// The two runs [j0, j1), [k0, k1) of one row of cells (x images ix1, ix2) that
+// a target's cutoff sphere can reach; empty for an idle lane.
+struct RowRuns {
+  int j0, j1, ix1, k0, k1, ix2;
+};
+
+// Rows are chosen and trimmed in the target's cell-relative FP32 coordinates.
+// The gaps are shrunk and the reach grown by margins (1e-5 of a cell, 2e-5 of
+// the cutoff) far above their FP32 rounding (~1e-7), so no cell that holds a
+// source inside the cutoff is ever skipped; mg, the skin margin of neighbour
+// reuse (atoms may sit that far outside their cells), does the same.
+struct RowTrim {
+  const int* cstart;
+  float w[3], inv_wx, a2m, mg;
+  int nc[3];
+  __device__ __forceinline__ RowTrim(const int* start, const CellGeom& g, const float* wf, float a2)
+      : cstart(start), w{wf[0], wf[1], wf[2]}, inv_wx(1.0f / wf[0]), a2m(a2 * (1.0f + 2e-5f)), mg((float)g.margin),
+        nc{g.nc[0], g.nc[1], g.nc[2]} {}
+  // distance of a target at cell-relative coordinate x to the cells d away
+  __device__ __forceinline__ float gap(int k, int d, float x) const {
+    return d == 0 ? 0.0f
+                  : fmaxf(0.0f, (d > 0 ? fmaf((float)d, w[k], -x) : fmaf((float)(-d - 1), w[k], x)) - 1e-5f * w[k] - mg);
+  }
+  // Runs of the row whose first cell is `row`, rem = a^2 minus the squared
+  // gaps in y and z, of a target at cell-relative x in cell cx.  Most waves
+  // have no lane whose run crosses the periodic edge.
+  __device__ __forceinline__ RowRuns runs(int cx, float x, bool active, float rem, int row) const {
+    const float reach = 1.0f + 2e-5f;
+    const int nc0 = nc[0];
+    int clo = 0, chi = -1;
+    if (active && rem > 0.0f) {
+      // hardware square root (about 1 ulp): far inside the margin
+      const float rx = fmaf(__builtin_amdgcn_sqrtf(rem), reach, 1e-5f * w[0] + mg);
+      clo = cx + max(-2, (int)floorf((x - rx) * inv_wx));
+      chi = cx + min(2, (int)floorf((x + rx) * inv_wx));
+    }
+    RowRuns r{0, 0, 0, 0, 0, 0};
+    int lo1 = clo, hi1 = chi;
+    if (__any((clo < 0) | (chi >= nc0))) {
+      int lo2 = 0, hi2 = -1;
+      if (clo < 0) {
+        lo1 = clo + nc0; hi1 = nc0 - 1; r.ix1 = -1;
+        lo2 = 0; hi2 = chi; r.ix2 = 0;
+      } else if (chi >= nc0) {
+        lo1 = clo; hi1 = nc0 - 1; r.ix1 = 0;
+        lo2 = 0; hi2 = chi - nc0; r.ix2 = 1;
+      }
+      if (lo2 <= hi2) {
+        r.k0 = at32(cstart, row + lo2);
+        r.k1 = at32(cstart, row + hi2 + 1);
+      }
+    }
+    if (lo1 <= hi1) {
+      r.j0 = at32(cstart, row + lo1);
+      r.j1 = at32(cstart, row + hi1 + 1);
+    }
+    return r;
+  }
+};
+
+// A wave's walk over its targets' rows (dz, dy): scan(runs, dz, dy, iz, iy) for
+// each, with the row's periodic images.  The wrapped row's first cell is kept
+// by additions.  Span: the loops' bounds (RowSpan).
+template <class Span, class Scan>
+__device__ __forceinline__ void walk_rows(const RowTrim& w, const Span& span, int cx, int cy, int cz, float x, float y,
+                                          float z, bool active, Scan&& scan) {
+  const int slab = w.nc[1] * w.nc[0];
+  for (int dz = span.z0(); dz <= span.z1(); ++dz) {
+    const int uz = cz + dz;
+    const int iz = uz < 0 ? -1 : (uz >= w.nc[2] ? 1 : 0);
+    const int rowz = (uz - iz * w.nc[2]) * slab;
+    const float gz = w.gap(2, dz, z);
+    const float rem_z = w.a2m - gz * gz;
+    const int y0 = span.y0(dz), y1 = span.y1(dz);
+    int uy = cy + y0;
+    int iy = uy < 0 ? -1 : (uy >= w.nc[1] ? 1 : 0);
+    int rowy = (uy - iy * w.nc[1]) * w.nc[0];
+    for (int dy = y0; dy <= y1; ++dy) {
+      const float gy = w.gap(1, dy, y);
+      scan(w.runs(cx, x, active, rem_z - gy * gy, rowz + rowy), dz, dy, iz, iy);
+      rowy += w.nc[0];
+      if (rowy == slab) {
+        rowy = 0;
+        ++iy;
+      }
+    }
+  }
 }
 
 // Per-wave sum of one value (lanes of a 64-wide block).
@@ -529,6 +665,7 @@ template <int K, bool LB = false, bool R = false, int NS = 1>
 struct PairTrimF64 {
   using Args = PairArgs;
   static constexpr int kThreads = kWaveQ * NS;
+  static constexpr int kWavesPerSimd = NS == 1 && !R ? 5 : 1;   // with R's sums it would spill
   static __device__ void run(const Args& ar, int blk) {
   const double4* __restrict__ xs = ar.xs;
   const int* __restrict__ cstart = ar.cstart;
@@ -544,68 +681,32 @@ struct PairTrimF64 {
   const int sc = active ? k : n - 1;
   const double4 xi = xs[sc];
   const double sig_i = LB ? ar.sig[sc] : 0.0;
-  const float* __restrict__ xf = ar.xf;
-  const int xfs = ar.xf_stride;
-  const float3 xf_i = make_float3(xf[sc], xf[xfs + sc], xf[2 * xfs + sc]);
+  const FilterRows f(ar.xf, ar.xf_stride);
+  const float3 xf_i = make_float3(f.x[sc], f.y[sc], f.z[sc]);
   const int c = ar.cell_s[sc];
   const int cx = c % g.nc[0], cy = (c / g.nc[0]) % g.nc[1], cz = c / (g.nc[0] * g.nc[1]);
   // the target itself, seen in the home image, is skipped in the drain
-  const int self_ent = active ? ((sc << 6) | image_bits(0, 0, 0)) : -1;
+  const int safe_ent = sc << 6;
+  const int self_ent = active ? safe_ent | image_bits(0, 0, 0) : -1;
   __shared__ double all_sums[NS * kSumSlots];
   double* const sums = all_sums + span.wv * kSumSlots;
   for (int k = 0; k < kSumSlots / kWaveQ; ++k) sums[k * kWaveQ + lane] = 0.0;
-  PairAcc A{LaneSums{sums + lane}, 0, 0};
+  PairAcc A{LaneSums{sums + lane}, 0};
   RepAcc B{{0.0, 0.0, 0.0, 0.0}};
   const PairRep& rp = ar.rep;
-  const float reach = (float)(1.0 + 1e-5);
-  for (int dz = span.z0(); dz <= span.z1(); ++dz) {
-    const int uz = cz + dz;
-    const int iz = uz < 0 ? -1 : (uz >= g.nc[2] ? 1 : 0);
-    const int tz = uz - iz * g.nc[2];
-    // gaps shrunk (and the reach below grown) by the skin margin: with
-    // neighbour reuse atoms may sit that far outside their cells
-    const double gz = gap1(xi.z, uz * g.w[2], g.w[2], 1e-12 * g.L[2] + g.margin);
-    const int y1 = span.y1(dz);
-    for (int dy = span.y0(dz); dy <= y1; ++dy) {
-      const int uy = cy + dy;
-      const int iy = uy < 0 ? -1 : (uy >= g.nc[1] ? 1 : 0);
-      const int ty = uy - iy * g.nc[1];
-      const double gy = gap1(xi.y, uy * g.w[1], g.w[1], 1e-12 * g.L[1] + g.margin);
-      const double rem = pc.a2 - (gy * gy + gz * gz);
-      int clo = 0, chi = -1;
-      if (active && rem > 0.0) {
-        // x cells the cutoff sphere reaches in this row (conservatively widened)
-        const double rx = (double)(sqrtf((float)rem) * reach) + 1e-6 * g.w[0] + g.margin;
-        clo = max(cx - 2, (int)floor((xi.x - rx) * g.inv_w[0]));
-        chi = min(cx + 2, (int)floor((xi.x + rx) * g.inv_w[0]));
-      }
-      // at most one box edge inside [clo, chi] (nc >= 5): two runs of cells
-      int lo1 = clo, hi1 = chi, ix1 = 0, lo2 = 0, hi2 = -1, ix2 = 0;
-      if (clo < 0) {
-        lo1 = clo + g.nc[0]; hi1 = g.nc[0] - 1; ix1 = -1;
-        lo2 = 0; hi2 = chi; ix2 = 0;
-      } else if (chi >= g.nc[0]) {
-        lo1 = clo; hi1 = g.nc[0] - 1; ix1 = 0;
-        lo2 = 0; hi2 = chi - g.nc[0]; ix2 = 1;
-      }
-      const int row = (tz * g.nc[1] + ty) * g.nc[0];
-      int j0 = 0, j1 = 0;
-      if (lo1 <= hi1) {
-        j0 = cstart[row + lo1];
-        j1 = cstart[row + hi1 + 1];
-      }
-      int k0 = 0, k1 = 0;
-      if (lo2 <= hi2) {
-        k0 = cstart[row + lo2];
-        k1 = cstart[row + hi2 + 1];
-      }
-      pair_scan_f64<K, LB, R>(j0, j1, image_bits(ix1, iy, iz), dy, dz, queue, lane, self_ent, sc, xi, xf_i, xs, xf,
-                              xfs, g, pc, ar.sig, sig_i, A, rp, B);
-      pair_scan_f64<K, LB, R>(k0, k1, image_bits(ix2, iy, iz), dy, dz, queue, lane, self_ent, sc, xi, xf_i, xs, xf,
-                              xfs, g, pc, ar.sig, sig_i, A, rp, B);
-    }
-  }
-  pair_drain_f64<K, LB, R>(queue, kQueue, lane, self_ent, sc, xi, xs, g, pc, ar.sig, sig_i, A, rp, B);
+  const RowTrim w(cstart, g, pc.wf, (float)pc.a2);
+  walk_rows(w, span, cx, cy, cz, (float)(xi.x - cx * g.w[0]), xf_i.y, xf_i.z, active,
+            [&](const RowRuns& r, int dz, int dy, int iz, int iy) {
+    auto scan = [&](int j0, int j1, int ix) {
+      if (!__any(j0 < j1)) return;
+      const FilterRun<6> run(j0, j1, fmaf((float)-ix, pc.Lf[0], xf_i.x), fmaf((float)-dy, pc.wf[1], xf_i.y),
+                             fmaf((float)-dz, pc.wf[2], xf_i.z), image_bits(ix, iy, iz));
+      pair_scan_f64<K, LB, R>(run, queue, lane, self_ent, safe_ent, xi, xs, f, g, pc, ar.sig, sig_i, A, rp, B);
+    };
+    scan(r.j0, r.j1, r.ix1);
+    scan(r.k0, r.k1, r.ix2);
+  });
+  pair_drain_f64<K, LB, R>(queue, kQueue, lane, self_ent, safe_ent, xi, xs, g, pc, ar.sig, sig_i, A, rp, B);
   if constexpr (NS > 1) {
     store_split<NS, R>(all_sums, queues, kQueue * kWaveQ, B, span.wv, lane, active, sc, blk, xi.w, ar.e0, ar.floc, rp);
     return;
@@ -627,36 +728,44 @@ struct PairTrimF64 {
 // drain.  The displacement is rebuilt as
 //   d_x = (cx_i - ix nc - cx_j) w_x + xr_i - xr_j,  d_y = yr_i - dy w_y - yr_j, ...
 // with integer cell offsets, so no large coordinates enter FP32 arithmetic.
-// Queue entries pack the source index (< 2^24), the x image and the row
-// offsets dy, dz.  Pair arithmetic is FP32; each drain sums its terms in
+// Queue entries pack the source index (< 2^24) and, in the top byte, one of the
+// 75 row offsets dz, dy and x images, looked up in LDS as shifts: cells along x
+// and lengths along y and z.  Pair arithmetic is FP32; each drain sums its terms in
 // FP32, and e_0 and the forces accumulate the drains' sums in FP64.
 struct PairAccM {
-  LaneSums a;   // e_0 and the force, FP64, in LDS
-  int cnt;
-  int head;     // the lane's queue is a ring of kQueueF slots
+  double a[4];  // e_0 and the force
+  int cnt;      // entries in the lane's queue
 };
 
 // An FP32 drain consumes at most this many entries per lane: the lane that
 // forced it is then below the limit again (at most 16 - 8 = 8 entries, one
 // filter step adds at most 4 to the 12 that trigger a drain), and lanes with
-// few entries idle for fewer steps than in a drain to empty (measured at 10^6
-// atoms with the 16-entry ring: pair kernel 0.44 ms with 8 and with 4, 0.46
-// ms with 12).
+// few entries idle for fewer steps than in a drain to empty (at 10^6 atoms the
+// kernel took 0.44 ms with 8 and with 4, 0.46 ms with 12).
 constexpr int kDrainF = 8;
 
 // Per-lane target data of the FP32 scan.
 struct PairLaneF {
   float xx, yy, zz;     // target cell-relative coordinates
-  float cxf, ncf;       // target cell x index, cells along x
+  float cxf;            // target cell x index
   int self_ent;         // the target's own home-row entry (-1 for idle lanes)
-  int safe_j;           // a valid source index for idle drain slots
+  int safe_ent;         // the target as an entry: a valid source for idle drain slots
+  const float4* shift;  // shifts by the entries' top byte (LDS)
   float sig_i;          // Lorentz-Berthelot: the target's sigma
   float xa;             // target absolute x (filter)
 };
 
-// Queue entry: source index << 8 | x image ix (2 bits) | dy (3 bits) | dz (3
-// bits), the three as two's-complement fields.
-__device__ __forceinline__ int entry_bits(int ix, int dy, int dz) { return (ix & 3) | ((dy & 7) << 2) | ((dz & 7) << 5); }
+// Top byte of a queue entry: x image ix and row offsets dy, dz.
+constexpr int kShifts = 75;
+__device__ __forceinline__ int entry_bits(int ix, int dy, int dz) { return ((dz + 2) * 15 + (dy + 2) * 3 + ix + 1) << 24; }
+
+// The shifts; dy w and dz w are exact (a power of two times w).  One wave.
+__device__ __forceinline__ void fill_shifts(float4* tab, int lane, const CellGeom& g, const PairConstF& pc) {
+  for (int c = lane; c < kShifts; c += kWaveQ) {
+    const int dz = c / 15 - 2, dy = c / 3 % 5 - 2, ix = c % 3 - 1;
+    tab[c] = make_float4((float)(-ix * g.nc[0]), (float)-dy * pc.w[1], (float)-dz * pc.w[2], 0.0f);
+  }
+}
 
 // The (at most 16) terms of one drain are summed in FP32: e_0, the force and,
 // with R, the repulsive energy and force.
@@ -669,21 +778,20 @@ struct DrainF {
 // evaluation, added to D; !ok: a harmless pair of weight 0, which adds exactly
 // 0 (no branches).
 template <int K, bool R, bool LB>
-__device__ __forceinline__ void pair_term_f32(bool ok, int ent, int j, const float4& xj, float wsrc,
-                                              const PairLaneF& L, const float* __restrict__ sig,
-                                              const PairConstF& pc, const PairRep& rp, DrainF<R>& D) {
-  const int ix = (ent << 30) >> 30, dy = (ent << 27) >> 29, dz = (ent << 24) >> 29;
-  const float bx = fmaf((float)ix, -L.ncf, L.cxf);
-  const float dxv = fmaf(bx - xj.w, pc.w[0], L.xx) - xj.x;
-  const float dyv = fmaf((float)-dy, pc.w[1], L.yy) - xj.y;
-  const float dzv = fmaf((float)-dz, pc.w[2], L.zz) - xj.z;
-  const float r2 = ok ? dxv * dxv + dyv * dyv + dzv * dzv : 0.25f * pc.a2;
+__device__ __forceinline__ void pair_term_f32(bool ok, int ent, const float4& xj, float wsrc, const PairLaneF& L,
+                                              const float* __restrict__ sig, const PairConstF& pc, const PairRep& rp,
+                                              DrainF<R>& D) {
+  const float4 sh = L.shift[(unsigned)ent >> 24];
+  const float dxv = fmaf((L.cxf + sh.x) - xj.w, pc.w[0], L.xx) - xj.x;
+  const float dyv = (L.yy + sh.y) - xj.y;
+  const float dzv = (L.zz + sh.z) - xj.z;
+  const float r2 = ok ? fmaf(dzv, dzv, fmaf(dyv, dyv, dxv * dxv)) : 0.25f * pc.a2;
   float gg, fr;
   g0_pair<float, K>(r2, pc, gg, fr);
   float wj = wsrc;
   if constexpr (LB) {
     // source weight e_j ((sigma_i + sigma_j) / 2)^6, as in the FP64 kernels
-    const float m = 0.5f * (L.sig_i + sig[j]);
+    const float m = 0.5f * (L.sig_i + at24(sig, ent));
     const float m3 = m * m * m;
     wj *= m3 * m3;
   }
@@ -695,7 +803,7 @@ __device__ __forceinline__ void pair_term_f32(bool ok, int ent, int j, const flo
   if constexpr (R) {
     const float ir2 = recip(r2);
     const float ir6 = ir2 * ir2 * ir2;
-    const float v = (ok && r2 < (float)rp.rc2 ? rp.x12f[j] : 0.0f) * ir6 * ir6;
+    const float v = (ok && r2 < (float)rp.rc2 ? at24(rp.x12f, ent) : 0.0f) * ir6 * ir6;
     const float fv = 12.0f * v * ir2;
     D.s[4] += v;
     D.s[5] = fmaf(fv, dxv, D.s[5]);
@@ -704,95 +812,70 @@ __device__ __forceinline__ void pair_term_f32(bool ok, int ent, int j, const flo
   }
 }
 
-// Full g_0 evaluation of up to `limit` queued sources per lane, oldest first.
+// Full g_0 evaluation of up to `limit` queued sources per lane, oldest first;
+// what is left moves to the front (at most kQueueF - kDrainF entries).
 template <int K, bool R, bool LB>
-__device__ __forceinline__ void pair_drain_f32(const int* __restrict__ queue, int limit, int lane,
-                                               const PairLaneF& L, const float4* __restrict__ xr,
-                                               const float* __restrict__ xif, const float* __restrict__ sig,
-                                               const PairConstF& pc, PairAccM& A, const PairRep& rp, RepAcc& B) {
-  sums_fence();
+__device__ __forceinline__ void pair_drain_f32(int* queue, int limit, int lane, const PairLaneF& L,
+                                               const float4* __restrict__ xr, const float* __restrict__ xif,
+                                               const float* __restrict__ sig, const PairConstF& pc, PairAccM& A,
+                                               const PairRep& rp, RepAcc& B) {
+  int* const qlane = queue + lane;
   const int cnt = A.cnt;
   DrainF<R> D;
-  for (int t = 0; t < limit && __any(t < cnt); ++t) {
-    const int q = queue[((A.head + t) & (kQueueF - 1)) * kWaveQ + lane];
+  // loop-carried: an idle lane keeps what it read last (at first its own row)
+  float4 xj = make_float4(L.xx, L.yy, L.zz, L.cxf);
+  float w = 0.0f;
+  const int* q0 = qlane;
+  for (int t = 0; t < limit && __any(t < cnt); ++t, q0 += kWaveQ) {
+    const int q = *q0;
+    // idle slots and the target itself load nothing and weigh 0
     const bool ok = (t < cnt) & (q != L.self_ent);
-    const int ent = ok ? q : 0;
-    const int j = ok ? (int)((unsigned)ent >> 8) : L.safe_j;
-    // idle slots load nothing (they take a harmless far pair of weight 0)
-    float4 xj = make_float4(L.xx + pc.w[0], L.yy, L.zz, L.cxf);
-    float wsrc = 0.0f;
+    const int ent = ok ? q : L.safe_ent;
     if (ok) {
-      xj = at32(xr, j);
-      wsrc = at32(xif, j);
+      xj = at24(xr, ent);
+      w = at24(xif, ent);
     }
-    pair_term_f32<K, R, LB>(ok, ent, j, xj, wsrc, L, sig, pc, rp, D);
+    pair_term_f32<K, R, LB>(ok, ent, xj, ok ? w : 0.0f, L, sig, pc, rp, D);
   }
   for (int c = 0; c < 4; ++c) A.a[c] += (double)D.s[c];
   if constexpr (R)
     for (int c = 0; c < 4; ++c) B[c] += (double)D.s[4 + c];
-  const int done = min(cnt, limit);
-  A.head = (A.head + done) & (kQueueF - 1);
-  A.cnt = cnt - done;
+  if (limit < kQueueF) {
+    int rest[kQueueF - kDrainF];
+#pragma unroll
+    for (int u = 0; u < kQueueF - kDrainF; ++u) rest[u] = qlane[(kDrainF + u) * kWaveQ];
+#pragma unroll
+    for (int u = 0; u < kQueueF - kDrainF; ++u) qlane[u * kWaveQ] = rest[u];
+  }
+  A.cnt = cnt - min(cnt, limit);
 }
 
-// Scan sources [j, j1) of one row run (image ix along x, row offsets dy, dz).
-// The filter loop touches no accumulator: it stops when a queue may
-// overflow, the queues are partly drained, and the filter resumes.
-// The filter takes x from the absolute FP32 coordinates (one subtraction per
-// candidate instead of rebuilding the cell offset) and y, z cell-relative;
-// its threshold a2f covers the rounding of absolute x (a few ulp of L), and
-// the few extra pairs it passes, just outside a, add g_0 ~ 0 in the drain,
-// which rebuilds the displacement exactly from the cell-relative data.  The
-// coordinates are three arrays, so one 16-byte load brings one coordinate of
-// a batch of four candidates; lanes past the end of their run load nothing.
-// The vector memory pipeline, as much as the ALU, bounds this loop.
-
+// Scan sources of one row run.  The filter takes x from the absolute FP32
+// coordinates (one subtraction per candidate instead of rebuilding the cell
+// offset) and y, z cell-relative; its threshold a2f covers the rounding of
+// absolute x (a few ulp of L), and the few extra pairs it passes, just outside
+// a, add g_0 ~ 0 in the drain, which rebuilds the displacement exactly from
+// the cell-relative data.  The coordinates are three arrays, so one 16-byte
+// load brings one coordinate of a batch of four candidates; lanes past the end
+// of their run load nothing, and the end test masks them.  One loop level, the
+// drain inside it: the accumulators change only on the drain path (a loop
+// nest made the compiler copy them every filter step).
 template <int K, bool R, bool LB>
-__device__ __forceinline__ void pair_scan_f32(int j, int j1, int ix, int dy, int dz, int* __restrict__ queue,
-                                              int lane, const PairLaneF& L, const float4* __restrict__ xr,
-                                              const float* __restrict__ xf, int xfs, const float* __restrict__ xif,
-                                              const float* __restrict__ sig, const PairConstF& pc, PairAccM& A,
-                                              const PairRep& rp, RepAcc& B, float4& X, float4& Y, float4& Z) {
+__device__ __forceinline__ void pair_scan_f32(FilterRun<0> r, int* __restrict__ queue, int lane, const PairLaneF& L,
+                                              const float4* __restrict__ xr, const FilterRows& f,
+                                              const float* __restrict__ xif, const float* __restrict__ sig,
+                                              const PairConstF& pc, PairAccM& A, const PairRep& rp, RepAcc& B) {
   static_assert(kBatchF == 4, "one 16-byte load per coordinate and batch");
-  const float ax = fmaf((float)-ix, pc.L[0], L.xa);
-  const float ay = fmaf((float)-dy, pc.w[1], L.yy);
-  const float az = fmaf((float)-dz, pc.w[2], L.zz);
-  const int bits = entry_bits(ix, dy, dz);
   int* const qlane = queue + lane;
-  const float* const xf1 = xf + xfs;
-  const float* const xf2 = xf1 + xfs;
-  // X, Y, Z are the caller's, carried across runs: a finished lane keeps
-  // stale values, which b < rem masks
-  // one loop level, the drain inside it: the accumulators change only on the
-  // drain path (a loop nest made the compiler copy them every filter step)
-  int cnt = A.cnt, head = A.head;
-  while (__any(j < j1)) {
-    const int rem = j1 - j;   // sources left in the run (<= 0: none)
-    if (j < j1) {
-      // a 32-bit byte offset from the uniform array bases
-      const unsigned off = (unsigned)j * 4u;
-      X = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf) + off));
-      Y = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf1) + off));
-      Z = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf2) + off));
-    }
-    const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
-    const int ent0 = (j << 8) | bits;
-#pragma unroll
-    for (int b = 0; b < kBatchF; ++b) {
-      const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
-      const float r2 = dxv * dxv + dyv * dyv + dzv * dzv;
-      const bool hit = (b < rem) & (r2 < pc.a2f);
-      qlane[kWaveQ * ((head + cnt) & (kQueueF - 1))] = ent0 + (b << 8);
-      cnt += hit ? 1 : 0;
-    }
-    // finished lanes advance too: rem <= 0 masks them and the loads stay
-    // guarded by j < j1 (j grows by at most 4 per step of the slowest lane)
-    j += kBatchF;
+  int cnt = A.cnt;
+  while (__any(r.more())) {
+    float4 X = any4(), Y = any4(), Z = any4();
+    if (r.more()) r.load(f, X, Y, Z);
+    cnt = r.test(X, Y, Z, pc.a2f, qlane, cnt);
     if (__builtin_expect(__any(cnt > kQueueF - kBatchF), 0)) {
       A.cnt = cnt;
       pair_drain_f32<K, R, LB>(queue, kDrainF, lane, L, xr, xif, sig, pc, A, rp, B);
       cnt = A.cnt;
-      head = A.head;
     }
   }
   A.cnt = cnt;
@@ -807,7 +890,7 @@ struct TargetF {
 };
 
 template <bool LB>
-__device__ __forceinline__ TargetF pair_target_f32(const PairArgsF& ar, int blk) {
+__device__ __forceinline__ TargetF pair_target_f32(const PairArgsF& ar, int blk, const float4* shift) {
   TargetF t;
   const CellGeom& g = ar.g;
   t.lane = threadIdx.x & (kWaveQ - 1);
@@ -819,92 +902,31 @@ __device__ __forceinline__ TargetF pair_target_f32(const PairArgsF& ar, int blk)
   t.cx = c % g.nc[0];
   t.cy = (c / g.nc[0]) % g.nc[1];
   t.cz = c / (g.nc[0] * g.nc[1]);
-  t.L = PairLaneF{t.xi.x, t.xi.y, t.xi.z, (float)t.cx, (float)g.nc[0],
-                  t.active ? ((t.sc << 8) | entry_bits(0, 0, 0)) : -1, t.sc, LB ? ar.sig[t.sc] : 0.0f, ar.xf[t.sc]};
+  t.L = PairLaneF{t.xi.x, t.xi.y, t.xi.z, (float)t.cx,
+                  t.active ? (t.sc | entry_bits(0, 0, 0)) : -1, t.sc | entry_bits(0, 0, 0), shift,
+                  LB ? ar.sig[t.sc] : 0.0f, ar.xf[t.sc]};
   return t;
-}
-
-// The two runs [j0, j1), [k0, k1) of one row of cells (x images ix1, ix2) that
-// a target's cutoff sphere can reach; empty for an idle lane.
-struct RowRuns {
-  int j0, j1, ix1, k0, k1, ix2;
-};
-
-// Rows are chosen and trimmed in the target's cell-relative FP32 coordinates.
-// The gaps are shrunk and the reach grown by margins (1e-5 of a cell, 2e-5 of
-// the cutoff) far above their FP32 rounding (~1e-7), so no cell that holds a
-// source inside the cutoff is ever skipped; mg, the skin margin of neighbour
-// reuse (atoms may sit that far outside their cells), does the same.
-// tz, ty: the row's wrapped cell coordinates.
-__device__ __forceinline__ float row_gap_f32(int d, float w, float x, float mg) {
-  return d == 0 ? 0.0f
-                : fmaxf(0.0f, (d > 0 ? fmaf((float)d, w, -x) : fmaf((float)(-d - 1), w, x)) - 1e-5f * w - mg);
-}
-
-__device__ __forceinline__ RowRuns row_runs_f32(const PairArgsF& ar, const TargetF& t, float rem, float inv_wx, float mg,
-                                                int row) {
-  const PairConstF& pc = ar.pc;
-  const float reach = 1.0f + 2e-5f;
-  const int nc0 = ar.g.nc[0];
-  int clo = 0, chi = -1;
-  if (t.active && rem > 0.0f) {
-    // hardware square root (about 1 ulp): far inside the margin
-    const float rx = fmaf(__builtin_amdgcn_sqrtf(rem), reach, 1e-5f * pc.w[0] + mg);
-    clo = t.cx + max(-2, (int)floorf((t.xi.x - rx) * inv_wx));
-    chi = t.cx + min(2, (int)floorf((t.xi.x + rx) * inv_wx));
-  }
-  int lo1 = clo, hi1 = chi, lo2 = 0, hi2 = -1;
-  RowRuns r{0, 0, 0, 0, 0, 0};
-  if (clo < 0) {
-    lo1 = clo + nc0; hi1 = nc0 - 1; r.ix1 = -1;
-    lo2 = 0; hi2 = chi; r.ix2 = 0;
-  } else if (chi >= nc0) {
-    lo1 = clo; hi1 = nc0 - 1; r.ix1 = 0;
-    lo2 = 0; hi2 = chi - nc0; r.ix2 = 1;
-  }
-  if (lo1 <= hi1) {
-    r.j0 = at32(ar.cstart, row + lo1);
-    r.j1 = at32(ar.cstart, row + hi1 + 1);
-  }
-  if (lo2 <= hi2) {
-    r.k0 = at32(ar.cstart, row + lo2);
-    r.k1 = at32(ar.cstart, row + hi2 + 1);
-  }
-  return r;
 }
 
 // One wave's scan of all rows of its targets, into A and B.
 template <int K, bool R, bool LB>
 __device__ __forceinline__ void pair_rows_f32(const PairArgsF& ar, const TargetF& t, int* queue, PairAccM& A, RepAcc& B) {
   const PairConstF& pc = ar.pc;
-  const CellGeom& g = ar.g;
-  const float a2m = pc.a2 * (1.0f + 2e-5f);
-  const float inv_wx = 1.0f / pc.w[0];
-  const float mg = (float)g.margin;
-  const int nc0 = g.nc[0], nc1 = g.nc[1], nc2 = g.nc[2];
-  // the candidate registers of the scans, carried from run to run
-  float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X;
-  for (int dz = -2; dz <= 2; ++dz) {
-    const int uz = t.cz + dz;
-    const int tz = uz < 0 ? uz + nc2 : (uz >= nc2 ? uz - nc2 : uz);
-    const float gz = row_gap_f32(dz, pc.w[2], t.xi.z, mg);
-    const float rem_z = a2m - gz * gz;
-    const int rowz = tz * nc1;
-    int ty = t.cy - 2 < 0 ? t.cy - 2 + nc1 : t.cy - 2;
-    for (int dy = -2; dy <= 2; ++dy) {
-      const float gy = row_gap_f32(dy, pc.w[1], t.xi.y, mg);
-      const RowRuns r = row_runs_f32(ar, t, rem_z - gy * gy, inv_wx, mg, (rowz + ty) * nc0);
-      ty = ty + 1 == nc1 ? 0 : ty + 1;
-      // the second run (across the periodic edge) is empty for most waves:
-      // its set-up is skipped unless some lane has one
-      if (__any(r.j0 < r.j1))
-        pair_scan_f32<K, R, LB>(r.j0, r.j1, r.ix1, dy, dz, queue, t.lane, t.L, ar.xr, ar.xf, ar.xf_stride, ar.xif,
-                                ar.sig, pc, A, ar.rep, B, X, Y, Z);
-      if (__any(r.k0 < r.k1))
-        pair_scan_f32<K, R, LB>(r.k0, r.k1, r.ix2, dy, dz, queue, t.lane, t.L, ar.xr, ar.xf, ar.xf_stride, ar.xif,
-                                ar.sig, pc, A, ar.rep, B, X, Y, Z);
-    }
-  }
+  const FilterRows f(ar.xf, ar.xf_stride);
+  const RowTrim w(ar.cstart, ar.g, pc.w, pc.a2);
+  walk_rows(w, RowSpan<1>(), t.cx, t.cy, t.cz, t.xi.x, t.xi.y, t.xi.z, t.active,
+            [&](const RowRuns& r, int dz, int dy, int, int) {
+    // the second run (across the periodic edge) is empty for most waves: its
+    // set-up is skipped unless some lane has one
+    auto scan = [&](int j0, int j1, int ix) {
+      if (!__any(j0 < j1)) return;
+      const FilterRun<0> run(j0, j1, fmaf((float)-ix, pc.L[0], t.L.xa), fmaf((float)-dy, pc.w[1], t.L.yy),
+                             fmaf((float)-dz, pc.w[2], t.L.zz), entry_bits(ix, dy, dz));
+      pair_scan_f32<K, R, LB>(run, queue, t.lane, t.L, ar.xr, f, ar.xif, ar.sig, pc, A, ar.rep, B);
+    };
+    scan(r.j0, r.j1, r.ix1);
+    scan(r.k0, r.k1, r.ix2);
+  });
   pair_drain_f32<K, R, LB>(queue, kQueueF, t.lane, t.L, ar.xr, ar.xif, ar.sig, pc, A, ar.rep, B);
 }
 
@@ -914,10 +936,10 @@ struct PairTrimF32 {
   static constexpr int kThreads = kWaveQ;
   static __device__ void run(const Args& ar, int blk) {
     __shared__ int queue[kQueueF * kWaveQ];
-    __shared__ double sums[kSumSlots];
-    const TargetF t = pair_target_f32<LB>(ar, blk);
-    for (int k = 0; k < kSumSlots / kWaveQ; ++k) sums[k * kWaveQ + t.lane] = 0.0;
-    PairAccM A{LaneSums{sums + t.lane}, 0, 0};
+    __shared__ float4 shift[kShifts];
+    const TargetF t = pair_target_f32<LB>(ar, blk, shift);
+    fill_shifts(shift, t.lane, ar.g, ar.pc);
+    PairAccM A{{0.0, 0.0, 0.0, 0.0}, 0};
     RepAcc B{{0.0, 0.0, 0.0, 0.0}};
     pair_rows_f32<K, R, LB>(ar, t, queue, A, B);
     if (t.active) {
@@ -960,21 +982,19 @@ struct PairSplitF32 {
     __shared__ __attribute__((aligned(16))) unsigned short list[kSplitHits * W];
     __shared__ unsigned short hits[NS * W];
     __shared__ int steps[NS];                   // filter steps of each wave, -1: too many
-    const TargetF t = pair_target_f32<LB>(ar, blk);
+    __shared__ float4 shift[kShifts];
+    const TargetF t = pair_target_f32<LB>(ar, blk, shift);
     const int lane = t.lane;
     const RowSpan<NS> span;
     const int wv = span.wv;
+    if (wv == 0) fill_shifts(shift, lane, ar.g, ar.pc);   // read after the barrier below
     const PairConstF& pc = ar.pc;
     const PairRep& rp = ar.rep;
     // ---- filter
     {
       const CellGeom& g = ar.g;
-      const float a2m = pc.a2 * (1.0f + 2e-5f);
-      const float inv_wx = 1.0f / pc.w[0];
-      const float mg = (float)g.margin;
-      const float* const xf0 = ar.xf;
-      const float* const xf1 = xf0 + ar.xf_stride;
-      const float* const xf2 = xf1 + ar.xf_stride;
+      const RowTrim trim(ar.cstart, g, pc.w, pc.a2);
+      const FilterRows f(ar.xf, ar.xf_stride);
       int ns = 0, nh = 0;
       // the cell ranges of all rows first, their loads in flight together
       constexpr int kRows = (25 + NS - 1) / NS;
@@ -986,9 +1006,9 @@ struct PairSplitF32 {
         int tz = t.cz + dz, ty = t.cy + dy;
         tz = tz < 0 ? tz + g.nc[2] : (tz >= g.nc[2] ? tz - g.nc[2] : tz);
         ty = ty < 0 ? ty + g.nc[1] : (ty >= g.nc[1] ? ty - g.nc[1] : ty);
-        const float gz = row_gap_f32(dz, pc.w[2], t.xi.z, mg), gy = row_gap_f32(dy, pc.w[1], t.xi.y, mg);
-        const float rem = r < span.r1 ? (a2m - gz * gz) - gy * gy : 0.0f;
-        rr[u] = row_runs_f32(ar, t, rem, inv_wx, mg, (tz * g.nc[1] + ty) * g.nc[0]);
+        const float gz = trim.gap(2, dz, t.xi.z), gy = trim.gap(1, dy, t.xi.y);
+        const float rem = r < span.r1 ? (trim.a2m - gz * gz) - gy * gy : 0.0f;
+        rr[u] = trim.runs(t.cx, t.xi.x, t.active, rem, (tz * g.nc[1] + ty) * g.nc[0]);
       }
 #pragma unroll
       for (int u = 0; u < kRows; ++u) {
@@ -1002,15 +1022,15 @@ struct PairSplitF32 {
           const int j1 = h ? rr[u].k1 : rr[u].j1, ix = h ? rr[u].ix2 : rr[u].ix1;
           if (!__any(j < j1)) continue;
           const float ax = fmaf((float)-ix, pc.L[0], t.L.xa);
-          first[(2 * r + h) * W + lane] = (j << 8) | entry_bits(ix, dy, dz);
+          first[(2 * r + h) * W + lane] = j | entry_bits(ix, dy, dz);
           // the next step's candidates are loaded before this step's are used
           float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X, Xn = X, Yn = X, Zn = X;
           auto load = [&](int i) {
             if (i < j1) {
               const unsigned off = (unsigned)i * 4u;
-              Xn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf0) + off));
-              Yn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf1) + off));
-              Zn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(xf2) + off));
+              Xn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.x) + (unsigned)off));
+              Yn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.y) + (unsigned)off));
+              Zn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.z) + (unsigned)off));
             }
           };
           load(j);
@@ -1029,7 +1049,7 @@ struct PairSplitF32 {
 #pragma unroll
             for (int b = 0; b < kBatchF; ++b) {
               const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
-              const float r2 = dxv * dxv + dyv * dyv + dzv * dzv;
+              const float r2 = fmaf(dzv, dzv, fmaf(dxv, dxv, dyv * dyv));
               m |= ((b < rem) & (r2 < pc.a2f)) ? 1 << b : 0;
             }
             mask[(wv * kSplitSteps + ns) * W + lane] = (unsigned char)m;
@@ -1056,9 +1076,7 @@ struct PairSplitF32 {
     if (few < 0 || __any(total > kSplitHits)) {   // the same in every wave
       if (wv == 0) {
         int* const queue = reinterpret_cast<int*>(list);
-        double* const sums = reinterpret_cast<double*>(list) + kQueueF * W / 2;
-        for (int c = 0; c < 4; ++c) sums[c * W + lane] = 0.0;
-        PairAccM A{LaneSums{sums + lane}, 0, 0};
+        PairAccM A{{0.0, 0.0, 0.0, 0.0}, 0};
         RepAcc B{{0.0, 0.0, 0.0, 0.0}};
         pair_rows_f32<K, R, LB>(ar, t, queue, A, B);
 #pragma unroll
@@ -1085,7 +1103,7 @@ struct PairSplitF32 {
         constexpr int kAhead = 4;
         for (int u0 = 0; __any(u0 < m); u0 += kAhead) {
           bool ok[kAhead];
-          int ent[kAhead], src[kAhead];
+          int ent[kAhead];
           float4 xj[kAhead];
           float wsrc[kAhead];
 #pragma unroll
@@ -1094,22 +1112,17 @@ struct PairSplitF32 {
             if (u0 + u < m) {
               const int e = list[(pos + u0 + u) * W + lane];
               const int pl = place[e >> 2];
-              q = first[(pl & 63) * W + lane] + ((((pl >> 6) << 2) + (e & 3)) << 8);
+              q = first[(pl & 63) * W + lane] + ((pl >> 6) << 2) + (e & 3);
             }
             // idle slots (and the target itself): as in pair_drain_f32
             ok[u] = q != t.L.self_ent;
-            ent[u] = ok[u] ? q : 0;
-            src[u] = ok[u] ? (int)((unsigned)q >> 8) : t.L.safe_j;
-            xj[u] = make_float4(t.L.xx + pc.w[0], t.L.yy, t.L.zz, t.L.cxf);
-            wsrc[u] = 0.0f;
-            if (ok[u]) {
-              xj[u] = at32(ar.xr, src[u]);
-              wsrc[u] = at32(ar.xif, src[u]);
-            }
+            ent[u] = ok[u] ? q : t.L.safe_ent;
+            xj[u] = at24(ar.xr, ent[u]);
+            wsrc[u] = at24(ar.xif, ent[u]);
           }
 #pragma unroll
           for (int u = 0; u < kAhead; ++u)
-            pair_term_f32<K, R, LB>(ok[u], ent[u], src[u], xj[u], wsrc[u], t.L, ar.sig, pc, rp, D);
+            pair_term_f32<K, R, LB>(ok[u], ent[u], xj[u], ok[u] ? wsrc[u] : 0.0f, t.L, ar.sig, pc, rp, D);
         }
 #pragma unroll
         for (int c = 0; c < (R ? 8 : 4); ++c) sum[c] += (double)D.s[c];
@@ -1172,7 +1185,9 @@ float filter_a2(const mls_plan_s* P) {
 }
 
 PairConst pair_const(const mls_plan_s* P) {
-  PairConst pc{P->a2, P->inv_a2, P->inv_a6, P->inv_a8, {}, {}, filter_a2(P), {}, {}};
+  PairConst pc{P->a2, P->inv_a2, P->inv_a6, P->inv_a8, {}, {}, filter_a2(P), {}, {},
+               {-15.0 / 8.0 * P->inv_a6, 5.0 / 4.0 * P->inv_a6, -3.0 / 8.0 * P->inv_a6, -9.0 * P->inv_a8,
+                15.0 * P->inv_a8}};
   for (int j = 0; j < 5; ++j) pc.gc[j] = P->gamma_c[j];
   for (int j = 0; j < 4; ++j) pc.gq[j] = 12.0 * (j + 1) * P->gamma_c[j + 1];
   for (int d = 0; d < 3; ++d) {
@@ -1195,17 +1210,17 @@ PairConstF pair_const_f(const mls_plan_s* P) {
 
 int pair_variant(const mls_plan_s* P) { return P->continuity == 2 ? 2 : 0; }
 
-// Waves per 64 targets.  One wave walks its 25 rows in about 100 us whatever
+// Waves per 64 targets.  One wave walks its 25 rows in about 95 us whatever
 // the number of atoms (dependent cell-range and candidate loads), so a launch
-// of fewer waves than the chip holds (16 per CU in FP64, 26 in FP32) is bound
+// of fewer waves than the chip holds (20 per CU in FP64, 28 in FP32) is bound
 // by that chain; dealing the rows to more waves shortens it.  Pair kernel
 // alone with 1 / 2 / 4 / 8 waves (us, FP64; cube at density 0.8, a = 3):
-// 1000 atoms 101 / 63 / 38 / 24, 32,000 atoms 106 / 66 / 42 / 32, 10^5 atoms
-// 119 / 82 / 83 / 85, 250,000 atoms 164 / 162 / 167 / 180, 10^6 atoms 516 /
-// 543 / 577 / 636 (the filter steps of a row are set by its slowest lane
+// 1000 atoms 95 / 60 / 36 / 24, 32,000 atoms 99 / 63 / 41 / 31, 10^5 atoms
+// 113 / 80 / 82 / 86, 250,000 atoms 161 / 155 / 161 / 176, 10^6 atoms 461 /
+// 473 / 538 / 606 (the filter steps of a row are set by its slowest lane
 // either way; what grows is the set-up): hence at most kPairSlots waves.
 // Beside the grid chain two waves at most: the chain's kernels then find free
-// slots (evaluation of 64,000 atoms, FP64: 164 / 140 / 167 / 160 us).
+// slots (evaluation of 64,000 atoms, FP64: 155 / 128 / 135 / 135 us).
 int pair_split(int64_t groups, bool alone) {
   for (int ns = alone ? 8 : 2; ns > 1; ns /= 2)
     if (groups * ns <= kPairSlots) return ns;
