@@ -585,6 +585,7 @@ struct mls_plan_s {
   int* d_bmax = nullptr;           // scan block maxima
   bool pair_fast = false;          // half-cutoff cells with per-atom row trimming
   int pair_after = 1;              // concurrent mode: grid-chain stages submitted before the local part
+  int cus = 0;                     // compute units of the device
   int pair_blocks = 0;             // > 0: the trimmed pair kernels run persistent with this many blocks
   // coarse points up to which restriction and prolongation use the forms
   // with a group of lanes per coarse point

@@ -1227,10 +1227,28 @@ int pair_split(int64_t groups, bool alone) {
   return 1;
 }
 
+// Beside the grid chain the FP32 kernel holds only so many waves of a CU and
+// walks its groups with them: a grid of all groups takes every slot that falls
+// free, and the anterpolation submitted before it, whose blocks want 22 KB of
+// LDS each, got through only as the pair kernel ended (59 us alone, 420 us
+// beside it), with the rest of the chain after that.  Evaluation, all slots /
+// 20 waves (us): 310,000 atoms 289 / 288, 500,000 390 / 363, 800,000 557 / 508,
+// 10^6 660 / 619, 2,000,000 1194 / 1199; 16 waves 312 / 369 / 558 / 654 / 1274.
+// The seven chains of Lorentz-Berthelot mixing want more room, all / 14 waves:
+// 310,000 574 / 545, 500,000 716 / 659, 800,000 1087 / 972, 1,200,000 2039 /
+// 1920; 20 waves 579 / 682 / 1046 / 2017.  The FP64 kernel leaves no slots worth
+// having at 20 waves, and fewer cost it what they give the chain (10^6 atoms,
+// all / 18 / 16: 734 / 734 / 762).  With the repulsion (R) a CU holds 20 anyway.
+constexpr int kBesideWaves = 20, kBesideSeven = 14;
+
 template <int K, bool R, bool LB>
-hipError_t launch_split_f32(const mls_plan_s* P, const PairArgsF& a, int groups, hipStream_t s) {
-  if (P->pair_blocks <= 0 && groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
-  return launch_persist<PairTrimF32<K, R, LB>>(a, groups, P->pair_blocks, s);
+hipError_t launch_split_f32(const mls_plan_s* P, const PairArgsF& a, int groups, bool alone, hipStream_t s) {
+  int blocks = P->pair_blocks;
+  if (blocks <= 0) {
+    if (groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
+    if (!alone && !R) blocks = P->cus * (LB ? kBesideSeven : kBesideWaves);
+  }
+  return launch_persist<PairTrimF32<K, R, LB>>(a, groups, blocks, s);
 }
 
 template <int K, bool LB, bool R>
@@ -1252,11 +1270,11 @@ hipError_t launch_pair_k(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep
                 P->d_floc};
     a.xf = P->d_xf;
     a.xf_stride = P->xf_stride;
-    if (!rep) return launch_split_f32<K, false, false>(P, a, waves, s);
+    if (!rep) return launch_split_f32<K, false, false>(P, a, waves, alone, s);
     a.rep = *rep;
     *fused = true;
     P->rep_nb = waves;
-    return launch_split_f32<K, true, false>(P, a, waves, s);
+    return launch_split_f32<K, true, false>(P, a, waves, alone, s);
   }
   PairArgs a{P->d_xs, P->d_cell_s, P->d_cell_start, n, g, pair_const(P), P->d_e0, P->d_floc, nullptr};
   a.xf = P->d_xf;
@@ -1281,7 +1299,7 @@ hipError_t launch_pair_lb_k(mls_plan_s* P, int n, hipStream_t s, bool alone) {
     a.sig = P->d_sigf;
     a.xf = P->d_xf;
     a.xf_stride = P->xf_stride;
-    return launch_split_f32<K, false, true>(P, a, (n + kWaveQ - 1) / kWaveQ, s);
+    return launch_split_f32<K, false, true>(P, a, (n + kWaveQ - 1) / kWaveQ, alone, s);
   }
   PairArgs a{P->d_xs, P->d_cell_s, P->d_cell_start, n, P->cg, pair_const(P), P->d_e0, P->d_floc, P->d_sig};
   a.xf = P->d_xf;
