@@ -209,7 +209,7 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   HIP_TRY(launch_sum_xi(P, ni, g), "sum of xi");
   HIP_TRY(mark(1 + MLS_T_ANTERP), "timing event");
   if (after == 1 && (st = pair()) != MLS_OK) return st;
-  HIP_TRY(launch_restrictions(P, g), "restriction");
+  HIP_TRY(launch_restrictions(P, g, !ev), "restriction");
   HIP_TRY(mark(1 + MLS_T_RESTRICT), "timing event");
   if (after == 2 && (st = pair()) != MLS_OK) return st;
   // (one launch; two with per-stage timing)
@@ -262,7 +262,7 @@ hipError_t evaluate_split(mls_plan_t P, int n, const double* pos, const double* 
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
-  if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
+  if ((e = launch_restrictions(P, g, true)) != hipSuccess) return e;
   if ((e = launch_stencils(P, n, g, 0, true)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g)) != hipSuccess) return e;
   if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
@@ -320,7 +320,7 @@ hipError_t evaluate_split3(mls_plan_s* P, int n, const double* pos, const double
   bool fused = false;
   if ((e = launch_pair(P, n, s, &prep, &fused, g == s)) != hipSuccess) return e;
   if (!fused && (e = launch_repulsion(P, n, rep.rc, s)) != hipSuccess) return e;
-  if ((e = launch_restrictions(P, g)) != hipSuccess) return e;
+  if ((e = launch_restrictions(P, g, true)) != hipSuccess) return e;
   if ((e = launch_stencils(P, n, g, 0, true)) != hipSuccess) return e;
   if ((e = launch_prolongations(P, g, two)) != hipSuccess) return e;
   if (g != s && (e = hipEventRecord(P->ev_join, g)) != hipSuccess) return e;
@@ -600,7 +600,7 @@ mls_status mls_evaluate_lb(mls_plan_t P, int64_t n, const double* pos, const dou
   HIP_TRY(launch_anterpolate(P, ni, g), "anterpolation");
   // submitted after the anterpolation, as in evaluate_geometric
   HIP_TRY(launch_pair_lb(P, ni, s, g == s), "pair kernel");
-  HIP_TRY(launch_restrictions(P, g), "restriction");
+  HIP_TRY(launch_restrictions(P, g, true), "restriction");
   HIP_TRY(launch_stencils(P, ni, g, 0, true), "level stencils");
   HIP_TRY(launch_prolongations(P, g), "prolongation");
   if (g != s) {

@@ -410,10 +410,10 @@ struct Restrict {
 // M - P/2 + 1 .. M + P/2 per dimension (the even one uses M alone), so the
 // thread walks those P z-planes, interpolates each plane in x then y, and
 // adds it into the 8 outputs.
-template <int P, bool ROLL = false>
-__device__ __forceinline__ void prolong_at(const TransferArgs& a, int M) {
-    const GridDims& c = a.gs;
-    const GridDims& f = a.gd;
+// src: the coarse values; store(J, v0, v1): the fine values at J and J + 1.
+template <int P, bool ROLL, class Store>
+__device__ __forceinline__ void prolong_at(const GridDims& c, const GridDims& f, const double* src, int M,
+                                           Store&& store) {
     const int X = M % c.n[0], Y = (M / c.n[0]) % c.n[1], Z = M / (c.n[0] * c.n[1]);
     constexpr int H = P / 2;
     double w[P];   // weight of coarse M - H + 1 + t for the odd fine point 2M + 1
@@ -449,7 +449,7 @@ __device__ __forceinline__ void prolong_at(const TransferArgs& a, int M) {
       double ye[2] = {0.0, 0.0}, yo[2] = {0.0, 0.0};   // y even / odd, [x parity]
 #pragma unroll
       for (int ty = 0; ty < P; ++ty) {
-        const double* row = a.src + ((size_t)izr[0] * c.n[1] + iy[ty]) * c.n[0];
+        const double* row = src + ((size_t)izr[0] * c.n[1] + iy[ty]) * c.n[0];
         double v[P];
 #pragma unroll
         for (int tx = 0; tx < P; ++tx) v[tx] = row[ix[tx]];
@@ -485,8 +485,7 @@ __device__ __forceinline__ void prolong_at(const TransferArgs& a, int M) {
 #pragma unroll
       for (int py = 0; py < 2; ++py) {
         const size_t J = ((size_t)(2 * Z + pz) * f.n[1] + (2 * Y + py)) * f.n[0] + 2 * X;
-        a.dst[J] = (a.add ? a.add[J] : 0.0) + acc[pz][py][0];
-        a.dst[J + 1] = (a.add ? a.add[J + 1] : 0.0) + acc[pz][py][1];
+        store(J, acc[pz][py][0], acc[pz][py][1]);
       }
 }
 
@@ -496,7 +495,55 @@ struct Prolong {
   static constexpr int kThreads = kBlock;
   static __device__ void run(const Args& a, int blk) {
     const int M = blk * kBlock + threadIdx.x;
-    if (M < a.gs.size) prolong_at<P, ROLL>(a, M);
+    if (M >= a.gs.size) return;
+    prolong_at<P, ROLL>(a.gs, a.gd, a.src, M, [&](size_t J, double v0, double v1) {
+      a.dst[J] = (a.add ? a.add[J] : 0.0) + v0;
+      a.dst[J + 1] = (a.add ? a.add[J + 1] : 0.0) + v1;
+    });
+  }
+};
+
+// The prolongations between the levels of at most kTailPoints points and the
+// first step beyond them, in one launch: a prolongation of a few thousand
+// points is all latency (5 to 7 us each, p = 6: 12 to 16), so every block works
+// out the small levels for itself in LDS, the same sums as Prolong's, and then
+// does its 256 coarse points of the last step.  With the last restriction in the
+// stencils' launch (stencil.hip), an evaluation of 32000 atoms in a slab goes
+// from 119.4 to 111.6 us, of 60000 with p = 6 from 284 to 265 us.
+constexpr int kTailPoints = 4096;
+constexpr int kTailLds = kTailPoints * 8 / 7 + 8;   // a level has eight times its coarser one's points
+
+template <int P>
+struct ProlongTail {
+  using Args = ProlongTailArgs;
+  static constexpr int kThreads = kBlock;
+  static __device__ void run(const Args& a, int blk) {
+    __shared__ double lds[kTailLds];
+    double* cur = lds;
+    for (int i = threadIdx.x; i < a.g[0].size; i += kBlock) cur[i] = a.E[0][i];
+    __syncthreads();
+    const int nblk = (a.g[a.nl - 1].size + kBlock - 1) / kBlock;
+    for (int k = 1; k < a.nl; ++k) {
+      const GridDims &c = a.g[k - 1], &f = a.g[k];
+      double* const next = cur + c.size;
+      const double* const add = a.add[k];
+      for (int M = threadIdx.x; M < c.size; M += kBlock)
+        prolong_at<P, true>(c, f, cur, M, [&](size_t J, double v0, double v1) {
+          next[J] = add[J] + v0;
+          next[J + 1] = add[J + 1] + v1;
+        });
+      __syncthreads();
+      for (int i = blk * kBlock + threadIdx.x; i < f.size; i += nblk * kBlock) a.E[k][i] = next[i];
+      cur = next;
+    }
+    const int M = blk * kBlock + threadIdx.x;
+    if (M >= a.g[a.nl - 1].size) return;
+    const double* const add = a.add[a.nl];
+    double* const dst = a.E[a.nl];
+    prolong_at<P, true>(a.g[a.nl - 1], a.g[a.nl], cur, M, [&](size_t J, double v0, double v1) {
+      dst[J] = (add ? add[J] : 0.0) + v0;
+      dst[J + 1] = (add ? add[J + 1] : 0.0) + v1;
+    });
   }
 };
 
@@ -1384,6 +1431,13 @@ hipError_t launch_restrict(mls_plan_s* Pl, const TransferArgs* a, int n, hipStre
 }
 
 template <int P>
+hipError_t launch_tails(const ProlongTailArgs* a, int n, int blocks, hipStream_t s) {
+  ChainArgs<ProlongTail<P>> c;
+  for (int k = 0; k < n; ++k) c.add(a[k]);
+  return launch_chains(c, blocks, s);
+}
+
+template <int P>
 hipError_t launch_prolong(mls_plan_s* Pl, const TransferArgs* a, int n, hipStream_t s) {
   const int size = a[0].gs.size;
   if (size <= Pl->split_prolong)
@@ -1400,9 +1454,11 @@ hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s) {
   return mixed ? launch_anterpolate_k<6, float>(P, n, s) : launch_anterpolate_k<6, double>(P, n, s);
 }
 
-hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s) {
+// joint: launch_stencils follows with the coarsest level in its launch.
+hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s, bool joint) {
   const ChainSet cs = chains(P);
-  for (int k = 2; k <= P->levels; ++k) {
+  const int last = joint && coarsest_restricts(P) ? P->levels - 1 : P->levels;
+  for (int k = 2; k <= last; ++k) {
     TransferArgs a[kLbVectors];
     for (int v = 0; v < cs.n; ++v) {
       const Level &F = (*cs.lv[v])[k - 2], &C = (*cs.lv[v])[k - 1];
@@ -1416,7 +1472,28 @@ hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s) {
 
 hipError_t launch_prolongations(mls_plan_s* P, hipStream_t s, bool drop_e1) {
   const ChainSet cs = chains(P);
-  for (int k = P->levels - 1; k >= 1; --k) {
+  int k = P->levels - 1;
+  // the small levels; a forced group-of-lanes form keeps its launches
+  int m = P->levels;   // the finest level held in LDS
+  while (m > 2 && P->levels - m < kTailLevels - 1 && P->lv[m - 2].g.size <= kTailPoints) --m;
+  if (k >= 1 && P->split_prolong == 0 && P->lv[m - 1].g.size <= kTailPoints) {
+    ProlongTailArgs a[kLbVectors];
+    for (int v = 0; v < cs.n; ++v) {
+      a[v].nl = P->levels - m + 1;
+      for (int i = 0; i <= a[v].nl; ++i) {
+        const int level = P->levels - i;
+        const Level& L = (*cs.lv[v])[level - 1];
+        a[v].g[i] = L.g;
+        a[v].add[i] = level == 1 && drop_e1 ? nullptr : L.e;
+        a[v].E[i] = L.E;
+      }
+    }
+    const int blocks = nblocks(P->lv[m - 1].g.size, kBlock);
+    const hipError_t e = P->order == 4 ? launch_tails<4>(a, cs.n, blocks, s) : launch_tails<6>(a, cs.n, blocks, s);
+    if (e != hipSuccess) return e;
+    k = m - 2;
+  }
+  for (; k >= 1; --k) {
     TransferArgs a[kLbVectors];
     for (int v = 0; v < cs.n; ++v) {
       const Level &F = (*cs.lv[v])[k - 1], &C = (*cs.lv[v])[k];

@@ -278,6 +278,15 @@ struct TransferArgs {              // restriction (fine -> coarse) and prolongat
   gptr<const double> add;               // prolongation: e^k added to the interpolated values
   gptr<double> dst; GridDims gd;
 };
+// The coarse end of the prolongations: levels lv[0] (the coarsest) .. lv[nl - 1]
+// in LDS, written to their E as well, and the step from there to lv[nl].
+constexpr int kTailLevels = 6;
+struct ProlongTailArgs {
+  int nl;
+  GridDims g[kTailLevels + 1];
+  gptr<const double> add[kTailLevels + 1];
+  gptr<double> E[kTailLevels + 1];
+};
 struct InterpArgs {
   gptr<const double4> xs; gptr<const int> perm; int n; GridGeom gg; gptr<const double> E1; gptr<const double> e0;
   gptr<const double> floc; double cself; OutPtrs out; gptr<double> partial;
@@ -719,10 +728,12 @@ hipError_t launch_stencils(mls_plan_s* P, int n, hipStream_t s, int kmax = 0, bo
 // mixed precision: the stencils of n atoms take the partial sums of the charges
 // (launch_sum_xi and the sums of launch_lb_charges are then left out)
 bool stencil_adds_sum(const mls_plan_s* P, int64_t n);
+// the stencils' launch with the coarsest level does the last restriction too
+bool coarsest_restricts(const mls_plan_s* P);
 int stencil_path(const mls_plan_s* P);   // mls_stencil_path of the plan
 hipError_t launch_coarsest(mls_plan_s* P, hipStream_t s);
 // All restrictions (levels 2..l) and all prolongations (l-1..1) of an evaluation.
-hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s);
+hipError_t launch_restrictions(mls_plan_s* P, hipStream_t s, bool joint = false);
 // drop_e1: the last prolongation writes E^1 = prolongated E^2 without e^1
 // (the levels 2..l part of multiple time stepping per level)
 hipError_t launch_prolongations(mls_plan_s* P, hipStream_t s, bool drop_e1 = false);

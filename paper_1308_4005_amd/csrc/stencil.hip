@@ -191,12 +191,16 @@ __device__ __forceinline__ void coarsest_rows(const CoarsestArgs& a, int blk, do
   }
 }
 
+// have_q: the charges are already at the end of lds (coarsest_restrict)
 template <bool STAGED>
-__device__ __forceinline__ void coarsest_sums(const CoarsestArgs& a, int blk, double* lds) {
+__device__ __forceinline__ void coarsest_sums(const CoarsestArgs& a, int blk, double* lds, bool have_q = false) {
   const GridDims& g = a.g;
   double* const sk = lds;
-  double* const sq = lds + kCoarseLds;
-  if constexpr (STAGED) {
+  double* const sq = lds + (have_q ? 2 * kCoarseLds - g.size : kCoarseLds);
+  if (STAGED && have_q) {
+    for (int i = threadIdx.x; i < g.size; i += kCoarsestThreads) sk[i] = a.K[i];
+    __syncthreads();
+  } else if constexpr (STAGED) {
     constexpr int kPer = kCoarseLds / kCoarsestThreads;
     double vq[kPer], vk[kPer];
 #pragma unroll
@@ -287,17 +291,67 @@ struct StencilLaunch {
   int ncoarse;
   gptr<const double> K;  // coarsest level
   GridDims gc;
-  gptr<const double> qc[kLbVectors];
+  gptr<double> qc[kLbVectors];
   gptr<double> ec[kLbVectors];
+  // the last restriction, done by the coarsest level's blocks too (qf null: not)
+  GridDims gf;
+  int taps;              // odd offsets per side
+  double w[3];           // their weights
+  gptr<const double> qf[kLbVectors];
 };
+
+// The coarsest level's charges from the next finer level's, to the end of lds
+// (and, by the chain's first block, to memory): the restriction dimension by
+// dimension, in the order of sums of Restrict (grid.hip).  Every block of the
+// level does it for itself, up to kJointCoarse points: a third of the work of
+// the points' (p + 1)^3 taps, while the level stencils run, against a launch
+// of 4 us on the chain (p = 6: 8 us).
+constexpr int kJointCoarse = 2 * kCoarseLds / 7;   // x and y passes (4 + 2 values per point) and the points
+__device__ __forceinline__ double restrict_line(const StencilLaunch& L, const double* line, int stride, int n, int X) {
+  double s = line[(size_t)wrapi(2 * X, n) * stride];
+  for (int k = 0; k < L.taps; ++k) {
+    const int o = 2 * k + 1;
+    s += L.w[k] * line[(size_t)wrapi(2 * X - o, n) * stride];
+    s += L.w[k] * line[(size_t)wrapi(2 * X + o, n) * stride];
+  }
+  return s;
+}
+
+__device__ __forceinline__ void coarsest_restrict(const StencilLaunch& L, int c, int blk, double* lds) {
+  const GridDims &f = L.gf, &g = L.gc;
+  const int nx = g.n[0], ny = g.n[1], fx = f.n[0], fy = f.n[1], fz = f.n[2];
+  double* const tx = lds;                      // (nx, fy, fz)
+  double* const ty = lds + nx * fy * fz;       // (nx, ny, fz)
+  double* const sq = lds + 2 * kCoarseLds - g.size;
+  const double* const q = L.qf[c];
+  for (int i = threadIdx.x; i < nx * fy * fz; i += kCoarsestThreads) {
+    const int r = i / nx;
+    tx[i] = restrict_line(L, q + (size_t)r * fx, 1, fx, i - r * nx);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nx * ny * fz; i += kCoarsestThreads) {
+    const int r = i / nx, z = r / ny;
+    ty[i] = restrict_line(L, tx + z * fy * nx + (i - r * nx), nx, fy, r - z * ny);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < g.size; i += kCoarsestThreads) {
+    const int z = i / (nx * ny);
+    const double v = restrict_line(L, ty + (i - z * nx * ny), nx * ny, fz, z);
+    sq[i] = v;
+    if (blk == 0) L.qc[c][i] = v;
+  }
+  __syncthreads();   // tx and ty are free
+}
 
 // A block of the coarsest level: done here (true).
 __device__ __forceinline__ bool coarsest_block(const StencilLaunch& L, int b, double* lds) {
   const int nt = L.nchain * L.ntiles;
   if (b < nt) return false;
   const int c = (b - nt) / L.ncoarse, blk = (b - nt) - c * L.ncoarse;
-  const CoarsestArgs a{L.qc[c], L.gc, L.K, L.ec[c], 1, 0};
-  if (L.gc.size <= kCoarseLds) coarsest_sums<true>(a, blk, lds);
+  const CoarsestArgs a{(double*)L.qc[c], L.gc, L.K, L.ec[c], 1, 0};
+  const bool joint = L.qf[c] != nullptr;
+  if (joint) coarsest_restrict(L, c, blk, lds);
+  if (L.gc.size <= kCoarseLds) coarsest_sums<true>(a, blk, lds, joint);
   else coarsest_sums<false>(a, blk, lds);
   return true;
 }
@@ -813,9 +867,15 @@ int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts,
   L.K = P->d_Kl;
   L.gc = C.g;
   L.sum_rows = o.sum_rows;
+  const bool joint = o.coarsest && coarsest_restricts(P);
+  L.gf = P->lv[P->levels - 2].g;
+  const double w4[3] = {9.0 / 16.0, -1.0 / 16.0, 0.0}, w6[3] = {75.0 / 128.0, -25.0 / 256.0, 3.0 / 256.0};
+  L.taps = P->order / 2;
+  for (int k = 0; k < 3; ++k) L.w[k] = P->order == 4 ? w4[k] : w6[k];
   for (int v = 0; v < cs.n; ++v) {
     L.qc[v] = (*cs.lv[v])[P->levels - 1].q;
     L.ec[v] = (*cs.lv[v])[P->levels - 1].e;
+    L.qf[v] = joint ? (*cs.lv[v])[P->levels - 2].q : nullptr;
     L.sum[v] = o.sum_rows > 0 ? (cs.n == 1 ? P->d_partial : lb_partial_buf(P, v)) : cs.sum[v];
   }
   return (t + L.ncoarse) * cs.n;
@@ -904,6 +964,12 @@ constexpr int64_t kSumRows = 65536;
 
 bool stencil_adds_sum(const mls_plan_s* P, int64_t n) {
   return n > 0 && n + kSortedPad <= kSumRows && stencil_path(P) == MLS_STENCIL_TILE_F32;
+}
+
+bool coarsest_restricts(const mls_plan_s* P) {
+  const int path = stencil_path(P);
+  return P->levels >= 2 && P->lv[P->levels - 1].g.size <= kJointCoarse &&
+         (path == MLS_STENCIL_TILE_F32 || path == MLS_STENCIL_TILE_F64 || path == MLS_STENCIL_STREAM_F64);
 }
 
 hipError_t launch_stencils(mls_plan_s* P, int n, hipStream_t s, int kmax, bool coarsest) {
