@@ -302,7 +302,7 @@ mls_status build_phases(mls_batch_s* B) {
       if (c.P->levels <= k) continue;
       Level& F = (*c.lv)[k - 1];
       Level& C = (*c.lv)[k];
-      set_box(r, c.id, TransferArgs{F.q, F.g, nullptr, C.q, C.g}, nblk(C.g.size, 256));
+      set_box(r, c.id, TransferArgs{F.q, F.g, nullptr, C.q, C.g}, restrict_tiles(C.g));
     }
     hp.push_back(std::move(r));
   }

@@ -352,54 +352,66 @@ struct AnterpCollect {
 };
 
 // ------------------------------------------------------------ restriction
-// Per-dimension taps around fine index 2M: offsets 0, +-1, +-3 (, +-5).
+// Per-dimension taps around fine index 2M: offsets 0, +-1, +-3 (, +-5), the
+// weighted values added in that order.  A block takes a tile of coarse points,
+// dimension by dimension: the x taps from memory, for every fine row the tile
+// reaches, into LDS, then the y and z taps from there.  A thread per coarse point
+// with all its (p + 1)^3 loads was bound by the L1 (16 lines per wave and
+// load); this reads a fourth of them.  All restrictions of 10^6 atoms, p = 4:
+// 36.3 -> 28.6 us, p = 6: 75.7 -> 39.7.
 template <int P>
-__device__ __forceinline__ void restrict_at(const TransferArgs& a, int M) {
-    const GridDims& f = a.gs;
-    const GridDims& c = a.gd;
-    const int X = M % c.n[0], Y = (M / c.n[0]) % c.n[1], Z = M / (c.n[0] * c.n[1]);
-    constexpr int K = P + 1;  // 0, +-1, +-3, (+-5)
-    int ix[K], iy[K], iz[K];
-    double w[K];
-    w[0] = 1.0;
-    ix[0] = wrapi(2 * X, f.n[0]);
-    iy[0] = wrapi(2 * Y, f.n[1]);
-    iz[0] = wrapi(2 * Z, f.n[2]);
-#pragma unroll
-    for (int k = 0; k < P / 2; ++k) {
-      const int o = 2 * k + 1;
-      w[1 + 2 * k] = w[2 + 2 * k] = rp_weight_odd<P>(k);
-      ix[1 + 2 * k] = wrapi(2 * X - o, f.n[0]);
-      ix[2 + 2 * k] = wrapi(2 * X + o, f.n[0]);
-      iy[1 + 2 * k] = wrapi(2 * Y - o, f.n[1]);
-      iy[2 + 2 * k] = wrapi(2 * Y + o, f.n[1]);
-      iz[1 + 2 * k] = wrapi(2 * Z - o, f.n[2]);
-      iz[2 + 2 * k] = wrapi(2 * Z + o, f.n[2]);
-    }
-    double acc = 0.0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double sy = 0.0;
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        const double* row = a.src + ((size_t)iz[i] * f.n[1] + iy[j]) * f.n[0];
-        double sx = 0.0;
-#pragma unroll
-        for (int cc = 0; cc < K; ++cc) sx += w[cc] * row[ix[cc]];
-        sy += w[j] * sx;
-      }
-      acc += w[i] * sy;
-    }
-    a.dst[M] = acc;
-}
-
-template <int P>
-struct Restrict {
+struct RestrictTile {
   using Args = TransferArgs;
   static constexpr int kThreads = kBlock;
+  static constexpr int TX = kRestrictTile[0], TY = kRestrictTile[1], TZ = kRestrictTile[2];
+  static constexpr int H = P - 1;   // largest offset
+  static constexpr int WY = 2 * (TY - 1) + 2 * H + 1, WZ = 2 * (TZ - 1) + 2 * H + 1;
+  // taps around element c of a line in LDS
+  static __device__ __forceinline__ double line(const double* c, int stride) {
+    double s = *c;
+#pragma unroll
+    for (int k = 0; k < P / 2; ++k) {
+      s += rp_weight_odd<P>(k) * c[-(2 * k + 1) * stride];
+      s += rp_weight_odd<P>(k) * c[(2 * k + 1) * stride];
+    }
+    return s;
+  }
   static __device__ void run(const Args& a, int blk) {
-    const int M = blk * kBlock + threadIdx.x;
-    if (M < a.gd.size) restrict_at<P>(a, M);
+    __shared__ double t1[WZ * WY * TX], t2[WZ * TY * TX];
+    __shared__ int ix[TX * (P + 1)], iy[WY], iz[WZ];
+    const GridDims &f = a.gs, &c = a.gd;
+    const int bx = (c.n[0] + TX - 1) / TX, by = (c.n[1] + TY - 1) / TY;
+    const int X0 = blk % bx * TX, Y0 = blk / bx % by * TY, Z0 = blk / (bx * by) * TZ;
+    const int t = threadIdx.x;
+    if (t < TX * (P + 1)) {
+      const int k = t / TX, o = k == 0 ? 0 : (k & 1 ? -k : k - 1);   // 0, -1, +1, -3, +3, ...
+      ix[t] = wrapi(2 * (X0 + t % TX) + o, f.n[0]);
+    }
+    if (t < WY) iy[t] = wrapi(2 * Y0 - H + t, f.n[1]);
+    if (t < WZ) iz[t] = wrapi(2 * Z0 - H + t, f.n[2]);
+    __syncthreads();
+    const int X = t % TX;
+    int xo[P + 1];
+#pragma unroll
+    for (int k = 0; k <= P; ++k) xo[k] = ix[k * TX + X];
+    for (int r = t / TX; r < WZ * WY; r += kBlock / TX) {
+      const double* row = a.src + ((size_t)iz[r / WY] * f.n[1] + iy[r % WY]) * f.n[0];
+      double s = row[xo[0]];
+#pragma unroll
+      for (int k = 1; k <= P; ++k) s += rp_weight_odd<P>((k - 1) / 2) * row[xo[k]];
+      t1[r * TX + X] = s;
+    }
+    __syncthreads();
+    for (int i = t; i < WZ * TY * TX; i += kBlock) {
+      const int z = i / (TY * TX), Y = i / TX % TY;
+      t2[i] = line(t1 + (z * WY + 2 * Y + H) * TX + X, TX);
+    }
+    __syncthreads();
+    static_assert(TX * TY * TZ == kBlock, "one point per thread");
+    const int Y = t / TX % TY, Z = t / (TX * TY);
+    const double v = line(t2 + ((2 * Z + H) * TY + Y) * TX + X, TY * TX);
+    if (X0 + X < c.n[0] && Y0 + Y < c.n[1] && Z0 + Z < c.n[2])
+      a.dst[((size_t)(Z0 + Z) * c.n[1] + Y0 + Y) * c.n[0] + X0 + X] = v;
   }
 };
 
@@ -548,8 +560,8 @@ struct ProlongTail {
 };
 
 // Small levels: a grid transfer of a few thousand points has too few threads
-// to hide its loads (each thread of the forms above issues (p+1)^3 or p^3 of
-// them one after another), so there a group of lanes shares one coarse point.
+// to hide its loads (a tile's three passes, or p^3 loads of one thread, follow
+// each other), so there a group of lanes shares one coarse point.
 // Restriction: 8 lanes per coarse point split its (p+1)^2 (z, y) rows, each
 // lane sums its rows' x taps, and the group adds its partial sums (fixed
 // order).  Prolongation: one lane per z-plane of the coarse point's p^3
@@ -1424,10 +1436,14 @@ hipError_t launch_transfer(const TransferArgs* a, int n, int blocks, hipStream_t
 template <int P>
 hipError_t launch_restrict(mls_plan_s* Pl, const TransferArgs* a, int n, hipStream_t s) {
   const int size = a[0].gd.size;
-  // small levels: counted over the chains, which share the launch
-  if ((int64_t)size * n <= Pl->split_restrict)
+  // small levels: counted over the chains, which share the launch.  All
+  // restrictions, split / tiles (us), p = 4: level 2 of 32^3 points 24.5 / 25.8
+  // (of that 4 for three smaller levels in tiles), 40^3 31.1 / 26.6; p = 6: 22^3
+  // 17.8 / 20.3 (5 for the smaller ones), 24^3 28.8 / 27.2, 32^3 39.8 / 27.5.
+  const int64_t limit = Pl->split_restrict >= 0 ? Pl->split_restrict : P == 4 ? 24576 : 8192;
+  if ((int64_t)size * n <= limit)
     return launch_transfer<RestrictSplit<P>>(a, n, nblocks((int64_t)size * kRestrictGroup, kBlock), s);
-  return launch_transfer<Restrict<P>>(a, n, nblocks(size, kBlock), s);
+  return launch_transfer<RestrictTile<P>>(a, n, restrict_tiles(a[0].gd), s);
 }
 
 template <int P>
@@ -1608,7 +1624,7 @@ hipError_t launch_batched_grid(const BatchPhase& ph, hipStream_t s) {
                    : launch_batched_phase<AnterpTile<4, double>>(ph, s);
     case BK_ANT_COLLECT: return launch_batched_phase<AnterpCollect>(ph, s);
     case BK_RESTRICT:
-      return p6 ? launch_batched_phase<Restrict<6>>(ph, s) : launch_batched_phase<Restrict<4>>(ph, s);
+      return p6 ? launch_batched_phase<RestrictTile<6>>(ph, s) : launch_batched_phase<RestrictTile<4>>(ph, s);
     case BK_PROLONG:
       return p6 ? launch_batched_phase<Prolong<6, true>>(ph, s) : launch_batched_phase<Prolong<4, true>>(ph, s);
     case BK_INTERP:

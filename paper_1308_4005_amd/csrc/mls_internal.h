@@ -273,6 +273,13 @@ struct AnterpTileArgs {
   gptr<double> scratch; gptr<const double> charge; gptr<int> flags;
 };
 struct AnterpCollectArgs { AntTiles t; gptr<const int> tab; gptr<const double> scratch; gptr<double> q; GridDims g; };
+// Coarse points of a block of the tiled restriction, and its blocks for a level.
+constexpr int kRestrictTile[3] = {8, 8, 4};
+inline int restrict_tiles(const GridDims& c) {
+  int t = 1;
+  for (int d = 0; d < 3; ++d) t *= (c.n[d] + kRestrictTile[d] - 1) / kRestrictTile[d];
+  return t;
+}
 struct TransferArgs {              // restriction (fine -> coarse) and prolongation (coarse -> fine)
   gptr<const double> src; GridDims gs;  // q^{k-1} (restriction) or E^{k+1} (prolongation)
   gptr<const double> add;               // prolongation: e^k added to the interpolated values
@@ -598,7 +605,7 @@ struct mls_plan_s {
   int pair_blocks = 0;             // > 0: the trimmed pair kernels run persistent with this many blocks
   // coarse points up to which restriction and prolongation use the forms
   // with a group of lanes per coarse point
-  int split_restrict = 65536, split_prolong = 0;
+  int split_restrict = -1, split_prolong = 0;   // -1: by the order
   int* d_cid = nullptr;            // n_max: cell of original atom
   int2* d_perm_tmp = nullptr;      // n_max: (original index, cell) in arrival order
   // bucketed binning (0 buckets: the counting sort with device-wide atomics)

@@ -302,7 +302,7 @@ struct StencilLaunch {
 
 // The coarsest level's charges from the next finer level's, to the end of lds
 // (and, by the chain's first block, to memory): the restriction dimension by
-// dimension, in the order of sums of Restrict (grid.hip).  Every block of the
+// dimension, in the order of sums of RestrictTile (grid.hip).  Every block of the
 // level does it for itself, up to kJointCoarse points: a third of the work of
 // the points' (p + 1)^3 taps, while the level stencils run, against a launch
 // of 4 us on the chain (p = 6: 8 us).

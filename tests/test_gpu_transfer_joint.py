@@ -39,3 +39,26 @@ def test_joint_transfers_match_oracle(name, order):
         assert max(d) < 1e-12
     assert out["energy"] == pytest.approx(ref["energy"], rel=1e-10)
     plan.close()
+
+
+@pytest.mark.parametrize("order", [4, 6])
+@pytest.mark.parametrize("name", ["odd_l3", "level4352", "deep_l5"])
+def test_tiled_restriction_matches_oracle(name, order, monkeypatch):
+    """Every restriction in tiles of 8 x 8 x 4 coarse points: levels smaller than
+    a tile, ragged last tiles, fine extents below the taps' reach (1e-12)."""
+    monkeypatch.setenv("MLS_SPLIT_RESTRICT", "0")
+    box, levels = CASES[name]
+    w = W.fill_box(int(0.06 * np.prod(box)), np.array(box), seed=33)
+    w.c6 = np.random.default_rng(34).uniform(1.0, 9.0, w.n)
+    ref = M.mls(w.pos, w.c6, w.box, 2.5, 1.0, order, levels)
+    plan, _ = gpu_eval(w.pos, w.c6, w.box, 2.5, 1.0, order, levels)
+    # timed stages run the last restriction in its own launch
+    plan.set_timing(True)
+    import torch
+    plan.evaluate(*(torch.tensor(x, dtype=torch.float64, device="cuda") for x in (w.pos, w.c6)))
+    st = stages(plan, w.n)
+    for k in range(levels):
+        d = rel_err(st["q"][k], ref["q"][k])
+        say(f"[tiled restriction] {name} p{order} level {k + 1}: q {d:.1e}")
+        assert d < 1e-12
+    plan.close()
