@@ -109,8 +109,9 @@ hipError_t ensure_side(mls_plan_s* P) {
 // other on the caller's stream: the local part, its rows dealt to eight waves
 // per 64 targets, is then shorter than what the second stream costs (two
 // events and two waits: about 25 us of host time per call and 10 us on the
-// device).  FP64 evaluation in one stream / two: 1000 atoms 80 / 88 us, 4000
-// atoms 107 / 110, 32,000 atoms 125 / 128, 64,000 atoms 148 / 138.
+// device).  Evaluation in one stream / two (us), FP64: 1000 atoms 65 / 86, 4000
+// 97 / 106, 32,000 112 / 115, 48,000 127 / 120, 64,000 136 / 122; mixed: 4000
+// 118 / 107, 32,000 129 / 146, 48,000 185 / 148.
 constexpr int64_t kForkAtoms = 32768;
 bool forks(const mls_plan_s* P, int64_t n) { return !P->serial && n > kForkAtoms; }
 
@@ -186,7 +187,7 @@ mls_status evaluate_geometric(mls_plan_t P, int64_t n, const double* pos, const 
   }
   // In concurrent mode the local part is submitted after the grid chain's
   // first `pair_after` stages (default 1: the anterpolation, whose blocks need
-  // 35 KB of LDS each and are otherwise held back until the pair kernel has
+  // 22 to 33 KB of LDS each and are otherwise held back until the pair kernel has
   // filled and drained every CU; measured with graph replays at 10^6 atoms:
   // 0.835 ms per evaluation against 0.877 ms with the pair kernel first).
   const int after = fork ? P->pair_after : 0;

@@ -1239,14 +1239,25 @@ int pair_split(int64_t groups, bool alone) {
 // 1920; 20 waves 579 / 682 / 1046 / 2017.  The FP64 kernel leaves no slots worth
 // having at 20 waves, and fewer cost it what they give the chain (10^6 atoms,
 // all / 18 / 16: 734 / 734 / 762).  With the repulsion (R) a CU holds 20 anyway.
+// In a captured graph, whose replay starts both branches together, the one
+// chain's anterpolation comes first and the whole grid is better (10^6 atoms
+// mixed, all / 20 waves: 604 / 627 us a replay; 633 / 597 a call); the seven
+// chains still want the room (all / 14: 1388 / 1324 us a replay).
 constexpr int kBesideWaves = 20, kBesideSeven = 14;
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();   // not an error of the launch that follows
+  return false;
+}
 
 template <int K, bool R, bool LB>
 hipError_t launch_split_f32(const mls_plan_s* P, const PairArgsF& a, int groups, bool alone, hipStream_t s) {
   int blocks = P->pair_blocks;
   if (blocks <= 0) {
     if (groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
-    if (!alone && !R) blocks = P->cus * (LB ? kBesideSeven : kBesideWaves);
+    if (!alone && !R && (LB || !capturing(s))) blocks = P->cus * (LB ? kBesideSeven : kBesideWaves);
   }
   return launch_persist<PairTrimF32<K, R, LB>>(a, groups, blocks, s);
 }
