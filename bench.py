@@ -97,7 +97,7 @@ def stage_rooflines(stage_ms, model, precision):
 
 # kernels that carry each stage of the 10^6-atom cube (cell width a/2 there)
 STAGE_KERNEL = {("pair", "mixed"): ["void k_one<PairTrimF32<2, false, false> >"],
-                ("pair", "fp64"): ["void k_one<PairTrimF64<2, false, false> >"],
+                ("pair", "fp64"): ["void k_one<PairTrimF64<2, false, false, 1> >"],
                 ("stencil", "mixed"): ["void k_stencil_tile<float, 6, 16, 8>"],
                 ("stencil", "fp64"): ["void k_stencil_tile<double, 6, 8, 8>"],
                 ("anterpolation", "mixed"): ["void k_one<AnterpTile<4, float, 2744> >", "void k_one<AnterpCollect>"],

@@ -250,8 +250,8 @@ struct PairWave {
 //
 // At 10^6 atoms the vector ALU issues 80 (FP64) to 97 % (FP32) of the time and
 // the L1 serves a line in three of four cycles, so what counts is the number
-// of instructions: of a filter step (47 vector ones for four candidates), of a
-// drained entry (FP64 51, FP32 43) and of a row's set-up (about 75); idle lanes
+// of instructions: of a filter step (48 to 50 vector ones for four candidates), of a
+// drained entry (FP64 52, FP32 42) and of a row's set-up (about 75); idle lanes
 // load nothing.  With 57, 67, 57 and 130 the kernel took 516 us in FP64
 // instead of 454 (10^6 atoms at density 0.8, a = 3), in FP32 392 instead of 376.
 constexpr int kWaveQ = 64;    // lanes per block (one wave)
