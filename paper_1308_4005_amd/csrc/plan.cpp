@@ -376,7 +376,9 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
       const GridDims& g = P->lv[k - 1].g;
       tiles16 += (int64_t)((g.n[0] + 7) / 8) * ((g.n[1] + 7) / 8) * ((g.n[2] + 15) / 16);
     }
-    const int zc = stencil_tile_zc(Rw, P->precision != MLS_MIXED, tiles16);
+    // the depth of the kernel that will run: a mixed plan's may be the FP64 slab one
+    const int path = stencil_path(P);
+    const int zc = stencil_tile_zc(Rw, path != MLS_STENCIL_TILE_F32 && path != MLS_STENCIL_TILE_MFMA_F32, tiles16);
     P->stencil_zc = zc;
     for (int k = 1; k < l; ++k) {
       const GridDims& g = P->lv[k - 1].g;

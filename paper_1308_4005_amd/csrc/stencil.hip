@@ -883,6 +883,7 @@ int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts,
 
 template <class T, int R, int ZC = tile_zc(R, sizeof(T) == 8)>
 hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, const StencilOpts& o) {
+  if (P->stencil_zc != ZC) return hipErrorInvalidValue;   // the tile table is laid out for another depth
   StencilLaunch L;
   const int t = stencil_levels(P, P->d_rows, wts, o, L);
   k_stencil_tile<T, R, ZC, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
@@ -891,6 +892,7 @@ hipError_t launch_tile(mls_plan_s* P, const T* wts, hipStream_t s, const Stencil
 
 template <int R, int ZC, int NCH>
 hipError_t launch_slab(mls_plan_s* P, hipStream_t s, const StencilOpts& o) {
+  if (P->stencil_zc != ZC) return hipErrorInvalidValue;   // as launch_tile
   StencilLaunch L;
   const int t = stencil_levels(P, P->d_rows, P->d_row_w_tile, o, L);
   k_stencil_slab<R, ZC, NCH, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
@@ -933,6 +935,7 @@ hipError_t launch_tile_f32(mls_plan_s* P, int R, hipStream_t s, const StencilOpt
 
 template <int R>
 hipError_t launch_mfma(mls_plan_s* P, hipStream_t s, const StencilOpts& o) {
+  if (P->stencil_zc != 16) return hipErrorInvalidValue;   // as launch_tile
   StencilLaunch L;
   const int t = stencil_levels(P, P->d_rows_mfma, P->d_mfma_a, o, L);
   k_stencil_mfma<R, kStencilWaves><<<t, 64 * kStencilWaves, 0, s>>>(L, P->d_tiles);
