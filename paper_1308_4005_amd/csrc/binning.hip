@@ -948,7 +948,7 @@ static hipError_t binning_core(mls_plan_s* P, int n, const double* pos, const do
   if (P->bin_nbucket) {
     const int nblk = nblocks(n, kBinItems), m = P->bin_nbucket * nblk;
     const int direct = m <= kDirectHist;
-    BinBucketArgs a{pos, c6, n, g, P->d_cid, P->d_xw, P->d_flags, scale, mixed ? P->d_partial : nullptr, cond,
+    BinBucketArgs a{pos, c6, n, g, P->d_cid, P->d_xw, P->d_flags, scale, mixed ? P->d_xi_partial : nullptr, cond,
                     xref, P->bin_shift, P->bin_nbucket, nblk, P->d_bin_hist};
     BucketSortArgs da{P->d_bin_hist, P->d_bsum, nblk, P->bin_shift, P->bin_nbucket, P->d_perm_tmp, P->d_perm_tmp2, n,
                       P->d_cell_start, P->d_perm, P->d_xw, P->d_xs, P->d_cell_s, P->d_xr, P->d_xif, g, cond,
@@ -973,7 +973,7 @@ static hipError_t binning_core(mls_plan_s* P, int n, const double* pos, const do
   }
   if (n > 0) {
     BinCountArgs a{pos, c6, n, g, P->d_cid, P->d_slot, P->d_count, P->d_xw, P->d_flags, scale,
-                   mixed ? P->d_partial : nullptr, cond, xref};
+                   mixed ? P->d_xi_partial : nullptr, cond, xref};
     if ((e = launch_one<BinCount>(a, nblocks(n, kBlock), s)) != hipSuccess) return e;
   }
   ScanArgs sa{P->d_count, g.ncell, P->d_cell_start, P->d_bsum, P->d_bmax, P->d_ncell_max, cond};
@@ -1024,7 +1024,7 @@ hipError_t launch_sum_xi(mls_plan_s* P, int n, hipStream_t s) {
   if (P->precision != MLS_MIXED || n == 0 || stencil_adds_sum(P, n)) return hipSuccess;
   // sum of xi: the mean of every grid level's charges (partition of unity),
   // from the binning's per-block partial sums
-  SumXiArgs sa{n, P->d_partial, P->d_scratch};
+  SumXiArgs sa{n, P->d_xi_partial, P->d_scratch};
   return launch_one<SumXiFinal>(sa, 1, s);
 }
 

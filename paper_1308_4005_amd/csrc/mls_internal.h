@@ -622,6 +622,10 @@ struct mls_plan_s {
   double* d_e0 = nullptr;          // n_max sorted local potential
   double* d_floc = nullptr;        // 3 n_max sorted local force / (xi_i)
   double* d_partial = nullptr;     // energy partial sums
+  // mixed precision: the binning's per-block sums of xi.  Neighbour reuse reads
+  // them on steps that do not bin again, so plans with a skin keep them apart;
+  // the others' lie in d_partial, which is free until the interpolation
+  double* d_xi_partial = nullptr;
   int n_partial = 0;
   int lb_interp_blocks = 0;        // Lorentz-Berthelot: blocks d_partial has room for in the tiled interpolation
   double* d_scratch = nullptr;     // small reductions (grid means)

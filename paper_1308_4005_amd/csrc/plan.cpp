@@ -485,6 +485,9 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
     if (nt <= 16 * (int64_t)P->n_partial) P->lb_interp_blocks = (int)nt;
   }
   ALLOC(P->d_partial, 2 * (size_t)std::max(P->n_partial, P->lb_interp_blocks) + 2);
+  P->d_xi_partial = P->d_partial;
+  // (one evaluation per workspace, the static scratch, never reuses a binning)
+  if (P->precision == MLS_MIXED && P->skin > 0.0 && !P->arena) ALLOC(P->d_xi_partial, P->n_partial);
   ALLOC(P->d_scratch, 64);
   ALLOC(P->d_flags, 4);
   ALLOC(P->d_ncell_max, 4);

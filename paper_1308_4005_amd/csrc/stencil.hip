@@ -876,7 +876,7 @@ int stencil_levels(const mls_plan_s* P, const StencilRow* rows, const void* wts,
     L.qc[v] = (*cs.lv[v])[P->levels - 1].q;
     L.ec[v] = (*cs.lv[v])[P->levels - 1].e;
     L.qf[v] = joint ? (*cs.lv[v])[P->levels - 2].q : nullptr;
-    L.sum[v] = o.sum_rows > 0 ? (cs.n == 1 ? P->d_partial : lb_partial_buf(P, v)) : cs.sum[v];
+    L.sum[v] = o.sum_rows > 0 ? (cs.n == 1 ? P->d_xi_partial : lb_partial_buf(P, v)) : cs.sum[v];
   }
   return (t + L.ncoarse) * cs.n;
 }
