@@ -7,6 +7,8 @@
 // eq:gamma.  Pairs are found through the linked cells of the binning step;
 // the neighbour-cell offsets carry their image shift, which covers boxes
 // narrower than three cells.
+#include <type_traits>
+
 #include "device_math.h"
 #include "mls_internal.h"
 
@@ -961,142 +963,176 @@ struct PairTrimF32 {
 // the step's place (run, step of the run).  Then each lane's hits are listed in
 // order, every wave replays the queue lengths over all steps (counts only)
 // and evaluates every eighth drain, and the drains' sums are added in FP64.
-// LDS: 69 KB, two blocks per CU.  A block that finds more steps or hits than
-// fit (beyond about 280 neighbours per target) lets its first wave do the
-// whole scan as PairTrimF32 does.
+// LDS: 81,104 bytes, two blocks per CU.  Rows that leave more steps or hits
+// than fit (all 25 of a target with more than about 280 neighbours) are done in
+// several passes, half as many rows in each, the queues' last entries carried
+// from one to the next.  A pass of one row takes as many of its steps as the
+// lists hold whatever hits, the waves sharing them.  Evaluations of 32,000
+// atoms at density 0.8 with a = 4 / 5 / 6 in passes 210 / 545 / 732 us, with
+// such blocks left to one wave 313 / 627 / 999.
 constexpr int kSplitF = 8;           // waves per block
-constexpr int kSplitSteps = 40;      // filter steps of one wave
+// Filter steps of one wave: as many as the LDS of two blocks leaves.  With 40
+// every lattice (near-equal atoms per cell row) had blocks that did not fit: 4000
+// atoms on a jittered one 189 us an evaluation, now 124.
+constexpr int kSplitSteps = 48;
 constexpr int kSplitHits = 288;      // hits of one target
+constexpr int kSplitShare = kSplitHits / kBatchF / kSplitF;   // a wave's steps in a pass of one row
 constexpr int kSplitRuns = 50;       // 25 rows, two runs each
+constexpr int kSplitCarry = kQueueF - kBatchF;   // entries a queue holds between two steps
 
 template <int K, bool R = false, bool LB = false>
 struct PairSplitF32 {
   using Args = PairArgsF;
   static constexpr int kThreads = kWaveQ * kSplitF;
+  static constexpr int kWavesPerSimd = 4;   // two blocks per CU, as the LDS allows
   static __device__ void run(const Args& ar, int blk) {
     constexpr int NS = kSplitF, W = kWaveQ;
     __shared__ unsigned char mask[NS * kSplitSteps * W];
-    __shared__ unsigned short place[NS * kSplitSteps];
+    __shared__ int place[NS * kSplitSteps];
     __shared__ int first[kSplitRuns * W];       // queue entry of a run's first source
     // hit lists (step << 2 | candidate); later the waves' sums
     __shared__ __attribute__((aligned(16))) unsigned short list[kSplitHits * W];
+    __shared__ int carry[kSplitCarry * W];      // queue entries left by the passes before
     __shared__ unsigned short hits[NS * W];
     __shared__ int steps[NS];                   // filter steps of each wave, -1: too many
     __shared__ float4 shift[kShifts];
+    static_assert(sizeof(mask) + sizeof(place) + sizeof(first) + sizeof(list) + sizeof(carry) + sizeof(hits) +
+                      sizeof(steps) + sizeof(shift) <= 80 * 1024, "two blocks per CU");
     const TargetF t = pair_target_f32<LB>(ar, blk, shift);
     const int lane = t.lane;
-    const RowSpan<NS> span;
-    const int wv = span.wv;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     if (wv == 0) fill_shifts(shift, lane, ar.g, ar.pc);   // read after the barrier below
     const PairConstF& pc = ar.pc;
     const PairRep& rp = ar.rep;
-    // ---- filter
-    {
-      const CellGeom& g = ar.g;
-      const RowTrim trim(ar.cstart, g, pc.w, pc.a2);
-      const FilterRows f(ar.xf, ar.xf_stride);
-      int ns = 0, nh = 0;
-      // the cell ranges of all rows first, their loads in flight together
-      constexpr int kRows = (25 + NS - 1) / NS;
-      RowRuns rr[kRows];
+    const CellGeom& g = ar.g;
+    const RowTrim trim(ar.cstart, g, pc.w, pc.a2);
+    const FilterRows f(ar.xf, ar.xf_stride);
+    double sum[R ? 8 : 4] = {};
+    int cnt = 0, drain = 0;   // the lane's queue length, drains so far
+    // the pass: from step `seg` of the first of `rows` rows (seg > 0: a part of one)
+    int row = 0, rows = 25, seg = 0;
+    // One pass; true when all rows are done.  ALL: the first one, of every row,
+    // without what only the others need (4000 atoms: the kernel 39.0 us, with
+    // one form for all passes 41.6).
+    auto pass = [&](auto all) -> bool {
+      constexpr bool ALL = decltype(all)::value;
+      if (ALL) rows = 25;
+      else rows = min(rows, 25 - row);
+      const bool single = !ALL && rows == 1;
+      int row_steps = 0;   // single: steps of the row
+      // ---- filter: this wave's share of the pass's rows
+      {
+        const int r0 = single ? row : row + rows * wv / NS;
+        const int r1 = single ? row + 1 : row + rows * (wv + 1) / NS;
+        int ns = 0, nh = 0;
+        // the cell ranges of all rows first, their loads in flight together
+        constexpr int kRows = (25 + NS - 1) / NS;
+        RowRuns rr[kRows];
 #pragma unroll
-      for (int u = 0; u < kRows; ++u) {
-        const int r = span.r0 + u;
-        const int dz = r / 5 - 2, dy = r % 5 - 2;
-        int tz = t.cz + dz, ty = t.cy + dy;
-        tz = tz < 0 ? tz + g.nc[2] : (tz >= g.nc[2] ? tz - g.nc[2] : tz);
-        ty = ty < 0 ? ty + g.nc[1] : (ty >= g.nc[1] ? ty - g.nc[1] : ty);
-        const float gz = trim.gap(2, dz, t.xi.z), gy = trim.gap(1, dy, t.xi.y);
-        const float rem = r < span.r1 ? (trim.a2m - gz * gz) - gy * gy : 0.0f;
-        rr[u] = trim.runs(t.cx, t.xi.x, t.active, rem, (tz * g.nc[1] + ty) * g.nc[0]);
-      }
+        for (int u = 0; u < kRows; ++u) {
+          const int r = r0 + u;
+          const int dz = r / 5 - 2, dy = r % 5 - 2;
+          int tz = t.cz + dz, ty = t.cy + dy;
+          tz = tz < 0 ? tz + g.nc[2] : (tz >= g.nc[2] ? tz - g.nc[2] : tz);
+          ty = ty < 0 ? ty + g.nc[1] : (ty >= g.nc[1] ? ty - g.nc[1] : ty);
+          const float gz = trim.gap(2, dz, t.xi.z), gy = trim.gap(1, dy, t.xi.y);
+          const float rem = r < r1 ? (trim.a2m - gz * gz) - gy * gy : 0.0f;
+          rr[u] = trim.runs(t.cx, t.xi.x, t.active, rem, (tz * g.nc[1] + ty) * g.nc[0]);
+        }
 #pragma unroll
-      for (int u = 0; u < kRows; ++u) {
-        const int r = span.r0 + u;
-        const int dz = r / 5 - 2, dy = r % 5 - 2;
-        const float ay = fmaf((float)-dy, pc.w[1], t.L.yy);
-        const float az = fmaf((float)-dz, pc.w[2], t.L.zz);
+        for (int u = 0; u < kRows; ++u) {
+          const int r = r0 + u;
+          const int dz = r / 5 - 2, dy = r % 5 - 2;
+          const float ay = fmaf((float)-dy, pc.w[1], t.L.yy);
+          const float az = fmaf((float)-dz, pc.w[2], t.L.zz);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          int j = h ? rr[u].k0 : rr[u].j0;
-          const int j1 = h ? rr[u].k1 : rr[u].j1, ix = h ? rr[u].ix2 : rr[u].ix1;
-          if (!__any(j < j1)) continue;
-          const float ax = fmaf((float)-ix, pc.L[0], t.L.xa);
-          first[(2 * r + h) * W + lane] = j | entry_bits(ix, dy, dz);
-          // the next step's candidates are loaded before this step's are used
-          float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X, Xn = X, Yn = X, Zn = X;
-          auto load = [&](int i) {
-            if (i < j1) {
-              const unsigned off = (unsigned)i * 4u;
-              Xn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.x) + (unsigned)off));
-              Yn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.y) + (unsigned)off));
-              Zn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.z) + (unsigned)off));
+          for (int h = 0; h < 2; ++h) {
+            int j = h ? rr[u].k0 : rr[u].j0;
+            const int j1 = h ? rr[u].k1 : rr[u].j1, ix = h ? rr[u].ix2 : rr[u].ix1;
+            if (!__any(j < j1)) continue;
+            int k = 0, kend = 1 << 30;   // the wave's steps of the run
+            if (single) {
+              int len = j1 - j + kBatchF - 1;
+#pragma unroll
+              for (int off = 32; off > 0; off >>= 1) len = max(len, __shfl_xor(len, off));
+              k = max(0, seg + wv * kSplitShare - row_steps);
+              kend = seg + (wv + 1) * kSplitShare - row_steps;
+              row_steps += len / kBatchF;
             }
-          };
-          load(j);
-          for (int k = 0; ns >= 0 && __any(j < j1); ++k) {
-            if (ns == kSplitSteps) {
-              ns = -1;
-              break;
-            }
-            const int rem = j1 - j;
-            X = Xn;
-            Y = Yn;
-            Z = Zn;
-            load(j + kBatchF);
-            const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
-            int m = 0;
+            const float ax = fmaf((float)-ix, pc.L[0], t.L.xa);
+            first[(2 * r + h) * W + lane] = j | entry_bits(ix, dy, dz);
+            // the next step's candidates are loaded before this step's are used
+            float4 X = make_float4(0.0f, 0.0f, 0.0f, 0.0f), Y = X, Z = X, Xn = X, Yn = X, Zn = X;
+            auto load = [&](int i) {
+              if (i < j1) {
+                const unsigned off = (unsigned)i * 4u;
+                Xn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.x) + (unsigned)off));
+                Yn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.y) + (unsigned)off));
+                Zn = load4f(reinterpret_cast<const float*>(reinterpret_cast<const char*>(f.z) + (unsigned)off));
+              }
+            };
+            j += k * kBatchF;
+            load(j);
+            for (; ns >= 0 && k < kend && __any(j < j1); ++k) {
+              if (ns == kSplitSteps) {
+                ns = -1;
+                break;
+              }
+              const int rem = j1 - j;
+              X = Xn;
+              Y = Yn;
+              Z = Zn;
+              load(j + kBatchF);
+              const float xb[4] = {X.x, X.y, X.z, X.w}, yb[4] = {Y.x, Y.y, Y.z, Y.w}, zb[4] = {Z.x, Z.y, Z.z, Z.w};
+              int m = 0;
 #pragma unroll
-            for (int b = 0; b < kBatchF; ++b) {
-              const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
-              const float r2 = fmaf(dzv, dzv, fmaf(dxv, dxv, dyv * dyv));
-              m |= ((b < rem) & (r2 < pc.a2f)) ? 1 << b : 0;
+              for (int b = 0; b < kBatchF; ++b) {
+                const float dxv = ax - xb[b], dyv = ay - yb[b], dzv = az - zb[b];
+                const float r2 = fmaf(dzv, dzv, fmaf(dxv, dxv, dyv * dyv));
+                m |= ((b < rem) & (r2 < pc.a2f)) ? 1 << b : 0;
+              }
+              mask[(wv * kSplitSteps + ns) * W + lane] = (unsigned char)m;
+              if (lane == 0) place[wv * kSplitSteps + ns] = (2 * r + h) | (k << 6);
+              nh += __builtin_popcount(m);
+              ++ns;
+              j += kBatchF;
             }
-            mask[(wv * kSplitSteps + ns) * W + lane] = (unsigned char)m;
-            if (lane == 0) place[wv * kSplitSteps + ns] = (unsigned short)((2 * r + h) | (k << 6));
-            nh += __builtin_popcount(m);
-            ++ns;
-            j += kBatchF;
           }
         }
+        hits[wv * W + lane] = (unsigned short)nh;
+        if (lane == 0) steps[wv] = ns;
       }
-      hits[wv * W + lane] = (unsigned short)nh;
-      if (lane == 0) steps[wv] = ns;
-    }
-    __syncthreads();
-    int base = 0, total = 0, few = 0;
+      __syncthreads();
+      int base = 0, total = 0, few = 0;
 #pragma unroll
-    for (int w = 0; w < NS; ++w) {
-      const int h = hits[w * W + lane];
-      base += w < wv ? h : 0;
-      total += h;
-      few = min(few, steps[w]);
-    }
-    double sum[R ? 8 : 4] = {};
-    if (few < 0 || __any(total > kSplitHits)) {   // the same in every wave
-      if (wv == 0) {
-        int* const queue = reinterpret_cast<int*>(list);
-        PairAccM A{{0.0, 0.0, 0.0, 0.0}, 0};
-        RepAcc B{{0.0, 0.0, 0.0, 0.0}};
-        pair_rows_f32<K, R, LB>(ar, t, queue, A, B);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          sum[c] = A.a[c];
-          if constexpr (R) sum[4 + c] = B[c];
-        }
+      for (int w = 0; w < NS; ++w) {
+        const int h = hits[w * W + lane];
+        base += w < wv ? h : 0;
+        total += h;
+        few = min(few, steps[w]);
       }
-    } else {
+      if (few < 0 || __any(total > kSplitHits)) {   // the same in every wave
+        rows = (rows + 1) / 2;   // never one row: kSplitShare steps, kSplitHits hits
+        __syncthreads();   // hits and steps have been read
+        return false;
+      }
       // ---- the hits in order
-      for (int s = 0; s < steps[wv]; ++s) {
-        const int st = wv * kSplitSteps + s;
+      for (int st = wv * kSplitSteps, n = st + steps[wv]; st < n; ++st) {
         const int m = mask[st * W + lane];
 #pragma unroll
         for (int b = 0; b < kBatchF; ++b)
           if (m >> b & 1) list[base++ * W + lane] = (unsigned short)(st << 2 | b);
       }
       __syncthreads();
-      // ---- the drains
-      int cnt = 0, pos = 0, drain = 0;
+      // ---- the drains; a lane's entries are its carried ones, then its list
+      const int old = cnt;
+      int pos = 0;
+      auto entry = [&](int i) {
+        if (!ALL && i < old) return carry[i * W + lane];
+        const int e = list[(i - old) * W + lane];
+        const int pl = place[e >> 2];
+        return first[(pl & 63) * W + lane] + ((pl >> 6) << 2) + (e & 3);
+      };
       auto evaluate = [&](int m) {
         DrainF<R> D;
         // four sources at a time, their look-ups and loads in flight together
@@ -1108,12 +1144,7 @@ struct PairSplitF32 {
           float wsrc[kAhead];
 #pragma unroll
           for (int u = 0; u < kAhead; ++u) {
-            int q = t.L.self_ent;
-            if (u0 + u < m) {
-              const int e = list[(pos + u0 + u) * W + lane];
-              const int pl = place[e >> 2];
-              q = first[(pl & 63) * W + lane] + ((pl >> 6) << 2) + (e & 3);
-            }
+            const int q = u0 + u < m ? entry(pos + u0 + u) : t.L.self_ent;
             // idle slots (and the target itself): as in pair_drain_f32
             ok[u] = q != t.L.self_ent;
             ent[u] = ok[u] ? q : t.L.safe_ent;
@@ -1128,12 +1159,12 @@ struct PairSplitF32 {
         for (int c = 0; c < (R ? 8 : 4); ++c) sum[c] += (double)D.s[c];
       };
       for (int w = 0; w < NS; ++w) {
-        const int n = steps[w];
-        const unsigned char* mw = mask + w * kSplitSteps * W + lane;
-        int next = mw[0];
-        for (int s = 0; s < n; ++s) {
+        int st = w * kSplitSteps;
+        const int n = st + steps[w];
+        int next = mask[st * W + lane];
+        for (; st < n; ++st) {
           cnt += __builtin_popcount(next);
-          next = mw[min(s + 1, kSplitSteps - 1) * W];
+          next = mask[min(st + 1, NS * kSplitSteps - 1) * W + lane];
           if (__any(cnt > kQueueF - kBatchF)) {
             const int m = min(cnt, kDrainF);
             if ((drain++ & (NS - 1)) == wv) evaluate(m);
@@ -1142,8 +1173,29 @@ struct PairSplitF32 {
           }
         }
       }
+      if (single && seg + NS * kSplitShare < row_steps) {
+        seg += NS * kSplitShare;
+      } else {
+        row += rows;
+        seg = 0;
+      }
+      if (!ALL && row < 25) {
+        // what the queues still hold (at most kSplitCarry entries) for the next pass
+        int v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) v[u] = wv + u * NS < cnt ? entry(pos + wv + u * NS) : 0;
+        static_assert(kSplitCarry <= 2 * NS, "two entries per wave");
+        __syncthreads();   // carry, and the lists and masks behind it, have been read
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (wv + u * NS < cnt) carry[(wv + u * NS) * W + lane] = v[u];
+        return false;
+      }
       if ((drain & (NS - 1)) == wv) evaluate(cnt);
-    }
+      return true;
+    };
+    bool done = pass(std::true_type{});
+    while (!done) done = pass(std::false_type{});
     __syncthreads();
     // ---- the waves' sums, in wave order
     double* const out = reinterpret_cast<double*>(list);
