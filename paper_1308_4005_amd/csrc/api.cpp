@@ -109,11 +109,22 @@ hipError_t ensure_side(mls_plan_s* P) {
 // other on the caller's stream: the local part, its rows dealt to eight waves
 // per 64 targets, is then shorter than what the second stream costs (two
 // events and two waits: about 25 us of host time per call and 10 us on the
-// device).  Evaluation in one stream / two (us), FP64: 1000 atoms 65 / 86, 4000
-// 97 / 106, 32,000 112 / 115, 48,000 127 / 120, 64,000 136 / 122; mixed: 4000
-// 118 / 107, 32,000 129 / 146, 48,000 185 / 148.
+// device).  Evaluation in one stream / two (us; jittered lattice at density 0.8,
+// a = 3): FP64 2000 atoms 78 / 94, 4000 101 / 106, 32,000 115 / 116, 48,000
+// 129 / 120; mixed 32,000 135 / 147, 48,000 189 / 152; the seven chains of
+// Lorentz-Berthelot mixing, FP64 8000 112 / 117, 32,000 156 / 154, 64,000 200 /
+// 184, mixed 32,000 167 / 180, 64,000 258 / 187; vapour of density 0.03, 32,000
+// atoms, FP64 152 / 175, mixed 150 / 173.  The line suits all but mixed liquids
+// of up to 16,000 atoms, whose eight waves take longer than FP64's and leave CUs
+// idle (4000 atoms 124 / 105, 16,000 122 / 110).
+//
+// The tap stencil (windows beyond 12 points) takes milliseconds and leaves the
+// pair kernel room: always beside it (16,000 atoms, a = 8, FP64 10.1 / 9.5 ms,
+// mixed 10.5 / 9.6).
 constexpr int64_t kForkAtoms = 32768;
-bool forks(const mls_plan_s* P, int64_t n) { return !P->serial && n > kForkAtoms; }
+bool forks(const mls_plan_s* P, int64_t n) {
+  return !P->serial && (n > kForkAtoms || stencil_path(P) == MLS_STENCIL_TAPS_F64);
+}
 
 // The grid chain's stream for an evaluation on stream s: the plan's second
 // one, started after what s holds so far, or s itself; and back again.

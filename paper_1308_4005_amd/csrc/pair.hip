@@ -1308,7 +1308,9 @@ template <int K, bool R, bool LB>
 hipError_t launch_split_f32(const mls_plan_s* P, const PairArgsF& a, int groups, bool alone, hipStream_t s) {
   int blocks = P->pair_blocks;
   if (blocks <= 0) {
-    if (groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
+    // (so few beside a chain: one with the tap stencil, whose waves the eight
+    // would displace: 30,000 atoms at a = 4, h = 0.5 19.1 ms in one, 24.9 in eight)
+    if (alone && groups <= kSplitGroupsF) return launch_one<PairSplitF32<K, R, LB>>(a, groups, s);
     if (!alone && !R && (LB || !capturing(s))) blocks = P->cus * (LB ? kBesideSeven : kBesideWaves);
   }
   return launch_persist<PairTrimF32<K, R, LB>>(a, groups, blocks, s);
