@@ -707,8 +707,8 @@ mls_status batch_evaluate(mls_batch_t B, const double* pos, const double* c6, co
   B->always_set_io |= capture != hipStreamCaptureStatusNone;
   if (!same_io || B->always_set_io) {
     // in stream order after the evaluations before it; work of another
-    // stream that may still read the old pointers is waited for
-    if (B->ran && B->last_stream != s && capture == hipStreamCaptureStatusNone)
+    // stream that may still read other pointers is waited for
+    if (!same_io && B->ran && B->last_stream != s && capture == hipStreamCaptureStatusNone)
       HIP_TRY(hipDeviceSynchronize(), "batch: synchronise");
     B->io = BatchIO{pos, c6, sigma, energies, forces, dE_dc6};
     HIP_TRY(launch_set_io(B->d_io, B->io, s), "batch: launch");
