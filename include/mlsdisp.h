@@ -389,10 +389,12 @@ mls_status mls_plan_destroy(mls_plan_t plan);
  * n_per_box; energies is device (nbox).  All arrays are device FP64 owned by
  * the caller; forces and dE_dc6 may be NULL.  Outputs are overwritten.
  * Calls are enqueue-only, with new pointers too, except the first, the one
- * after mls_batch_set_tuning, and one with new pointers on another stream than
- * the call before (they synchronise the device).  Errors: as mls_evaluate; mls_batch_create returns
- * MLS_ERR_UNSUPPORTED for a box whose level-stencil window 2a/h exceeds 8
- * grid points.  A batch is not thread-safe.
+ * after mls_batch_set_tuning, and one with other pointers than the last
+ * enqueued one's on another stream than its (they synchronise the device).  A
+ * captured call keeps its pointers for its replays; once there is
+ * one, every call writes its pointers to the device again.  Errors: as
+ * mls_evaluate; mls_batch_create returns MLS_ERR_UNSUPPORTED for a box whose
+ * level-stencil window 2a/h exceeds 8 grid points.  A batch is not thread-safe.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int blocks[MLS_NUM_STAGES]; /* persistent grid of each MLS_T_* stage in blocks; 0 = one block per item */

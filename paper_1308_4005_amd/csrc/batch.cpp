@@ -43,11 +43,12 @@ struct mls_batch_s {
   void* arena = nullptr;
   bool built = false;
 
-  // the caller's arrays of the last evaluation, and their device copy, which
-  // the kernels read
+  // the caller's arrays of the last evaluation enqueued (not captured), and
+  // the device copy that the kernels read
   BatchIO io{};
   BatchIO* d_io = nullptr;
-  bool ran = false;                  // some evaluation was enqueued
+  bool ran = false;                  // some evaluation was enqueued,
+  hipStream_t ran_on = nullptr;      // the last one on this stream
   bool always_set_io = false;        // an evaluation was captured: its replays write d_io too
 
   mls_batch_tuning tune{};
@@ -708,17 +709,22 @@ mls_status batch_evaluate(mls_batch_t B, const double* pos, const double* c6, co
   if (!same_io || B->always_set_io) {
     // in stream order after the evaluations before it; work of another
     // stream that may still read other pointers is waited for
-    if (!same_io && B->ran && B->last_stream != s && capture == hipStreamCaptureStatusNone)
+    if (!same_io && B->ran && B->ran_on != s && capture == hipStreamCaptureStatusNone)
       HIP_TRY(hipDeviceSynchronize(), "batch: synchronise");
-    B->io = BatchIO{pos, c6, sigma, energies, forces, dE_dc6};
-    HIP_TRY(launch_set_io(B->d_io, B->io, s), "batch: launch");
+    const BatchIO io{pos, c6, sigma, energies, forces, dE_dc6};
+    HIP_TRY(launch_set_io(B->d_io, io, s), "batch: launch");
+    // a captured call writes nothing yet: the work in flight has the arrays before it
+    if (capture == hipStreamCaptureStatusNone) B->io = io;
   }
   if (B->tune_pending) {
     B->tune_pending = false;
     if ((st = autotune(B, s)) != MLS_OK) return st;
   }
   B->last_stream = s;
-  B->ran = true;
+  if (capture == hipStreamCaptureStatusNone) {
+    B->ran = true;
+    B->ran_on = s;
+  }
   if (!B->use_graph) return run_phases(B, s, nullptr);
   if (!B->exec) {
     HIP_TRY(hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeRelaxed), "batch: begin capture");

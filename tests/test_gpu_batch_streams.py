@@ -42,3 +42,36 @@ def test_unchanged_arrays_on_two_streams_after_a_capture(lb):
     g.replay()
     torch.cuda.synchronize()
     _same(out, ref)
+
+
+@pytest.mark.parametrize("own", [False, True], ids=["second stream", "the capture's stream"])
+def test_new_arrays_after_a_capture_wait_for_the_ones_in_flight(own):
+    """An evaluation still waiting on its stream keeps its arrays when a call
+    with others is captured and then made on another stream."""
+    import torch
+    x, y = _inputs(1, False), _inputs(2, False)
+    bp = _plan(False)
+    bp.set_graph(False)
+    refx, refy = _run(_plan(False), False, x), _run(_plan(False), False, y)
+    outx, outy = _run(bp, False, x), _run(bp, False, y)
+    m = torch.randn(8192, 8192, device="cuda")
+    r = torch.mm(m, m)
+    a, b, c = (torch.cuda.Stream() for _ in range(3))
+    torch.cuda.synchronize()
+    outx.forces.zero_()
+    outy.forces.zero_()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(a):
+        for _ in range(30):
+            torch.mm(m, m, out=r)
+        _run(bp, False, y, out=outy)
+    with torch.cuda.stream(c):
+        g.capture_begin(capture_error_mode="relaxed")
+        _run(bp, False, x, out=outx)
+        g.capture_end()
+    with torch.cuda.stream(c if own else b):
+        _run(bp, False, x, out=outx)
+    torch.cuda.synchronize()
+    _same(outy, refy)
+    _same(outx, refx)
