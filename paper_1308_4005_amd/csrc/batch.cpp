@@ -555,9 +555,16 @@ mls_status time_stages(mls_batch_s* B, hipStream_t s, int reps, double* stage_ms
   return MLS_OK;
 }
 
+// The stencil tile depth of 16 is used: some box's window allows it.
+bool deep_tiles(const mls_batch_s* B) {
+  for (const mls_plan_s* P : B->plans)
+    if (P->levels > 1 && stencil_tile_ok(stencil_template(stencil_window(P)), 16, B->precision != MLS_MIXED)) return true;
+  return false;
+}
+
 // Autotuner: every stage's persistent grid over kCandidateGrids and the
-// stencil tile depth over {16, 8}, timed on the caller's data; per stage the
-// fastest candidate is kept.
+// stencil tile depth over {16, 8} (8 alone where no box takes 16), timed on the
+// caller's data; per stage the fastest candidate is kept.
 mls_status autotune(mls_batch_s* B, hipStream_t s) {
   if (B->events.empty()) {
     B->events.resize(MLS_NUM_STAGES + 1);
@@ -565,13 +572,14 @@ mls_status autotune(mls_batch_s* B, hipStream_t s) {
   }
   double best[MLS_NUM_STAGES];
   int best_grid[MLS_NUM_STAGES];
-  int best_zc = 16;
+  const int first_zc = deep_tiles(B) ? 16 : 8;
+  int best_zc = first_zc;
   for (int k = 0; k < MLS_NUM_STAGES; ++k) {
     best[k] = 1e30;
     best_grid[k] = 0;
   }
   mls_status st;
-  for (int zc : {16, 8}) {
+  for (int zc = first_zc; zc >= 8; zc -= 8) {
     B->tune.stencil_zc = zc;
     if ((st = build_phases(B)) != MLS_OK) return st;
     for (int g : kCandidateGrids) {
@@ -582,7 +590,7 @@ mls_status autotune(mls_batch_s* B, hipStream_t s) {
       for (int k = 0; k < MLS_NUM_STAGES; ++k) {
         // the tile depth only matters to the stencil stage; other stages are
         // compared on the first depth only
-        if (k != MLS_T_STENCIL && zc != 16) continue;
+        if (k != MLS_T_STENCIL && zc != first_zc) continue;
         if (ms[k] < best[k]) {
           best[k] = ms[k];
           best_grid[k] = g;
