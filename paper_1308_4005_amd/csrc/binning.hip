@@ -867,11 +867,6 @@ __global__ void k_zero(double* __restrict__ p, int64_t n) {
   for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0.0;
 }
 
-__global__ void k_zero_i(int* __restrict__ p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
-}
-
 __global__ void k_set_io(BatchIO* to, BatchIO io) { *to = io; }
 
 inline int nblocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
@@ -903,13 +898,6 @@ hipError_t launch_zero(double* p, int64_t count, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   int blocks = (int)std::min<int64_t>(nblocks(count, kBlock), 4096);
   k_zero<<<blocks, kBlock, 0, s>>>(p, count);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_i(int* p, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  int blocks = (int)std::min<int64_t>(nblocks(count, kBlock), 4096);
-  k_zero_i<<<blocks, kBlock, 0, s>>>(p, count);
   return hipGetLastError();
 }
 
@@ -1026,14 +1014,6 @@ hipError_t launch_sum_xi(mls_plan_s* P, int n, hipStream_t s) {
   // from the binning's per-block partial sums
   SumXiArgs sa{n, P->d_xi_partial, P->d_scratch};
   return launch_one<SumXiFinal>(sa, 1, s);
-}
-
-hipError_t launch_scan(mls_plan_s* P, int* count, int m, int* start, hipStream_t s) {
-  ScanArgs a{count, m, start, P->d_bsum, P->d_bmax, P->d_ncell_max};
-  hipError_t e;
-  if ((e = launch_one<ScanBlocks>(a, scan_blocks(m), s)) != hipSuccess) return e;
-  if ((e = launch_one<ScanSums>(a, 1, s)) != hipSuccess) return e;
-  return launch_one<ScanAdd>(a, nblocks(m, kBlock), s);
 }
 
 hipError_t launch_batched_binning(const BatchPhase& ph, hipStream_t s) {

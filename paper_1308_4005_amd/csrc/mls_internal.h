@@ -584,8 +584,6 @@ struct mls_plan_s {
   int ntiles = 0;
   int stencil_kernel = 1;          // 1: LDS tile kernel, 0: slab kernel (FP64) for every window
   int stencil_zc = 16;             // z extent of a level-stencil tile
-  double* d_row_w = nullptr;
-  float* d_row_wf = nullptr;
   double taps_wsum = 0;            // sum of level-1 weights (mean term in mixed precision)
 
   // coarsest kernel K_l, x fastest
@@ -731,7 +729,6 @@ hipError_t launch_sum_xi(mls_plan_s* P, int n, hipStream_t s);
 // `alone`: nothing runs beside it (pair_split).
 hipError_t launch_pair(mls_plan_s* P, int n, hipStream_t s, const PairRep* rep = nullptr, bool* fused = nullptr,
                        bool alone = false);
-hipError_t launch_scan(mls_plan_s* P, int* count, int m, int* start, hipStream_t s);
 hipError_t launch_anterpolate(mls_plan_s* P, int n, hipStream_t s);
 // Level stencils of levels 1..kmax (kmax = 0: all levels below the coarsest),
 // and with `coarsest` the coarsest level in the same launch.
@@ -764,7 +761,6 @@ hipError_t launch_interpolate_lb(mls_plan_s* P, int n, double* energy, double* f
 hipError_t launch_binning_scaled(mls_plan_s* P, int n, const double* pos, const double* c6, double scale,
                                  hipStream_t s);
 hipError_t launch_zero(double* p, int64_t count, hipStream_t s);
-hipError_t launch_zero_i(int* p, int64_t count, hipStream_t s);
 hipError_t launch_copy_stage(mls_plan_s* P, int what, int level, void* dst, hipStream_t s);
 // molecular dynamics (md.hip): repulsion over the sorted atoms of the current
 // evaluation (its forces and energy join the outputs in the interpolation,

@@ -275,11 +275,6 @@ __device__ __forceinline__ const T& at32(const T* base, int j) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (unsigned)j * (unsigned)sizeof(T));
 }
 
-template <class T>
-__device__ __forceinline__ const T& at32(const gptr<const T>& base, int j) {
-  return at32((const T*)base, j);
-}
-
 // the same for the element that the low 24 bits of ent name
 template <class T>
 __device__ __forceinline__ const T& at24(const T* base, int ent) {

@@ -546,8 +546,6 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
   ALLOC(P->d_row_w_tile, P->row_w.size());
   ALLOC(P->d_row_wf_tile, P->row_w.size());
   ALLOC(P->d_tiles, tiles.size());
-  ALLOC(P->d_row_w, P->row_w.size());
-  ALLOC(P->d_row_wf, P->row_w.size());
   ALLOC(P->d_Kl, P->Kl.size());
   if (P->stencil_mfma) {
     ALLOC(P->d_mfma_a, mfma_a.size());
@@ -565,11 +563,6 @@ mls_status build_plan(const mls_params& p, int64_t n_max, mls_plan_s* P) {
       return hip_fail(e, "copy stencil taps");
     if ((e = hipMemcpy(P->d_rows, P->rows.data(), P->rows.size() * sizeof(StencilRow), hipMemcpyHostToDevice)) != hipSuccess)
       return hip_fail(e, "copy stencil rows");
-    if ((e = hipMemcpy(P->d_row_w, P->row_w.data(), P->row_w.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "copy stencil weights");
-    std::vector<float> wf(P->row_w.begin(), P->row_w.end());
-    if ((e = hipMemcpy(P->d_row_wf, wf.data(), wf.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "copy stencil weights (fp32)");
   }
   if (!tiles.empty()) {
     if ((e = hipMemcpy(P->d_tiles, tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice)) != hipSuccess)
