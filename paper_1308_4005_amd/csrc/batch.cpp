@@ -207,7 +207,16 @@ mls_status build_phases(mls_batch_s* B) {
 
   // ------------------------------------------------ local part (eq:g_0)
   {
-    // boxes share the smoothing function; 0x10 selects the LB source weight
+    // boxes share the smoothing function; 0x10 selects the LB source weight.
+    // The waves that share 64 targets follow from the groups of all boxes, up to
+    // kSplitGroupsF as if the chain did not run beside: so few leave it room.
+    // Evaluation of several boxes with 1 / 2 / 4 / 8 waves (us), FP64: 252 groups
+    // 146 / 111 / 97 / 97, 367 151 / 138 / 135 / 139, 1000 158 / 128 / 125 / 133,
+    // 2000 184 / 175 / 185 / 195, 3728 327 / 338 / 336 / 346; mixed, 1 / 8: 252
+    // groups 147 / 109, 367 153 / 139, 1000 160 / 164, 2000 180 / 247.  Beside the
+    // seven chains of Lorentz-Berthelot mixing a few waves gain less, or cost: FP64
+    // 252 groups 181 / 145 / 128 / 135, 1000 236 / 232 / 229 / 242, 1855 582 / 613 /
+    // 632 / 612; mixed, 1 / 8: 252 groups 168 / 135, 367 229 / 255.
     int64_t groups = 0;
     for (int b = 0; b < nb; ++b)
       if (B->plans[b]->pair_fast) groups += nblk(n_of(b), 64);
