@@ -1289,7 +1289,8 @@ int pair_split(int64_t groups, bool alone) {
 // In a captured graph, whose replay starts both branches together, the one
 // chain's anterpolation comes first and the whole grid is better (10^6 atoms
 // mixed, all / 20 waves: 604 / 627 us a replay; 633 / 597 a call); the seven
-// chains still want the room (all / 14: 1388 / 1324 us a replay).
+// chains still want the room (all / 14: 1406 / 1378 us a replay of a jittered
+// lattice, 1388 / 1324 on another card).
 constexpr int kBesideWaves = 20, kBesideSeven = 14;
 
 bool capturing(hipStream_t s) {
