@@ -958,7 +958,7 @@ struct PairTrimF32 {
 // the step's place (run, step of the run).  Then each lane's hits are listed in
 // order, every wave replays the queue lengths over all steps (counts only)
 // and evaluates every eighth drain, and the drains' sums are added in FP64.
-// LDS: 81,104 bytes, two blocks per CU.  Rows that leave more steps or hits
+// LDS: 80,336 bytes, two blocks per CU.  Rows that leave more steps or hits
 // than fit (all 25 of a target with more than about 280 neighbours) are done in
 // several passes, half as many rows in each, the queues' last entries carried
 // from one to the next.  A pass of one row takes as many of its steps as the
@@ -983,7 +983,7 @@ struct PairSplitF32 {
   static __device__ void run(const Args& ar, int blk) {
     constexpr int NS = kSplitF, W = kWaveQ;
     __shared__ unsigned char mask[NS * kSplitSteps * W];
-    __shared__ int place[NS * kSplitSteps];
+    __shared__ unsigned short place[NS * kSplitSteps];
     __shared__ int first[kSplitRuns * W];       // queue entry of a run's first source
     // hit lists (step << 2 | candidate); later the waves' sums
     __shared__ __attribute__((aligned(16))) unsigned short list[kSplitHits * W];
@@ -1007,8 +1007,8 @@ struct PairSplitF32 {
     // the pass: from step `seg` of the first of `rows` rows (seg > 0: a part of one)
     int row = 0, rows = 25, seg = 0;
     // One pass; true when all rows are done.  ALL: the first one, of every row,
-    // without what only the others need (4000 atoms: the kernel 39.0 us, with
-    // one form for all passes 41.6).
+    // without what only the others need (4000 atoms: 37.3 us; one form for all
+    // passes cost 2.6 us).
     auto pass = [&](auto all) -> bool {
       constexpr bool ALL = decltype(all)::value;
       if (ALL) rows = 25;
@@ -1050,8 +1050,11 @@ struct PairSplitF32 {
               int len = j1 - j + kBatchF - 1;
 #pragma unroll
               for (int off = 32; off > 0; off >>= 1) len = max(len, __shfl_xor(len, off));
-              k = max(0, seg + wv * kSplitShare - row_steps);
-              kend = seg + (wv + 1) * kSplitShare - row_steps;
+              // counted from the pass's first step of the run
+              const int from = max(0, seg - row_steps);
+              j += from * kBatchF;
+              k = max(0, seg + wv * kSplitShare - row_steps - from);
+              kend = seg + (wv + 1) * kSplitShare - row_steps - from;
               row_steps += len / kBatchF;
             }
             const float ax = fmaf((float)-ix, pc.L[0], t.L.xa);
@@ -1068,7 +1071,7 @@ struct PairSplitF32 {
             };
             j += k * kBatchF;
             load(j);
-            for (; ns >= 0 && k < kend && __any(j < j1); ++k) {
+            for (; ns >= 0 && (!single || k < kend) && __any(j < j1); ++k) {
               if (ns == kSplitSteps) {
                 ns = -1;
                 break;
@@ -1087,7 +1090,7 @@ struct PairSplitF32 {
                 m |= ((b < rem) & (r2 < pc.a2f)) ? 1 << b : 0;
               }
               mask[(wv * kSplitSteps + ns) * W + lane] = (unsigned char)m;
-              if (lane == 0) place[wv * kSplitSteps + ns] = (2 * r + h) | (k << 6);
+              if (lane == 0) place[wv * kSplitSteps + ns] = (unsigned short)((2 * r + h) | (k << 6));
               nh += __builtin_popcount(m);
               ++ns;
               j += kBatchF;
